@@ -426,3 +426,104 @@ def tolerance(case):
     if case["dtype"] == "f32":
         return {"rel": 3e-6, "max": 2e-5, "differ": 0.002}
     return {"rel": 1e-2, "max": 6e-2, "differ": 0.002}
+
+
+# ------------------------------------------------------------------ the same results from plain torch in 64 bits
+
+def _clamped(parent):
+    return [-1] + [p if 0 <= p < i else 0 for i, p in enumerate(parent) if i > 0]
+
+
+def _sees(parent, gamma):
+    """Which of a sequence's new rows each of them sees: a main row its ancestors and itself, a stream row those and the
+    node's streams up to its own."""
+    t = len(parent)
+    up = torch.zeros(t, t, dtype=torch.bool)
+    for i, p in enumerate(_clamped(parent)):
+        if p >= 0:
+            up[i] = up[p]
+        up[i, i] = True
+    see = torch.zeros(t * (1 + gamma), t * (1 + gamma), dtype=torch.bool)
+    see[:t, :t] = up
+    for i in range(t):
+        for j in range(gamma):
+            see[t + i * gamma + j, :t] = up[i]
+            see[t + i * gamma + j, t + i * gamma:t + i * gamma + j + 1] = True
+    return see.to(DEVICE)
+
+
+def _exact_attention(case, s, x, trees):
+    """Attention of one layer; trees: (parents, rows that count) of every sequence."""
+    out = torch.zeros_like(x["out"], dtype=torch.float64)
+    table, lens, page, g = s["table"].cpu(), s["lens"].cpu(), case["page"], case["h"] // case["hkv"]
+    for i, (parent, rows) in enumerate(trees):
+        n = int(lens[i])
+        pages, see = table[i, :-(-n // page)].long().to(DEVICE), _sees(parent, case["gamma"])[rows]
+        for j in range(case["hkv"]):
+            k = torch.cat([x["k_cache"][pages, j].reshape(-1, case["d"])[:n], x["k_new"][i, :, j]]).double()
+            v = torch.cat([x["v_cache"][pages, j].transpose(1, 2).reshape(-1, case["d"])[:n], x["v_new"][i, :, j]]).double()
+            for h in range(j * g, (j + 1) * g):
+                score = (x["q"][i, rows, h].double() @ k.T) * s["scale"]
+                score[:, n:].masked_fill_(~see, -math.inf)
+                out[i, rows, h] = torch.softmax(score, 1) @ v
+    return out
+
+
+def _product(x, W):
+    """x . W^T, a slice of W at a time."""
+    return torch.cat([x.double() @ w.double().T for w in W.split(4096)], 1)
+
+
+_TAIL = ("n_accept", "last", "bonus", "path", "out_tokens", "next_tok", "next_parent")
+
+
+def _exact_step(case, s):
+    trees = [(p, slice(None)) for p in s["parent"].cpu().tolist()]
+    outs = [_exact_attention(case, s, x, trees) for x in s["layers"]]
+    return (outs, dict.fromkeys(_TAIL + ("main_argmax",))) if case["vocab"] else outs
+
+
+def _exact_layer(case, s):
+    return [_product(m["x"], m["W"]) for m in s["maps"]]
+
+
+def _exact_entry(case, s):
+    b, t, gamma = case["b"], case["t"], case["gamma"]
+    logits = _product(s["exit_h"], s["W"])
+    lse = torch.logsumexp(logits, 1)
+    parent, tok = s["parent"].cpu().tolist(), s["tok"].cpu().tolist()
+    prob = torch.ones(b, t, dtype=torch.float64, device=DEVICE)
+    for i in range(b):
+        for c, p in enumerate(_clamped(parent[i])):
+            if c:
+                prob[i, c] = torch.exp(logits[i * t + p, tok[i][c]] - lse[i * t + p])
+    m, p = _product(s["M"].view(b * t, -1), s["Wqkv"]).view(b, t, -1), _product(s["P"], s["Wqkv"])
+    streams = (m[:, :, None] + p).view(b, t * gamma, -1)
+    return lse, prob, dict.fromkeys(("keep", "tok", "parent", "old_index", "n_nodes")), torch.cat([m, streams], 1)
+
+
+def _exact_pruned(case, s):
+    t, gamma, trees, live = case["t"], case["gamma"], [], []
+    for i, (parent, prob) in enumerate(zip(s["parent"].cpu().tolist(), s["prob"].cpu().tolist())):
+        new, old = {}, _clamped(parent)
+        for c in range(t):
+            if c == 0 or (old[c] in new and prob[c] >= 0.05):
+                new[c] = len(new)
+        n = len(new)
+        rows = list(range(n)) + list(range(t, t + n * gamma))
+        trees.append(([new.get(old[c], -1) for c in new] + [0] * (t - n), torch.tensor(rows, device=DEVICE)))
+        live += [i * t * (1 + gamma) + r for r in rows]
+    layers = []
+    for x in s["layers"]:
+        out, y = _exact_attention(case, s, x, trees), torch.zeros_like(x["y"], dtype=torch.float64)
+        y[live] = _product(out.view(len(y), -1)[live], x["Wo"])
+        layers.append((out, y))
+    return layers, None, dict.fromkeys(_TAIL)
+
+
+def exact(case, seed):
+    """The outputs that are computed numbers; tokens, trees and copied bytes have no such value."""
+    if case["kind"] == "commit":
+        return None
+    kinds = dict(step=_exact_step, layer=_exact_layer, entry=_exact_entry, pruned=_exact_pruned)
+    return kinds[case["kind"]](case, prepare(case, seed)[1])
