@@ -17,14 +17,23 @@ struct MsaArgs {
   const int32_t* parent;
   const int32_t* n_nodes;  // [B] kept nodes per sequence after pruning (rows of the others are not computed), or NULL
   void* out;
-  float* part_o;    // [B,H,S,R,D]  per-split outputs, already divided by their own sum
-  float* part_lse;  // [B,H,S,R]    log2-domain log-sum-exp of each split
+  float* part_o;    // [slots,H,R,D]  per-split outputs, already divided by their own sum; split s of sequence b is
+                    // slot b*S + s, or where the device cuts the sequences (below) the slot after the earlier splits
+  float* part_lse;  // [slots,H,R]    log2-domain log-sum-exp of each split
   int B, T, gamma, R, H, Hkv, g, D;
   int page, page_shift, max_pages, num_pages;
   int split_keys;  // cached tokens per split (multiple of 32; of 64 for the fp32 kernel)
   int split0_keys; // cached tokens of split 0 (MFMA path: shorter, that split also scans the step's own rows)
   int n_splits;    // S: upper bound on splits per sequence
   int n_qc;        // query-row chunks per (sequence, KV head) (MFMA path)
+  int2* cut_table;  // [B] adaptive calls: splits and first slot of every sequence, which workgroup 0 of the attention
+                    // kernel leaves in the workspace for the merge kernel; else NULL
+  int adaptive;    // 1: a batch the host's split lengths do not fit is cut anew on the device (plan_uneven)
+  int even_len;    // 7/8 of the capacity, in tokens
+  int new_units;   // blocks' worth of time that scanning the step's own rows costs split 0
+  int max_n;       // most splits per sequence plan_uneven may make (2: merged in the kernel; else 0 = no limit)
+  int min_units;   // shortest split plan_uneven considers, in blocks
+  int chunk_rows;  // folded query rows per row chunk (MFMA path)
   int groups;      // wave groups per workgroup the plan asks for (MFMA path)
   int stages;      // ring stages per wave group the plan asks for (MFMA path)
   unsigned int* arrive;  // MFMA path, two splits merged inside the kernel: arrival counters [B,Hkv,n_qc,kArriveTiles] in the
@@ -44,6 +53,73 @@ SS_DEV int active_splits(int L, const MsaArgs& a) {
 SS_DEV int kept_nodes(int b, const MsaArgs& a) { return a.n_nodes ? min(max(a.n_nodes[b], 1), a.T) : a.T; }
 SS_DEV int split_begin(int s, const MsaArgs& a) { return s == 0 ? 0 : a.split0_keys + (s - 1) * a.split_keys; }
 SS_DEV int split_len(int s, const MsaArgs& a) { return s == 0 ? a.split0_keys : a.split_keys; }
+
+// ---- splits cut on the device.  The host plans from the capacity of the block table; what the sequences really
+// hold (and, after pruning, how many row chunks they have) is known on the device only.  As long as every sequence
+// fills at least 7/8 of the capacity and no node was removed, the host's lengths are within that much of the best
+// and are used as they are.  Otherwise the lengths are chosen here, by one wavefront, from 64 candidates: the one
+// with the least (rounds of 256 workgroups) x (blocks per workgroup + 4, its fixed cost), among those whose splits
+// fit the B x S slots of the workspace.  Lane b holds sequence b, so this is for B <= kAdaptiveMaxB.
+// Measured with the merge kernel, per layer: two sequences of 9005 and 3001 tokens (8 KV heads of 4 query heads, 24
+// nodes) in a table of 1.8 times the capacity 63 -> 48 us; eight of 2000..8192 tokens with a third to two thirds of
+// 32 nodes kept 217 -> 168 us.
+constexpr int kAdaptiveMaxB = 64;
+SS_DEV int len_units(int L, const MsaArgs& a) { return (clamp_len(L, a) + 31) >> 5; }
+SS_DEV bool plan_is_even(const MsaArgs& a, int lane, int len, int kept) {
+  return __all(lane >= a.B || (len >= a.even_len && kept == a.T));
+}
+SS_DEV int wave_sum(int v) {
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+SS_DEV int wave_scan(int v, int lane) {  // inclusive
+  for (int off = 1; off < 64; off <<= 1) {
+    const int o = __shfl_up(v, off, 64);
+    if (lane >= off) v += o;
+  }
+  return v;
+}
+// Of the lane's sequence: cached blocks of split 0 and of the others, number of splits, row chunks with kept rows.
+struct SeqCut {
+  int split0, split, n, chunks;
+};
+SS_DEV SeqCut plan_uneven(const MsaArgs& a, int lane, int U, int kept) {
+  const bool mine = lane < a.B;
+  const int x = mine ? U + a.new_units : 0;
+  SeqCut r;
+  r.chunks = mine ? (a.g * kept * (1 + a.gamma) + a.chunk_rows - 1) / a.chunk_rows : 0;
+  int x_max = x;
+  for (int off = 32; off > 0; off >>= 1) x_max = max(x_max, __shfl_xor(x_max, off, 64));
+  const int slots_max = a.B * a.n_splits;
+  // rounding the sum down keeps every candidate worth a look; what does not fit the slots is dropped below
+  // (the merge inside the attention kernel takes two splits of a sequence at most)
+  const int fill = (int)((float)wave_sum(x) / (float)slots_max), floor2 = a.max_n == 2 ? (x_max + 1) / 2 : 1;
+  const int lo = max(max(a.min_units, fill), floor2), hi = max(x_max, lo);
+  // lane j's candidate: geometric steps from lo to hi; the last leaves every sequence whole, which always fits
+  int c = lane == 63 ? hi : min(hi, (int)((float)lo * __builtin_amdgcn_exp2f(__log2f((float)hi / (float)lo) * ((float)lane * (1.f / 63.f)))));
+  c = (max(c, lo) + a.groups - 1) / a.groups * a.groups;
+  const float rc = 1.f / (float)c;
+  int slots = 0, wgs = 0;
+  for (int i = 0; i < a.B; ++i) {
+    const int up = __builtin_amdgcn_readlane(x, i) + c - 1;
+    int q = (int)((float)up * rc);  // off by one at most
+    const int rem = up - q * c;
+    q += (rem >= c) - (rem < 0);
+    slots += q;
+    wgs += q * __builtin_amdgcn_readlane(r.chunks, i);
+  }
+  const int rounds = (wgs * a.Hkv + 255) >> 8;
+  const float cost = slots <= slots_max ? (float)rounds * (float)(c + 4) : INFINITY;
+  float best = cost;
+  for (int off = 32; off > 0; off >>= 1) best = fminf(best, __shfl_xor(best, off, 64));
+  const int win = 63 - __builtin_clzll(__ballot(cost == best));  // the longest splits among equals
+  const int cut = __builtin_amdgcn_readlane(c, win);
+  const int q = max(1, (x + cut - 1) / cut), even = (x + q - 1) / q;
+  r.split = max((even + a.groups - 1) / a.groups, 1) * a.groups;
+  r.split0 = max(0, r.split - a.new_units);
+  r.n = !mine ? 0 : U <= r.split0 ? 1 : 1 + (U - r.split0 + r.split - 1) / r.split;  // <= q
+  return r;
+}
 
 // Arrival counters of the in-kernel split merge: one per (sequence, KV head, row chunk, query tile of at most
 // kArriveTiles per chunk).

@@ -160,7 +160,7 @@ __global__ __launch_bounds__(256) void msa_f32_kernel(MsaArgs a) {
 #pragma unroll
       for (int dd = 0; dd < DL; ++dd) out[lane + 64 * dd] = o[i][dd] * inv;
     } else {
-      const size_t pr = (((size_t)b * a.H + h) * a.n_splits + s) * R + row;
+      const size_t pr = (((size_t)b * a.n_splits + s) * a.H + h) * R + row;
 #pragma unroll
       for (int dd = 0; dd < DL; ++dd) a.part_o[pr * D + lane + 64 * dd] = o[i][dd] * inv;
       if (lane == 0) a.part_lse[pr] = m[i] + log2f(l[i]);
@@ -173,7 +173,8 @@ __global__ __launch_bounds__(256) void msa_f32_kernel(MsaArgs a) {
 // out = sum_s w_s * o_s with w_s = 2^(lse_s - max) / sum.  One thread per (sequence, row, head,
 // 4 features).  The partial outputs are fetched four splits at a time without waiting for the
 // log-sum-exps (their addresses do not depend on them) and folded in with a running maximum, so the
-// kernel is one round of independent loads deep; splits a sequence does not use are never read.
+// kernel is one round of independent loads deep for each four splits; what lies in the place of a split that a
+// sequence does not have may be fetched but is not used.
 template <bool BF16>
 __global__ __launch_bounds__(256) void msa_combine_kernel(MsaArgs a) {
   const int dq = a.D >> 2;  // threads per row
@@ -185,20 +186,33 @@ __global__ __launch_bounds__(256) void msa_combine_kernel(MsaArgs a) {
   const int r = (item / a.H) % a.R;
   const int b = item / ((long)a.H * a.R);
   if ((r < a.T ? r : (r - a.T) / max(a.gamma, 1)) >= kept_nodes(b, a)) return;  // rows of removed nodes: no partials, not written
-  const int n_active = active_splits(clamp_len(a.seq_lens[b], a), a);
-  const size_t base = (((size_t)b * a.H + h) * a.n_splits) * a.R + r;
-  float m = -INFINITY, wsum = 0.f;
-  floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
-  for (int s0 = 0; s0 < n_active; s0 += 4) {
-    floatx4 v[4];
-    float l[4];
+  const size_t stride = (size_t)a.H * a.R, row0 = (size_t)h * a.R + r;  // rows from a slot to the next, row in a slot
+  // The first four splits are fetched where the host's cut puts them, before it is known whether that stands and how
+  // many the sequence has: one round of loads less to wait for.
+  floatx4 v[4];
+  float l[4];
+  auto fetch = [&](int slot0, int s0, int n) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int s = min(s0 + i, n_active - 1);
-      const size_t row = base + (size_t)s * a.R;
+      const size_t row = (size_t)(slot0 + min(s0 + i, n - 1)) * stride + row0;
       v[i] = *reinterpret_cast<const floatx4*>(a.part_o + row * a.D + d0);
       l[i] = a.part_lse[row];
     }
+  };
+  fetch(b * a.n_splits, 0, a.n_splits);
+  int n_active, slot0 = b * a.n_splits;
+  if (BF16 && a.cut_table) {
+    const int2 cut = a.cut_table[b];
+    n_active = min(max(cut.x, 1), a.B * a.n_splits);  // clamped: whatever the workspace holds, what is read lies in it
+    slot0 = min(max(cut.y, 0), a.B * a.n_splits - n_active);
+    if (slot0 != b * a.n_splits || n_active > a.n_splits) fetch(slot0, 0, n_active);
+  } else {
+    n_active = active_splits(clamp_len(a.seq_lens[b], a), a);
+  }
+  float m = -INFINITY, wsum = 0.f;
+  floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int s0 = 0; s0 < n_active; s0 += 4) {
+    if (s0 > 0) fetch(slot0, s0, n_active);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       if (s0 + i < n_active && l[i] > -INFINITY) {
@@ -227,7 +241,8 @@ static std::atomic<int> g_merge_in_kernel{1};
 
 struct MsaPlan {
   int split_keys, split0_keys, n_splits, n_qc, groups, stages;
-  size_t part_o_bytes, part_lse_bytes, arrive_bytes, total_bytes;
+  int adaptive, new_units, min_units, chunk_rows;
+  size_t part_o_bytes, part_lse_bytes, arrive_bytes, table_bytes, total_bytes;
 };
 
 // Chooses the split length from the shape alone (sequence lengths live on the device).  Every split
@@ -320,6 +335,14 @@ static MsaPlan make_plan(int B, int R, int H, int Hkv, int D, int max_len, int d
       p.split0_keys = 32 * (nu - (n - 1) * rest);
     }
   }
+  // Cutting on the device needs slots to deal out and a lane per sequence; a caller's split length stays.  With one
+  // row chunk a launch is so short that waiting for the lengths costs 1 us of 16 even where the host's cut stands
+  // (one sequence of 2048 tokens, 32 heads; 2 % of a step), so those keep the host's cut.
+  p.adaptive = dtype == SS_BF16 && p.n_qc > 1 && p.n_splits > 1 && !overridden && B <= kAdaptiveMaxB;
+  p.new_units = ceil_div(R, 32) + split0_extra_blocks();
+  if (p.new_units < 0) p.new_units = 0;
+  p.min_units = base >= 256 ? 16 : 8;  // the more rounds a launch has, the less a short split gains it
+  p.chunk_rows = dtype == SS_BF16 ? msa_bf16_rows_per_chunk(g * R) : 32;
   if (p.n_splits > 1) {
     p.part_o_bytes = align_up((size_t)B * H * p.n_splits * R * D * sizeof(float), 256);
     p.part_lse_bytes = align_up((size_t)B * H * p.n_splits * R * sizeof(float), 256);
@@ -328,7 +351,8 @@ static MsaPlan make_plan(int B, int R, int H, int Hkv, int D, int max_len, int d
   } else {
     p.part_o_bytes = p.part_lse_bytes = p.arrive_bytes = 0;
   }
-  p.total_bytes = p.part_o_bytes + p.part_lse_bytes + p.arrive_bytes + 256;
+  p.table_bytes = p.adaptive ? kAdaptiveMaxB * sizeof(int2) : 0;
+  p.total_bytes = p.part_o_bytes + p.part_lse_bytes + p.arrive_bytes + p.table_bytes + 256;
   return p;
 }
 
@@ -375,7 +399,7 @@ static int zero_bytes(unsigned char* p, size_t bytes, hipStream_t st, const char
 // the array; host code reaches it only through the address hipGetSymbolAddress reports for the device that
 // is current, looked up once per device.
 constexpr size_t kStaticScratchBytes = (size_t)32 << 20;
-static __device__ __align__(256) unsigned char g_msa_scratch[kStaticScratchBytes];
+static __device__ __align__(256) unsigned char g_msa_scratch[kStaticScratchBytes + kAdaptiveMaxB * sizeof(int2)];  // ... and the table of cuts
 constexpr int kMaxDevices = 64;
 static std::mutex g_scratch_mutex;
 static void* g_scratch_ptr[kMaxDevices];  // guarded by g_scratch_mutex
@@ -428,9 +452,10 @@ static int msa_run(const char* fn, const void* q, const void* k_new, const void*
   const int max_len = max_pages_per_seq * page_size;
   const MsaPlan plan = make_plan(B, R, H, Hkv, D, max_len, dtype);
   if (library_scratch) {
-    SS_REQUIRE(plan.total_bytes <= workspace_bytes, SS_ERR_UNSUPPORTED,
+    const size_t need = plan.total_bytes - plan.table_bytes;  // the table has a place of its own behind the array's bytes
+    SS_REQUIRE(need <= workspace_bytes, SS_ERR_UNSUPPORTED,
                "%s: this shape needs %zu bytes of scratch memory, the library's array holds %zu; use "
-               "ss_msa_attention with a workspace", fn, plan.total_bytes, workspace_bytes);
+               "ss_msa_attention with a workspace", fn, need, workspace_bytes);
   } else {
     SS_REQUIRE(plan.n_splits == 1 || (workspace != nullptr && workspace_bytes >= plan.total_bytes), SS_ERR_WORKSPACE,
                "%s: workspace of %zu bytes needed, %zu given", fn, plan.total_bytes, workspace_bytes);
@@ -446,6 +471,9 @@ static int msa_run(const char* fn, const void* q, const void* k_new, const void*
   a.page = page_size; a.page_shift = page_size == 16 ? 4 : (page_size == 32 ? 5 : 6);
   a.max_pages = max_pages_per_seq; a.num_pages = num_pages;
   a.split_keys = plan.split_keys; a.split0_keys = plan.split0_keys; a.n_splits = plan.n_splits; a.n_qc = plan.n_qc; a.groups = plan.groups; a.stages = plan.stages;
+  a.max_n = plan.n_splits == 2 && dtype == SS_BF16 ? 2 : 0;  // also where the merge kernel does it: the same cut either way
+  a.even_len = max_len - max_len / 8;
+  a.adaptive = plan.adaptive; a.new_units = plan.new_units; a.min_units = plan.min_units; a.chunk_rows = plan.chunk_rows;
   a.scale_log2 = scale * 1.4426950408889634f;
   // In-kernel merge (MFMA path, two splits): the second split of a (sequence, head) to finish adds the other's
   // partial rows to its own and writes the output, which saves the merge kernel and its kernel boundary.  With
@@ -453,6 +481,7 @@ static int msa_run(const char* fn, const void* q, const void* k_new, const void*
   a.arrive = nullptr;
   if (merges_in_kernel(plan, dtype) && !(flags & SS_MSA_MERGE_ONLY))
     a.arrive = (unsigned int*)(ws + plan.part_o_bytes + plan.part_lse_bytes);
+  a.cut_table = plan.adaptive ? (int2*)(ws + plan.part_o_bytes + plan.part_lse_bytes + plan.arrive_bytes) : nullptr;
   a.flags = flags;
   hipStream_t st = (hipStream_t)stream;
 

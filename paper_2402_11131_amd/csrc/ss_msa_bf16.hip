@@ -182,13 +182,25 @@ SS_DEV void wait_vm_units(int units) {
 }
 constexpr int kMaxStages = 10;  // ring stages per wave group: at most kMaxStages - 1 blocks in flight per group
 
+// The kernel's arguments, to be read from memory again from here on.  Kept in scalar registers from the start of the
+// kernel to its end, over the code that cuts a batch anew, they do not fit, and what is pushed out there is paid for
+// by every launch, also where the host's cut stands (1.5 us).
+template <bool YES>
+SS_DEV const MsaArgs& reread_args(const MsaArgs& args) {
+  if constexpr (!YES) return args;
+  auto p = __builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const MsaArgs*)p;
+}
+
 // NW = waves (query tiles) per group; it only fixes how the 1 KB load slots of a unit are dealt to
 // the waves of a group.  The number of groups and the ring depth are launch parameters.
 // STREAM: the cache is loaded with the streaming hint.  Right when a (sequence, KV head, split) has one row
 // chunk, so that every byte of the cache is wanted by exactly one workgroup; with several row chunks (long GQA
 // trees) the chunks share K/V through the L2 and the hint undoes that (measured: +25 % time).
 template <int D, int NW, bool STREAM>
-__global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves / NW : kMaxGroups)) void msa_bf16_kernel(MsaArgs a, int n_groups, int n_stages) {
+__global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves / NW : kMaxGroups)) void msa_bf16_kernel(MsaArgs args, int n_groups, int n_stages) {
+  constexpr bool CUTS = !STREAM;               // the device may cut the batch anew (several row chunks)
   constexpr int KS = D / 32, DT = D / 16;
   constexpr int K_BYTES = 32 * D * 2;          // K rows of a unit (V takes the same)
   constexpr int STAGE_BYTES = 2 * K_BYTES;
@@ -203,44 +215,28 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
 
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   // smem: [n_groups][n_stages][STAGE_BYTES] ring stages, overlaid by the buffer of the final merge of the groups
-  // ([n_groups - 1][NW][DT] KB); behind the larger of the two: par | anc | ml
+  // ([n_groups - 1][NW][DT] KB); behind the larger of the two: par (first used for `cut`) | anc | ml
   unsigned char* stages = smem;
   const int ring_bytes = n_groups * n_stages * STAGE_BYTES, merge_bytes = (n_groups - 1) * NW * DT * 1024;
   int* par = reinterpret_cast<int*>(smem + max(ring_bytes, merge_bytes));
   uint64_t* anc = reinterpret_cast<uint64_t*>(par + SS_MAX_T);
   float* ml = reinterpret_cast<float*>(anc + SS_MAX_T);  // [n_groups][NW][2][16]: max, sum per query
-
-  // ---- which piece of work: XCD-aware order.  Workgroup ids go round-robin over
-  // the 8 XCDs, so ids that are equal mod 8 share an L2: the query chunks of one
-  // (sequence, KV head, split) are given such ids and read K/V through one L2.
-  const int G = a.B * a.Hkv * a.n_splits;
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int qc = slot % a.n_qc;
-  const int group = (slot / a.n_qc) * 8 + xcd;
-  if (group >= G) return;
-  const int s = group % a.n_splits;
-  const int hk = (group / a.n_splits) % a.Hkv;
-  const int b = group / (a.n_splits * a.Hkv);
+  int* cut = par;                                        // [8]: this workgroup's piece where the device cuts the sequences
 
   // The wave index is made known to be wave-uniform, so that everything derived from it (unit, load
   // slots, base addresses) is computed on the scalar unit.
   const int tid = threadIdx.x, lane = tid & 63, lq = lane & 15, lg = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = w / NW, wt = w % NW;  // wave group, query tile of this wave
-  const int R = a.R, T = a.T, F = a.g * R;
-  const int k0 = split_begin(s, a);     // this split's cached tokens are [k0, k1)
-  const float c = a.scale_log2;
-
-  const uint16_t* q = (const uint16_t*)a.q;
-  const int32_t* my_table = a.block_table + (size_t)b * a.max_pages;
-  const size_t page_stride = (size_t)a.Hkv * a.page * D;  // elements per physical page (K and V alike)
-  const uint16_t* k_head = (const uint16_t*)a.k_cache + (size_t)hk * a.page * D;  // this head inside page 0
-  const uint16_t* v_head = (const uint16_t*)a.v_cache + (size_t)hk * a.page * D;
-  const int pmask = a.page - 1;
-
+  const bool loader = wt < LW;
+  const int wl = loader ? wt : 0;
   unsigned char* my_stages = stages + (size_t)grp * n_stages * STAGE_BYTES;
   const uint32_t lds_stages = (uint32_t)(uintptr_t)my_stages;
+  const uint32_t new_stage = lds_stages + (uint32_t)(n_stages - 1) * STAGE_BYTES;
 
+  // This workgroup's piece: splits of the sequence (0: not known yet) and the first one's slot, lengths of split 0 and
+  // of the others; this split's cached tokens are [k0, k1).
+  int b, hk, s, qc, n_active = 0, slot0, split0_keys, split_keys, k0;
   // ---- first round trip: page ids, sequence length, tree, queries.
   // Physical pages of the two 16-key halves of this group's main-loop units (equal for pages of 32
   // or 64 tokens; positions past the table are clamped, such units are never used).  Lane i of every
@@ -249,39 +245,160 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
   // What is kept is the page's offset in the cache in units of 256 bytes (a page of one head is at least
   // 16 x 64 x 2 bytes, and 2^32 such units are 1 TB), so that the scalar unit needs a shift, not a 64-bit product.
   uint32_t tab_a = 0, tab_b = 0;
-  const uint32_t page_units = (uint32_t)(page_stride / 128);
-  const int key_cap = max(a.max_pages * a.page - 32, 0) & ~31;  // last 32-key block the table covers
-  auto refill_pages = [&](int jbase) {
+  const int32_t* my_table;
+  auto refill_pages = [&](const MsaArgs& a, int jbase) {
+    const uint32_t page_units = (uint32_t)((size_t)a.Hkv * a.page * D / 128);
+    const int key_cap = max(a.max_pages * a.page - 32, 0) & ~31;  // last 32-key block the table covers
     const int kb = min(k0 + 32 * (grp + (jbase + lane) * n_groups), key_cap);
     tab_a = (uint32_t)min(max(my_table[kb >> a.page_shift], 0), a.num_pages - 1) * page_units;
     tab_b = (uint32_t)min(max(my_table[min((kb + 16) >> a.page_shift, a.max_pages - 1)], 0), a.num_pages - 1) * page_units;
   };
-  refill_pages(0);
-  const int L_raw = a.seq_lens[b];
-  const int n_kept = kept_nodes(b, a);
-  int par_v = tid < T ? clamp_parent(a.parent[(size_t)b * T + tid], tid) : 0;
-
   // this wave's query tile: MFMA B operands (lane (lq, lg) holds features 8*(4*ks+lg).. of folded query row f)
   // Rows of nodes that pruning removed are neither computed nor written: the folded row index runs over the
   // kept rows only (per query head the n_kept main rows, then the n_kept*gamma stream rows of those nodes), so
   // the kept rows fill the first row chunks and the workgroups of the others leave at once.
-  const int R_kept = n_kept * (1 + a.gamma);
-  if (qc * (16 * NW) >= a.g * R_kept) return;
-  const int f = qc * (16 * NW) + 16 * wt + lq;
-  const bool f_valid = f < a.g * R_kept;
-  const int f_row = f_valid ? f % R_kept : 0;
-  const int q_r = f_row < n_kept ? f_row : T + (f_row - n_kept), q_h = hk * a.g + (f_valid ? f / R_kept : 0);
+  int L_raw, n_kept, R_kept, par_v, q_r, q_h;
+  bool f_valid, has_new;  // every sequence has a split 0, which scans the step's own rows
   bf16x8 Qr[KS];
+
+  // Rows c0 .. c0+31 of the step's own block -> LDS stage at st_addr: K rows as above, V rows token-major
+  // (row r at 2*D*r, chunk position p holding chunk p ^ 2*(r&3)) for the transposing operand read.  Rows past
+  // R repeat the last one (they are masked).  The lane id is laundered so that none of this arithmetic is
+  // kept in registers across the main loop.
+  auto dma_new = [&](const MsaArgs& a, int c0, uint32_t st_addr) {
+    int lane2 = lane;
+    asm volatile("" : "+v"(lane2));
+    const int ril2 = lane2 / CPR, pch2 = lane2 % CPR;
+    const size_t head0 = ((size_t)b * a.R * a.Hkv + hk) * D;  // elements to row 0 of this sequence and head
+    const uint16_t* kn = (const uint16_t*)a.k_new + head0;
+    const uint16_t* vn = (const uint16_t*)a.v_new + head0;
+#pragma unroll
+    for (int j = 0; j < KJ; ++j) {
+      const int sl = wl + LW * j;
+      const int rr = ROWS_PER_SLOT * sl + ril2;
+      const uint32_t row_off = (uint32_t)min(c0 + rr, a.R - 1) * (uint32_t)(a.Hkv * D * 2);
+      dma16<false>(kn, row_off + (uint32_t)((pch2 ^ k_swz<D>(rr)) * 16), st_addr + sl * 1024);
+      dma16<false>(vn, row_off + (uint32_t)((pch2 ^ (2 * (rr & 3))) * 16), st_addr + K_BYTES + sl * 1024);
+    }
+  };
+
   {
-    const uint16_t* qp = q + (((size_t)b * R + q_r) * a.H + q_h) * D + lg * 8;
+  const MsaArgs& a = args;
+  // ---- which piece of work: XCD-aware order.  Workgroup ids go round-robin over
+  // the 8 XCDs, so ids that are equal mod 8 share an L2: the query chunks of one
+  // (sequence, KV head, split) are given such ids and read K/V through one L2.
+  const int G = a.B * a.Hkv * a.n_splits;
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  qc = slot % a.n_qc;
+  int group = (slot / a.n_qc) * 8 + xcd;
+  const bool spare = group >= G;  // has a piece at most where the device cuts the sequences
+  if (spare && !(CUTS && a.adaptive)) return;
+  group = min(group, G - 1);
+  s = group % a.n_splits;
+  hk = (group / a.n_splits) % a.Hkv;
+  b = group / (a.n_splits * a.Hkv);
+  split0_keys = a.split0_keys;
+  split_keys = a.split_keys;
+  slot0 = b * a.n_splits;
+
+  // Split 0's first block of the step's own rows travels with the first round trip (its addresses need
+  // nothing from memory), into the last ring stage, which the main loop does not fill before its first barrier.
+  // Where the device may cut the sequences, the lengths of all of them travel with the first trip, which goes out for
+  // the host's cut: if that stands nothing is lost.  Otherwise one wave cuts anew and finds this workgroup's piece,
+  // and the trip is made again.  Pieces keep the order above: those of one sequence together, the splits of a head
+  // next to each other, the live row chunks of a (sequence, KV head, split) on one XCD.
+  int lane_len = 0, lane_kept = a.T;
+  if (CUTS && a.adaptive && lane < a.B) {
+    lane_len = a.seq_lens[lane];
+    lane_kept = kept_nodes(lane, a);
+  }
+#pragma unroll 1
+  for (bool first = true;; first = false) {
+    const MsaArgs& a = reread_args<CUTS>(args);
+    k0 = s == 0 ? 0 : split0_keys + (s - 1) * split_keys;
+    my_table = a.block_table + (size_t)b * a.max_pages;
+    refill_pages(a, 0);
+    L_raw = a.seq_lens[b];
+    n_kept = kept_nodes(b, a);
+    par_v = tid < a.T ? clamp_parent(a.parent[(size_t)b * a.T + tid], tid) : 0;
+    R_kept = n_kept * (1 + a.gamma);
+    const int f = qc * (16 * NW) + 16 * wt + lq;
+    f_valid = f < a.g * R_kept;
+    const int f_row = f_valid ? f % R_kept : 0;
+    q_r = f_row < n_kept ? f_row : a.T + (f_row - n_kept);
+    q_h = hk * a.g + (f_valid ? f / R_kept : 0);
+    const uint16_t* qp = (const uint16_t*)a.q + (((size_t)b * a.R + q_r) * a.H + q_h) * D + lg * 8;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       uintx4 u = uintx4{0u, 0u, 0u, 0u};
       if (f_valid) u = ld16(qp + 32 * ks);
       Qr[ks] = as_bf16x8(u);
     }
+    has_new = s == 0 && !(spare && n_active == 0) && qc * (16 * NW) < a.g * R_kept;
+    if (has_new && loader && grp < (a.R + 31) >> 5) dma_new(a, 32 * grp, new_stage);
+    if (!CUTS || !first || !a.adaptive) break;
+    const bool even = plan_is_even(a, lane, lane_len, lane_kept);
+    if (even) {
+      if (blockIdx.x == 0 && w == 0 && lane < a.B)
+        a.cut_table[lane] = make_int2(active_splits(clamp_len(lane_len, a), a), lane * a.n_splits);
+      if (spare) return;
+      break;
+    }
+    const int U = len_units(lane_len, a);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing of the abandoned trip is under way to LDS
+    if (w == 0) {
+      const MsaArgs& a = reread_args<CUTS>(args);
+      const SeqCut r = plan_uneven(a, lane, U, lane_kept);
+      const int slots = wave_scan(r.n, lane), groups0 = (slots - r.n) * a.Hkv;  // pieces of earlier sequences
+      const int skip = (groups0 + 7 - xcd) >> 3;    // this XCD takes the pieces that are xcd mod 8
+      const int here = (((slots * a.Hkv + 7 - xcd) >> 3) - skip) * r.chunks;
+      const int upto = wave_scan(here, lane);
+      const int bb = __popcll(__ballot(upto <= slot));
+      if (blockIdx.x == 0 && lane < a.B) a.cut_table[lane] = make_int2(r.n, slots - r.n);
+      if (lane == 0) cut[0] = bb;  // 64: none
+      if (lane == bb) {
+        const int at = slot - (upto - here);
+        const int piece = 8 * (skip + at / r.chunks) + xcd - groups0;
+        cut[1] = piece % r.n;
+        cut[2] = piece / r.n;
+        cut[3] = at % r.chunks;
+        cut[4] = r.n;
+        cut[5] = 32 * r.split0;
+        cut[6] = 32 * r.split;
+        cut[7] = slots - r.n;
+      }
+    }
+    __syncthreads();
+    b = __builtin_amdgcn_readfirstlane(cut[0]);
+    if (b >= 64) return;
+    s = __builtin_amdgcn_readfirstlane(cut[1]);
+    hk = __builtin_amdgcn_readfirstlane(cut[2]);
+    qc = __builtin_amdgcn_readfirstlane(cut[3]);
+    n_active = __builtin_amdgcn_readfirstlane(cut[4]);
+    split0_keys = __builtin_amdgcn_readfirstlane(cut[5]);
+    split_keys = __builtin_amdgcn_readfirstlane(cut[6]);
+    slot0 = __builtin_amdgcn_readfirstlane(cut[7]);
+    __syncthreads();  // `cut` is free: the tree's parents go there
+  }
   }
 
+  const MsaArgs& a = reread_args<CUTS>(args);
+  const int R = a.R, T = a.T, F = a.g * R;
+  const float c = a.scale_log2;
+  const size_t page_stride = (size_t)a.Hkv * a.page * D;  // elements per physical page (K and V alike)
+  const uint16_t* k_head = (const uint16_t*)a.k_cache + (size_t)hk * a.page * D;  // this head inside page 0
+  const uint16_t* v_head = (const uint16_t*)a.v_cache + (size_t)hk * a.page * D;
+  const int pmask = a.page - 1;
+  const int n_new_units = (R + 31) >> 5;
+
+  // ---- what there is to do.  The sequence length arrives with the page ids.
+  if (qc * (16 * NW) >= a.g * R_kept) return;
+  const int L = clamp_len(L_raw, a);
+  if (n_active == 0) {
+    n_active = active_splits(L, a);
+    if (s >= n_active) return;
+  }
+  const int k1 = max(k0, min(L, k0 + (s == 0 ? split0_keys : split_keys)));
   floatx4 O[DT];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) O[dt] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -308,8 +425,6 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
   // (16 features x 16 bytes) hit 64 different banks.  In a feature-major page a slot is one contiguous KB.
   // The first LW waves of a group move the data: wave wt takes K slots and V slots wt + LW*j.
   const int ril = lane / CPR, pch = lane % CPR;
-  const bool loader = wt < LW;
-  const int wl = loader ? wt : 0;
   // Slot sl lies in the second 16-key half of the unit when sl >= K_SLOTS / 2 (K and V alike); its offset inside
   // the half is part of the lane's byte offset, so that a half has one scalar base.
   uint32_t k_voff[KJ], v_voff[KJ];  // per lane, bytes from the half's scalar base
@@ -344,27 +459,6 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
 #pragma unroll
     for (int j = 0; j < KJ; ++j) dma16<STREAM>(second[j] ? vb : va, v_voff[j], slot_addr + K_BYTES + LW * j * 1024);
   };
-  // Rows c0 .. c0+31 of the step's own block -> LDS stage at st_addr: K rows as above, V rows token-major
-  // (row r at 2*D*r, chunk position p holding chunk p ^ 2*(r&3)) for the transposing operand read.  Rows past
-  // R repeat the last one (they are masked).  The lane id is laundered so that none of this arithmetic is
-  // kept in registers across the main loop.
-  auto dma_new = [&](int c0, uint32_t st_addr) {
-    int lane2 = lane;
-    asm volatile("" : "+v"(lane2));
-    const int ril2 = lane2 / CPR, pch2 = lane2 % CPR;
-    const size_t head0 = ((size_t)b * R * a.Hkv + hk) * D;  // elements to row 0 of this sequence and head
-    const uint16_t* kn = (const uint16_t*)a.k_new + head0;
-    const uint16_t* vn = (const uint16_t*)a.v_new + head0;
-#pragma unroll
-    for (int j = 0; j < KJ; ++j) {
-      const int sl = wl + LW * j;
-      const int rr = ROWS_PER_SLOT * sl + ril2;
-      const uint32_t row_off = (uint32_t)min(c0 + rr, R - 1) * (uint32_t)(a.Hkv * D * 2);
-      dma16<false>(kn, row_off + (uint32_t)((pch2 ^ k_swz<D>(rr)) * 16), st_addr + sl * 1024);
-      dma16<false>(vn, row_off + (uint32_t)((pch2 ^ (2 * (rr & 3))) * 16), st_addr + K_BYTES + sl * 1024);
-    }
-  };
-
   // ---- the ragged last block of the prefix goes through registers (per-lane page lookups, clamped to
   // existing keys; what is read in excess is masked).  base = its first cached token, last = the last one.
   uintx4 stg[2 * KJ];
@@ -399,18 +493,6 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
     }
   };
 
-  // Split 0's first block of the step's own rows travels with the first round trip (its addresses need
-  // nothing from memory), into the last ring stage, which the main loop does not fill before its first barrier.
-  const bool has_new = s == 0;  // every sequence has a split 0
-  const int n_new_units = (R + 31) >> 5;
-  const uint32_t new_stage = lds_stages + (uint32_t)(n_stages - 1) * STAGE_BYTES;
-  if (has_new && loader && grp < n_new_units) dma_new(32 * grp, new_stage);
-
-  // ---- what there is to do.  The sequence length arrives with the page ids.
-  const int L = clamp_len(L_raw, a);
-  const int n_active = active_splits(L, a);
-  if (s >= n_active) return;
-  const int k1 = max(k0, min(L, k0 + split_len(s, a)));
   // Units of this split: full 32-key blocks of the prefix (ring-buffered main loop of n_main iterations,
   // one block per group and iteration; group grp has n_mine of them) and its ragged last block.
   const int n_full = (k1 - k0) >> 5;
@@ -540,7 +622,7 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
       const bool mine = un < n_new_units;
       if (jn > 0) {
         __syncthreads();  // the previous round's block has been consumed
-        if (loader && mine) dma_new(32 * un, new_stage);
+        if (loader && mine) dma_new(a, 32 * un, new_stage);
       }
       // round 0: only the prefix blocks issued after it may still be in flight; later rounds: nothing
       if (loader && mine) wait_vm_units<LPB>(jn == 0 ? n_pre : 0);
@@ -563,7 +645,7 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
       __syncthreads();
       const int jl = it + n_stages - 1;
       if (loader && jl < n_mine) {
-        if ((jl & 63) == 0) refill_pages(jl);
+        if ((jl & 63) == 0) refill_pages(a, jl);
         dma_main(grp + jl * n_groups, __builtin_amdgcn_readlane(tab_a, jl & 63), __builtin_amdgcn_readlane(tab_b, jl & 63),
                  lds_stages + (uint32_t)st_fill * STAGE_BYTES);
       }
@@ -623,7 +705,8 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
   const bool prefetched = others_ready && n_active == 2 && f_valid;
   float l_other = -INFINITY;
   floatx4 o_other[DT];
-  const size_t pr_other = (((size_t)b * a.H + q_h) * a.n_splits + s_other) * R + q_r;
+  auto part_row = [&](int sp) { return ((size_t)(slot0 + sp) * a.H + q_h) * R + q_r; };
+  const size_t pr_other = part_row(s_other);
   if (prefetched) ld_row_device<DT>(a.part_lse + pr_other, a.part_o + pr_other * D + 4 * lg, l_other, o_other);
 
   float mm = m_run;
@@ -654,7 +737,7 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
     }
     return;
   }
-  const size_t pr = (((size_t)b * a.H + q_h) * a.n_splits + s) * R + q_r;
+  const size_t pr = part_row(s);
   float* op = a.part_o + pr * D + 4 * lg;
   const float my_lse = mm * c + __log2f(l_run);
 #pragma unroll

@@ -1,0 +1,84 @@
+"""Attention over batches whose lengths do not fill the block table; with several row chunks (the query heads of a
+KV head times the tree's rows beyond 80) the device cuts them into splits itself.  One chunk and several,
+against the oracle (large shapes: against the host's cut, forced), full and pruned trees, one call and two."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from helpers import rel_err, to_np_f32
+from paper_2402_11131_amd import api, synth
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+CASES = {
+    # B, H, Hkv, D, page, T, gamma, lens, columns of the table over the longest sequence's, large
+    "one_short": (1, 4, 1, 128, 16, 5, 1, [300], 6.0, False),
+    "empty_and_odd_heads": (3, 6, 3, 64, 32, 8, 3, [1200, 0, 77], 1.0, False),
+    "merged_in_kernel": (4, 32, 32, 64, 16, 3, 1, [2000, 700, 31, 1500], 1.5, False),
+    "all_lanes": (64, 2, 2, 64, 16, 2, 1, [(i * 37) % 600 for i in range(64)], 1.0, False),
+    "more_than_lanes": (65, 2, 2, 64, 16, 2, 1, [(i * 37) % 600 for i in range(65)], 1.0, False),
+    "chunks_merged_in_kernel": (4, 48, 16, 64, 16, 16, 2, [1100, 513, 0, 700], 1.0, False),
+    "chunks_all_lanes": (64, 4, 1, 64, 16, 8, 2, [(i * 37) % 600 for i in range(64)], 1.0, False),
+    "chunks_more_than_lanes": (65, 4, 1, 64, 16, 8, 2, [(i * 37) % 600 for i in range(65)], 1.0, False),
+    "chunks_three_kv_heads": (3, 12, 3, 128, 32, 8, 3, [1200, 0, 77], 1.5, False),
+    "row_chunks": (2, 8, 1, 128, 64, 24, 3, [1500, 400], 2.0, False),
+    "new_rows_longer_than_a_split": (2, 4, 2, 64, 16, 64, 8, [700, 300], 2.0, False),
+    "many_rounds": (8, 32, 8, 128, 64, 32, 4, [2000, 8192, 3000, 5000, 2500, 33, 7000, 4097], 1.0, True),
+}
+
+
+@pytest.mark.parametrize("pruned", [False, True])
+@pytest.mark.parametrize("name", list(CASES))
+def test_uneven_batches(name, pruned):
+    B, H, Hkv, D, page, T, gamma, lens, room, large = CASES[name]
+    cfg = synth.scaled(synth.CONFIGS["c2"], B=B, H=H, Hkv=Hkv, D=D, page=page, T=T, gamma=gamma, branching=(8, 8),
+                       max_depth=2, L_min=max(lens), L_max=max(lens))
+    inp = synth.make_msa_inputs(cfg, 5, device=DEV if large else None)
+    d = {k: (v.to(DEV) if isinstance(v, torch.Tensor) else v) for k, v in inp.items()}
+    d["seq_lens"] = torch.tensor(lens, dtype=torch.int32, device=DEV)
+    table = d["block_table"]
+    d["block_table"] = torch.zeros(B, int(table.shape[1] * room), dtype=torch.int32, device=DEV)
+    d["block_table"][:, :table.shape[1]] = table
+    nodes = torch.tensor([1 + (i * 5) % T for i in range(B)], dtype=torch.int32) if pruned else None
+    parent = d["parent"].clone()
+    if pruned:
+        for b in range(B):
+            parent[b, int(nodes[b]):] = 0
+    args = (d["q"], d["k_new"], d["v_new"], d["k_cache"], d["v_cache"], d["block_table"], d["seq_lens"], parent, gamma, d["scale"])
+    kw = dict(n_nodes=nodes.to(DEV)) if pruned else {}
+    got = api.ss_msa_attention(*args, out=torch.full_like(d["q"], 3.0), **kw)
+    # the two kernels as two calls give the same bits
+    ws = api.ss_msa_workspace(B, T, gamma, H, Hkv, D, d["block_table"].shape[1] * page, api.SS_BF16, DEV)
+    two = torch.full_like(d["q"], 3.0)
+    merge_kernel = api.ss_msa_plan(B, T, gamma, H, Hkv, D, d["block_table"].shape[1] * page, api.SS_BF16)[0] > 1
+    api.ss_msa_attention(*args, out=two, workspace=ws, flags=api.SS_MSA_PARTIALS_ONLY, **kw)
+    if merge_kernel:
+        api.ss_msa_attention(*args, out=two, workspace=ws, flags=api.SS_MSA_MERGE_ONLY, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(got, two)
+    if large:
+        prev = api.ss_msa_set_split_keys(1024)
+        try:
+            want = to_np_f32(api.ss_msa_attention(*args, out=torch.full_like(d["q"], 3.0), **kw))
+        finally:
+            api.ss_msa_set_split_keys(prev)
+    else:
+        a = [to_np_f32(inp[k]) for k in ("q", "k_new", "v_new", "k_cache", "v_cache")]
+        a += [d["block_table"].cpu().numpy(), np.array(lens, np.int32), parent.cpu().numpy(), gamma, inp["scale"]]
+        want = oracle.msa_attention_pruned(*a, nodes.numpy()) if pruned else oracle.msa_attention(*a)
+    keep = np.ones(B * cfg.R, bool)
+    if pruned:
+        keep[:] = False
+        keep[oracle.live_rows(nodes.numpy(), T, gamma)] = True
+        assert bool((got.view(B * cfg.R, -1)[torch.from_numpy(~keep).to(DEV)] == 3.0).all())
+    keep = keep.reshape(B, cfg.R)
+    # Per sequence, for a short one's values are many times a long one's.  2e-2 is the bf16 path's tolerance; a row of
+    # few keys averages nothing out, so for short sequences the bound counts: bf16 probabilities (2^-9 each, in the
+    # sum over the values and in the sum they are divided by) and the rounding of the result, 3 * 2^-9 of the largest
+    # value; a twentieth more for the second order.
+    few = 1.05 * 3 * 2.0 ** -9 * float(d["v_new"].float().abs().max())
+    for b in range(B):
+        g, w = to_np_f32(got[b])[keep[b]], want[b][keep[b]]
+        assert rel_err(g, w) <= 2e-2 or (lens[b] < 64 and np.abs(g - w).max() <= few), (b, rel_err(g, w))
