@@ -71,16 +71,19 @@ SS_DEV int key_id(uint64_t k) { return k == 0 ? INT_MAX : (int)(0xffffffffu - (u
 
 // ------------------------------------------------------------------ fp32 kernel (small problems)
 //
-// Workgroup tile 32 rows x 64 vocabulary columns, feature chunks of 32 through
-// LDS; thread (wave w, lane c) accumulates rows w, w+4, ... of column c.
+// Workgroup tile BM (32 or 8) rows x 64 vocabulary columns, feature chunks of 64 through LDS (rows padded by 16
+// bytes: 16-byte reads of 16 lanes meet 64 different banks), the next chunk on its way to registers meanwhile;
+// thread (wave w, lane c) accumulates rows w, w+4, ... of column c.  8 rows where tiles of 32 would be fewer than 256
+// workgroups: 32 rows x 256 features x 1000 ids took 40.4 us in 16 workgroups with nothing in flight (the step it
+// is half of: 91 -> 28 us).
 //
 // MODE 0: top-K search.  MODE 1: the plain projection, the tile is written to y.  MODE 2: (max, sum of
 // exp) of the tile's logits per row, for the log-sum-exp over the vocabulary.
-template <int MODE>
+template <int MODE, int BM>
 __global__ __launch_bounds__(256) void lm_head_f32_kernel(LmArgs a) {
-  constexpr int BM = 32, BN = 64, BK = 32;
-  __shared__ float As[BM][BK + 1];
-  __shared__ float Ws[BN][BK + 1];
+  constexpr int BN = 64, BK = 64;
+  __shared__ __attribute__((aligned(16))) float As[BM][BK + 4];
+  __shared__ __attribute__((aligned(16))) float Ws[BN][BK + 4];
   __shared__ float Z[BM][BN + 1];
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
   const int v0 = blockIdx.x * BN, r0 = blockIdx.y * BM;
@@ -88,25 +91,46 @@ __global__ __launch_bounds__(256) void lm_head_f32_kernel(LmArgs a) {
   if (r0 >= n_rows) return;
   const float* hidden = (const float*)a.hidden;
   const float* W = (const float*)a.W;
-  float acc[BM / 4];
+  float acc[BM / 4], av[BM / 4], wv[BN / 4];
+  size_t a_row[BM / 4];  // rows w, w+4, ... of the tile: the ones this wave fetches
 #pragma unroll
-  for (int i = 0; i < BM / 4; ++i) acc[i] = 0.f;
+  for (int i = 0; i < BM / 4; ++i) {
+    acc[i] = 0.f;
+    a_row[i] = (size_t)lm_row_id(a, r0 + w + 4 * i, n_rows) * a.d;
+  }
+  // features past d become zeros; rows and ids past the end repeat the last one (they are not written or selected)
+  auto fetch = [&](int k0) {
+    const bool in = k0 + lane < a.d;
+    const int k = min(k0 + lane, a.d - 1);
+#pragma unroll
+    for (int i = 0; i < BM / 4; ++i) {
+      const float x = hidden[a_row[i] + k];
+      av[i] = in ? x : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < BN / 4; ++i) {
+      const float x = W[(size_t)min(v0 + w + 4 * i, a.V - 1) * a.d + k];
+      wv[i] = in ? x : 0.f;
+    }
+  };
+  fetch(0);
   for (int k0 = 0; k0 < a.d; k0 += BK) {
     __syncthreads();
-    for (int e = tid; e < BM * BK; e += 256) {
-      const int r = e / BK, kk = e % BK;
-      As[r][kk] = (r0 + r < n_rows && k0 + kk < a.d) ? hidden[(size_t)lm_row_id(a, r0 + r, n_rows) * a.d + k0 + kk] : 0.f;
-    }
-    for (int e = tid; e < BN * BK; e += 256) {
-      const int cc = e / BK, kk = e % BK;
-      Ws[cc][kk] = (v0 + cc < a.V && k0 + kk < a.d) ? W[(size_t)(v0 + cc) * a.d + k0 + kk] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll 8
-    for (int kk = 0; kk < BK; ++kk) {
-      const float wv = Ws[lane][kk];
 #pragma unroll
-      for (int i = 0; i < BM / 4; ++i) acc[i] = fmaf(As[w + 4 * i][kk], wv, acc[i]);
+    for (int i = 0; i < BM / 4; ++i) As[w + 4 * i][lane] = av[i];
+#pragma unroll
+    for (int i = 0; i < BN / 4; ++i) Ws[w + 4 * i][lane] = wv[i];
+    __syncthreads();
+    if (k0 + BK < a.d) fetch(k0 + BK);
+#pragma unroll 4
+    for (int kk = 0; kk < BK; kk += 4) {
+      const floatx4 wk = *reinterpret_cast<const floatx4*>(&Ws[lane][kk]);
+#pragma unroll
+      for (int i = 0; i < BM / 4; ++i) {
+        const floatx4 ak = *reinterpret_cast<const floatx4*>(&As[w + 4 * i][kk]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[i] = fmaf(ak[e], wk[e], acc[i]);
+      }
     }
   }
   if constexpr (MODE == 1) {
@@ -856,6 +880,16 @@ static LmFlavour lm_choose(int N, int V, LmArgs* a, bool six_waves_ok = false) {
   return best;
 }
 
+template <int MODE>
+static int launch_lm_f32(const char* fn, hipStream_t st, const LmArgs& a) {
+  const int chunks = ceil_div(a.N, 32);
+  SS_REQUIRE(chunks <= 65535, SS_ERR_UNSUPPORTED, "%s: N too large", fn);
+  // eight rows per workgroup while tiles of 32 leave the chip partly empty (see the kernel)
+  if ((long)a.n_tiles * chunks < 256) hipLaunchKernelGGL((lm_head_f32_kernel<MODE, 8>), dim3(a.n_tiles, ceil_div(a.N, 8)), dim3(256), 0, st, a);
+  else hipLaunchKernelGGL((lm_head_f32_kernel<MODE, 32>), dim3(a.n_tiles, chunks), dim3(256), 0, st, a);
+  return check_launch(fn);
+}
+
 // Sum of the feature slices' fp32 partial products, in slice order, rounded once to bf16: four outputs per thread.
 __global__ __launch_bounds__(256) void linear_ksplit_reduce_kernel(const float* __restrict__ part, uint16_t* __restrict__ y,
                                                                  size_t nv, int n_ksplit) {
@@ -992,9 +1026,7 @@ static int lm_candidates(const char* fn, const void* hidden, const void* W, int 
   a.live_rows = sel.rows; a.n_live = sel.n;
   a.n_ksplit = 1; a.part = nullptr;
   if (dtype == SS_F32) {
-    dim3 grid(a.n_tiles, ceil_div(N, 32));
-    SS_REQUIRE(grid.y <= 65535, SS_ERR_UNSUPPORTED, "%s: N too large", fn);
-    hipLaunchKernelGGL(lm_head_f32_kernel<0>, grid, dim3(256), 0, st, a);
+    if (int rc = launch_lm_f32<0>(fn, st, a)) return rc;
   } else {
     LmFlavour f = lm_choose(plan_n(sel, N), V, &a);
     lm_flavour_override(false, plan_n(sel, N), V, &f, &a);
@@ -1137,9 +1169,7 @@ int ss_lm_head_logsumexp(const void* hidden, const void* W, int N, int d, int V,
   a.n_ksplit = 1; a.part = nullptr;
   hipStream_t st = (hipStream_t)stream;
   if (dtype == SS_F32) {
-    dim3 grid(a.n_tiles, ceil_div(N, 32));
-    SS_REQUIRE(grid.y <= 65535, SS_ERR_UNSUPPORTED, "%s: N too large", fn);
-    hipLaunchKernelGGL(lm_head_f32_kernel<2>, grid, dim3(256), 0, st, a);
+    if (int rc = launch_lm_f32<2>(fn, st, a)) return rc;
   } else {
     LmFlavour f = lm_choose(N, V, &a);
     lm_flavour_override(false, N, V, &f, &a);
@@ -1170,9 +1200,7 @@ static int linear_run(const char* fn, const void* x, const void* W, int N, int d
   a.y = y;
   hipStream_t st = (hipStream_t)stream;
   if (dtype == SS_F32) {
-    dim3 grid(a.n_tiles, ceil_div(N, 32));
-    SS_REQUIRE(grid.y <= 65535, SS_ERR_UNSUPPORTED, "%s: N too large", fn);
-    hipLaunchKernelGGL(lm_head_f32_kernel<1>, grid, dim3(256), 0, st, a);
+    if (int rc = launch_lm_f32<1>(fn, st, a)) return rc;
   } else {
     LmFlavour f = lm_choose(plan_n(sel, N), V, &a, true);
     lm_flavour_override(true, plan_n(sel, N), V, &f, &a);

@@ -13,18 +13,25 @@ namespace ss {
 
 // ------------------------------------------------------------------ fp32 kernel
 //
-// One workgroup = (row chunk of 32 rows, split, sequence, head); wave w owns 8 of
-// the rows.  Keys are taken 64 at a time: the K tile sits in LDS token-major
-// (padded), the V tile feature-major (padded); in the score phase a lane owns a
-// key, in the P.V phase it owns output features.  Softmax is the usual running
-// max / running sum in the log2 domain.
-template <int D>
+// One workgroup = (row chunk of 4*RW rows, split, sequence, head); wave w owns RW of the rows.  Keys are taken 64 at a
+// time: the K tile sits in LDS token-major, the V tile feature-major, rows padded by 16 bytes (16-byte reads of 16
+// lanes then meet 64 different banks); in the score phase a lane owns a key, in the P.V phase it owns output features.
+// Softmax is the usual running max / running sum in the log2 domain.
+//
+// Small problems are all latency: a tile's values are fetched into registers while the tile before is computed, with
+// one page lookup per lane (the wave's other lanes' rows come by lane reads), and operands leave LDS four at a time.
+// RW = 8, or 2 where chunks of 32 rows would be too few workgroups (see the launch).  One layer of
+// 4 heads of 64, 128 cached tokens, 32 rows: 45.6 us before, with eight rows per wave,
+// a lookup and an uncovered load per value; with the fp32 LM head (1000 ids) the whole step 91 -> 28 us, and where RW
+// is 8 either way (4 sequences of 500..1000 tokens, 192 rows, 8 heads) the attention 174 -> 106 us.
+template <int D, int RW>
 __global__ __launch_bounds__(256) void msa_f32_kernel(MsaArgs a) {
-  constexpr int RC = 32, RW = 8, KT = 64, DL = D / 64;
-  __shared__ float Qs[RC][D];
-  __shared__ float Ks[KT][D + 1];
-  __shared__ float Vs[D][KT + 1];
-  __shared__ float Ps[4][RW][KT];
+  constexpr int RC = 4 * RW, KT = 64, DL = D / 64;
+  constexpr int NL = KT * D / 256;  // values of a K (or V) tile per thread
+  __shared__ __attribute__((aligned(16))) float Qs[RC][D];
+  __shared__ __attribute__((aligned(16))) float Ks[KT][D + 4];
+  __shared__ __attribute__((aligned(16))) float Vs[D][KT + 4];
+  __shared__ __attribute__((aligned(16))) float Ps[4][RW][KT];
   __shared__ int par[SS_MAX_T];
   __shared__ uint64_t anc[SS_MAX_T];
 
@@ -69,47 +76,62 @@ __global__ __launch_bounds__(256) void msa_f32_kernel(MsaArgs a) {
     for (int dd = 0; dd < DL; ++dd) o[i][dd] = 0.f;
   }
 
+  // Tile t0's values on their way to registers.  Of K a wave takes whole rows (or halves), of V whole features of the
+  // 64 tokens.  Keys past the end repeat the last one; their scores are masked, and their V becomes zero.
+  float kv[NL], vv[NL];
+  const int w_u = __builtin_amdgcn_readfirstlane(w);
+  auto fetch = [&](int t0) {
+    const int u = min(t0 + lane, total - 1);  // this lane's key
+    const float *kp, *vp;
+    int vstride;
+    if (u < n_prefix) {
+      const int tok = k0 + u;
+      int pg = a.block_table[(size_t)b * a.max_pages + (tok >> a.page_shift)];
+      pg = min(max(pg, 0), a.num_pages - 1);
+      const size_t head = ((size_t)pg * a.Hkv + hk) * a.page * D;
+      const int at = tok & (a.page - 1);
+      kp = k_cache + head + (size_t)at * D;
+      vp = v_cache + head + at;
+      vstride = a.page;
+    } else {
+      const size_t row = (((size_t)b * R + (u - n_prefix)) * a.Hkv + hk) * D;
+      kp = k_new + row;
+      vp = v_new + row;
+      vstride = 1;
+    }
+    const uint64_t kbits = (uint64_t)kp;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int kk = (w_u + 4 * i) / DL, d = ((w_u + 4 * i) % DL) * 64 + lane;
+      const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)kbits, kk), hi = __builtin_amdgcn_readlane((uint32_t)(kbits >> 32), kk);
+      kv[i] = reinterpret_cast<const float*>(((uint64_t)hi << 32) | lo)[d];
+    }
+#pragma unroll
+    for (int i = 0; i < NL; ++i) vv[i] = vp[(size_t)(w_u + 4 * i) * vstride];
+  };
+  if (total > 0) fetch(0);
   for (int t0 = 0; t0 < total; t0 += KT) {
     __syncthreads();  // the previous tile has been consumed
-    // K tile: consecutive threads take consecutive features of one key
-    for (int e = tid; e < KT * D; e += 256) {
-      const int kk = e / D, d = e % D, u = t0 + kk;
-      float v = 0.f;
-      if (u < n_prefix) {
-        const int tok = k0 + u;
-        int pg = a.block_table[(size_t)b * a.max_pages + (tok >> a.page_shift)];
-        pg = min(max(pg, 0), a.num_pages - 1);
-        v = k_cache[(((size_t)pg * a.Hkv + hk) * a.page + (tok & (a.page - 1))) * D + d];
-      } else if (u < total) {
-        v = k_new[(((size_t)b * R + (u - n_prefix)) * a.Hkv + hk) * D + d];
-      }
-      Ks[kk][d] = v;
-    }
-    // V tile: consecutive threads take consecutive tokens (contiguous inside a feature-major page)
-    for (int e = tid; e < KT * D; e += 256) {
-      const int kk = e % KT, d = e / KT, u = t0 + kk;
-      float v = 0.f;
-      if (u < n_prefix) {
-        const int tok = k0 + u;
-        int pg = a.block_table[(size_t)b * a.max_pages + (tok >> a.page_shift)];
-        pg = min(max(pg, 0), a.num_pages - 1);
-        v = v_cache[(((size_t)pg * a.Hkv + hk) * D + d) * a.page + (tok & (a.page - 1))];
-      } else if (u < total) {
-        v = v_new[(((size_t)b * R + (u - n_prefix)) * a.Hkv + hk) * D + d];
-      }
-      Vs[d][kk] = v;
-    }
+#pragma unroll
+    for (int i = 0; i < NL; ++i) Ks[(w_u + 4 * i) / DL][((w_u + 4 * i) % DL) * 64 + lane] = kv[i];
+#pragma unroll
+    for (int i = 0; i < NL; ++i) Vs[w_u + 4 * i][lane] = t0 + lane < total ? vv[i] : 0.f;
     __syncthreads();
+    if (t0 + KT < total) fetch(t0 + KT);
 
-    // scores of this lane's key against the wave's 8 rows
+    // scores of this lane's key against the wave's rows
     float sc[RW];
 #pragma unroll
     for (int i = 0; i < RW; ++i) sc[i] = 0.f;
 #pragma unroll 4
-    for (int d = 0; d < D; ++d) {
-      const float kd = Ks[lane][d];
+    for (int d = 0; d < D; d += 4) {
+      const floatx4 kd = *reinterpret_cast<const floatx4*>(&Ks[lane][d]);
 #pragma unroll
-      for (int i = 0; i < RW; ++i) sc[i] = fmaf(Qs[w * RW + i][d], kd, sc[i]);
+      for (int i = 0; i < RW; ++i) {
+        const floatx4 qd = *reinterpret_cast<const floatx4*>(&Qs[w * RW + i][d]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sc[i] = fmaf(qd[e], kd[e], sc[i]);
+      }
     }
     const int u = t0 + lane;
 #pragma unroll
@@ -136,15 +158,17 @@ __global__ __launch_bounds__(256) void msa_f32_kernel(MsaArgs a) {
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll 4
-    for (int kk = 0; kk < KT; ++kk) {
-      float vk[DL];
+    for (int kk = 0; kk < KT; kk += 4) {
+      floatx4 vk[DL];
 #pragma unroll
-      for (int dd = 0; dd < DL; ++dd) vk[dd] = Vs[lane + 64 * dd][kk];
+      for (int dd = 0; dd < DL; ++dd) vk[dd] = *reinterpret_cast<const floatx4*>(&Vs[lane + 64 * dd][kk]);
 #pragma unroll
       for (int i = 0; i < RW; ++i) {
-        const float pk = Ps[w][i][kk];
+        const floatx4 pk = *reinterpret_cast<const floatx4*>(&Ps[w][i][kk]);
 #pragma unroll
-        for (int dd = 0; dd < DL; ++dd) o[i][dd] = fmaf(pk, vk[dd], o[i][dd]);
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int dd = 0; dd < DL; ++dd) o[i][dd] = fmaf(pk[e], vk[dd][e], o[i][dd]);
       }
     }
   }
@@ -490,10 +514,14 @@ static int msa_run(const char* fn, const void* q, const void* k_new, const void*
   if (flags & SS_MSA_MERGE_ONLY) {
     // the attention kernel ran in an earlier call with SS_MSA_PARTIALS_ONLY
   } else if (dtype == SS_F32) {
-    dim3 grid(plan.n_qc, plan.n_splits, B * H);
+    // Rows per workgroup of the fp32 kernel: 8 instead of 32 while chunks of 32 are at most 64 workgroups a split, so
+    // that four times as many still fit the chip at once (they read K and V four times as often, from the L2).
+    const bool few = (long)B * H * plan.n_qc <= 64;
+    dim3 grid(few ? ceil_div(R, 8) : plan.n_qc, plan.n_splits, B * H);
     SS_REQUIRE((long)B * H <= 65535 && plan.n_splits <= 65535, SS_ERR_UNSUPPORTED, "%s: grid too large", fn);
-    if (D == 64) hipLaunchKernelGGL(msa_f32_kernel<64>, grid, dim3(256), 0, st, a);
-    else hipLaunchKernelGGL(msa_f32_kernel<128>, grid, dim3(256), 0, st, a);
+    auto kern = D == 64 ? (few ? msa_f32_kernel<64, 2> : msa_f32_kernel<64, 8>)
+                        : (few ? msa_f32_kernel<128, 2> : msa_f32_kernel<128, 8>);
+    hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, a);
     if (int rc = check_launch(fn)) return rc;
   } else {
     if (int rc = launch_msa_bf16(a, st)) return rc;

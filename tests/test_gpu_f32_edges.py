@@ -1,0 +1,36 @@
+"""The fp32 kernels on both sides of their choice of rows per workgroup, with remainders of every tile."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from helpers import rel_err, to_np_f32
+from paper_2402_11131_amd import api, synth
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+# 64 workgroups of 32 rows are cut into smaller ones, 65 and more are not
+@pytest.mark.parametrize("B,H,Hkv,D,T,gamma,L", [(4, 16, 4, 64, 8, 3, 70), (5, 13, 13, 64, 8, 3, 70), (2, 4, 2, 128, 11, 2, 1),
+                                                 (9, 4, 4, 128, 17, 1, 129), (1, 2, 1, 128, 1, 0, 0), (3, 4, 4, 64, 5, 1, 700)])
+def test_attention(B, H, Hkv, D, T, gamma, L):
+    cfg = synth.scaled(synth.CONFIGS["c1"], B=B, H=H, Hkv=Hkv, D=D, T=T, gamma=gamma, branching=(8, 8), max_depth=2, L_min=L, L_max=L)
+    inp = synth.make_msa_inputs(cfg, 3)
+    d = {k: (v.to(DEV) if isinstance(v, torch.Tensor) else v) for k, v in inp.items()}
+    got = api.ss_msa_attention(d["q"], d["k_new"], d["v_new"], d["k_cache"], d["v_cache"], d["block_table"], d["seq_lens"],
+                               d["parent"], gamma, d["scale"])
+    want = oracle.msa_attention(*[to_np_f32(inp[k]) for k in ("q", "k_new", "v_new", "k_cache", "v_cache")],
+                                inp["block_table"].numpy(), inp["seq_lens"].numpy(), inp["parent"].numpy(), gamma, inp["scale"])
+    assert rel_err(to_np_f32(got), want) <= 1e-5     # the fp32 path's tolerance
+
+
+# 255 and 256 tiles of 64 ids x 32 rows; features and ids with remainders
+@pytest.mark.parametrize("N,d,V", [(1, 1, 1), (7, 63, 65), (33, 65, 64 * 127 + 1), (32, 64, 64 * 255), (32, 64, 64 * 255 + 1), (70, 130, 6000)])
+def test_projection(N, d, V):
+    rng = synth.rng_for(N + d + V)
+    x, W = rng.standard_normal((N, d), np.float32), rng.standard_normal((V, d), np.float32)
+    got = api.ss_linear_rows(torch.from_numpy(x).to(DEV), torch.from_numpy(W).to(DEV), torch.empty(N, V, device=DEV)).cpu().numpy()
+    want = x.astype(np.float64) @ W.astype(np.float64).T
+    bound = (d + 1) * 2.0 ** -24 * (np.abs(x).astype(np.float64) @ np.abs(W).astype(np.float64).T)   # d rounded steps
+    assert (np.abs(got - want) <= bound).all()
