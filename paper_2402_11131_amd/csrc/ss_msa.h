@@ -106,9 +106,9 @@ SS_DEV SeqCut plan_uneven(const MsaArgs& a, int lane, int U, int kept) {
     const int rem = up - q * c;
     q += (rem >= c) - (rem < 0);
     slots += q;
-    wgs += q * __builtin_amdgcn_readlane(r.chunks, i);
+    wgs += ((q * a.Hkv + 7) >> 3) * __builtin_amdgcn_readlane(r.chunks, i);
   }
-  const int rounds = (wgs * a.Hkv + 255) >> 8;
+  const int rounds = (wgs + 31) >> 5;  // of the 32 workgroups an XCD holds; wgs: those of the XCD with the most
   const float cost = slots <= slots_max ? (float)rounds * (float)(c + 4) : INFINITY;
   float best = cost;
   for (int off = 32; off > 0; off >>= 1) best = fminf(best, __shfl_xor(best, off, 64));

@@ -361,8 +361,10 @@ static MsaPlan make_plan(int B, int R, int H, int Hkv, int D, int max_len, int d
   }
   // Cutting on the device needs slots to deal out and a lane per sequence; a caller's split length stays.  With one
   // row chunk a launch is so short that waiting for the lengths costs 1 us of 16 even where the host's cut stands
-  // (one sequence of 2048 tokens, 32 heads; 2 % of a step), so those keep the host's cut.
-  p.adaptive = dtype == SS_BF16 && p.n_qc > 1 && p.n_splits > 1 && !overridden && B <= kAdaptiveMaxB;
+  // (one sequence of 2048 tokens, 32 heads; 2 % of a step), so those keep the host's cut.  So do launches whose
+  // splits are short by the host's plan: cutting anew takes 2 to 4 us (splits of 300 tokens: 10 to 15 % lost, from
+  // 1024 tokens on 5 to 20 % gained).
+  p.adaptive = dtype == SS_BF16 && p.n_qc > 1 && p.n_splits > 1 && p.split_keys >= 1024 && !overridden && B <= kAdaptiveMaxB;
   p.new_units = ceil_div(R, 32) + split0_extra_blocks();
   if (p.new_units < 0) p.new_units = 0;
   p.min_units = base >= 256 ? 16 : 8;  // the more rounds a launch has, the less a short split gains it
