@@ -220,14 +220,33 @@ int ss_msa_attention_static(const void* q, const void* k_new, const void* v_new,
 
 /*
  * What a full call of a2 with this shape will launch, as currently tuned:
- * *n_splits = number of splits of the cached prefix (1 = unsplit, no workspace
- * needed), *n_kernels = 1 if the call is a single kernel (unsplit, or two
+ * *n_splits = number of splits of the cached prefix that a sequence of
+ * max_seq_len tokens has (1 = unsplit, no workspace needed; see
+ * ss_msa_plan_splits for shorter ones), *n_kernels = 1 if the call is a single kernel (unsplit, or two
  * splits merged inside the attention kernel), 2 if a merge kernel follows.
  * Either pointer may be NULL.  Host-only, no GPU work.  Returns SS_OK or the
  * error ss_msa_attention would return for the shape.
  */
 int ss_msa_plan(int B, int T, int gamma, int H, int Hkv, int D, int max_seq_len, int dtype,
                 int* n_splits, int* n_kernels);
+
+/*
+ * How a2 would split sequences of these lengths.  Without pruning and with every
+ * sequence at 7/8 of max_seq_len or more the split lengths are ss_msa_plan's.
+ * Otherwise launches with several row chunks and long splits choose the lengths
+ * on the device, from the lengths and kept nodes of the whole batch: the
+ * boundaries, and so the rounding, of one sequence's result then depend on the
+ * other sequences too.
+ *  seq_lens [B], n_nodes [B] or NULL (no pruning): HOST arrays
+ *  *where: 0 = a call of this shape does not look at the lengths, 1 = it does and
+ *          ss_msa_plan's split lengths stand, 2 = it cuts on the device
+ *  n_splits [B] (HOST): splits of each sequence (for 2 as far as the device's
+ *          exponentials round like the host's: it may come to the next candidate)
+ * where and n_splits may be NULL.  Host-only, no GPU work.  Returns SS_OK or the
+ * error ss_msa_attention would return for the shape.
+ */
+int ss_msa_plan_splits(int B, int T, int gamma, int H, int Hkv, int D, int max_seq_len, int dtype,
+                       const int32_t* seq_lens, const int32_t* n_nodes, int* where, int32_t* n_splits);
 
 /*
  * Tuning knob for a2: number of cached tokens one workgroup scans (the KV

@@ -27,7 +27,7 @@ SS_MAX_T, SS_MAX_GAMMA, SS_MAX_K = 64, 8, 8
 
 EXPORTS = (
     "ss_version", "ss_last_error", "ss_probe_hbm_read", "ss_probe_mfma_bf16", "ss_check_tree_host", "ss_build_mask", "ss_msa_workspace_bytes",
-    "ss_msa_attention", "ss_msa_workspace_init", "ss_msa_attention_static", "ss_msa_static_scratch_bytes", "ss_msa_plan", "ss_msa_set_split_keys", "ss_msa_set_merge_in_kernel", "ss_lm_head_workspace_bytes", "ss_lm_set_flavour", "ss_lm_set_stagger", "ss_lm_set_candidates_only", "ss_lm_head_argmax_topk", "ss_lm_head_verify_draft",
+    "ss_msa_attention", "ss_msa_workspace_init", "ss_msa_attention_static", "ss_msa_static_scratch_bytes", "ss_msa_plan", "ss_msa_plan_splits", "ss_msa_set_split_keys", "ss_msa_set_merge_in_kernel", "ss_lm_head_workspace_bytes", "ss_lm_set_flavour", "ss_lm_set_stagger", "ss_lm_set_candidates_only", "ss_lm_head_argmax_topk", "ss_lm_head_verify_draft",
     "ss_tree_verify", "ss_tree_draft", "ss_full_tree_template_host", "ss_kv_commit", "ss_kv_alloc_pages", "ss_linear_rows", "ss_linear_rows_ws", "ss_linear_rows_workspace_bytes", "ss_linear_rows_splits", "ss_stream_insert", "ss_stream_insert_linear", "ss_stream_insert_linear_workspace_bytes", "ss_value_rotate",
     "ss_lm_head_logsumexp", "ss_transition_probs", "ss_tree_prune", "ss_live_rows", "ss_msa_attention_pruned",
     "ss_linear_rows_live", "ss_lm_head_argmax_topk_live", "ss_lm_head_verify_draft_live",
@@ -64,6 +64,7 @@ def load_library() -> ctypes.CDLL:
     lib.ss_msa_workspace_bytes.restype = sz
     lib.ss_msa_plan.argtypes = [i32] * 8 + [ctypes.POINTER(ctypes.c_int)] * 2
     lib.ss_msa_plan.restype = i32
+    lib.ss_msa_plan_splits.argtypes = [i32] * 8 + [vp, vp, c.POINTER(c.c_int), vp]
     lib.ss_msa_attention.argtypes = [vp, vp, vp, vp, vp, vp, i32, i32, vp, vp, i32, i32, i32, i32, i32, i32, i32,
                                      c.c_float, i32, u32, vp, vp, sz, vp]
     lib.ss_msa_workspace_init.argtypes = [vp, sz, vp]
@@ -180,6 +181,19 @@ def ss_msa_plan(B, T, gamma, H, Hkv, D, max_seq_len, dtype_code):
     ns, nk = ctypes.c_int(0), ctypes.c_int(0)
     _check(load_library().ss_msa_plan(B, T, gamma, H, Hkv, D, max_seq_len, dtype_code, ctypes.byref(ns), ctypes.byref(nk)))
     return ns.value, nk.value
+
+
+def ss_msa_plan_splits(B, T, gamma, H, Hkv, D, max_seq_len, dtype_code, seq_lens: Sequence[int],
+                       n_nodes: Optional[Sequence[int]] = None):
+    """(where, splits of each sequence) for sequences of these lengths (host numbers); where: 0 = lengths not looked
+    at, 1 = looked at and ss_msa_plan's split lengths stand, 2 = cut on the device."""
+    if len(seq_lens) != B or (n_nodes is not None and len(n_nodes) != B):
+        raise ValueError("seq_lens / n_nodes must have B entries")
+    arr = ctypes.c_int32 * max(B, 1)
+    where, n = ctypes.c_int(0), arr()
+    _check(load_library().ss_msa_plan_splits(B, T, gamma, H, Hkv, D, max_seq_len, dtype_code, arr(*seq_lens),
+                                             None if n_nodes is None else arr(*n_nodes), ctypes.byref(where), n))
+    return where.value, list(n)[:B]
 
 
 def ss_msa_set_split_keys(split_keys: int) -> int:

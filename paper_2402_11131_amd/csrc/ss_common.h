@@ -43,6 +43,7 @@ typedef __attribute__((__vector_size__(2 * sizeof(uint32_t)))) uint32_t uintx2;
 
 // ---------------------------------------------------------------- device helpers
 #define SS_DEV __device__ __forceinline__
+#define SS_HD __host__ __device__ __forceinline__
 
 // fp32 -> bf16 bits, round to nearest even (inputs are finite here).
 SS_DEV uint32_t f32_to_bf16_bits(float f) {

@@ -45,8 +45,8 @@ struct MsaArgs {
 // A sequence of L cached tokens has active_splits(L) splits; every sequence has at least one (split 0, which
 // also scans the step's new keys).  Split 0 takes the tokens [0, min(L, split0_keys)), split s > 0 the
 // tokens [split_begin(s), min(L, split_begin(s) + split_keys)).
-SS_DEV int clamp_len(int L, const MsaArgs& a) { return min(max(L, 0), a.max_pages * a.page); }
-SS_DEV int active_splits(int L, const MsaArgs& a) {
+SS_HD int clamp_len(int L, const MsaArgs& a) { return min(max(L, 0), a.max_pages * a.page); }
+SS_HD int active_splits(int L, const MsaArgs& a) {
   return L <= a.split0_keys ? 1 : 1 + (L - a.split0_keys + a.split_keys - 1) / a.split_keys;
 }
 // Kept nodes of sequence b: all T unless the call passes n_nodes (clamped to [1,T]).
@@ -64,9 +64,10 @@ SS_DEV int split_len(int s, const MsaArgs& a) { return s == 0 ? a.split0_keys : 
 // nodes) in a table of 1.8 times the capacity 63 -> 48 us; eight of 2000..8192 tokens with a third to two thirds of
 // 32 nodes kept 217 -> 168 us.
 constexpr int kAdaptiveMaxB = 64;
-SS_DEV int len_units(int L, const MsaArgs& a) { return (clamp_len(L, a) + 31) >> 5; }
+SS_HD int len_units(int L, const MsaArgs& a) { return (clamp_len(L, a) + 31) >> 5; }
+SS_HD bool seq_is_even(const MsaArgs& a, int len, int kept) { return len >= a.even_len && kept == a.T; }
 SS_DEV bool plan_is_even(const MsaArgs& a, int lane, int len, int kept) {
-  return __all(lane >= a.B || (len >= a.even_len && kept == a.T));
+  return __all(lane >= a.B || seq_is_even(a, len, kept));
 }
 SS_DEV int wave_sum(int v) {
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
@@ -79,45 +80,74 @@ SS_DEV int wave_scan(int v, int lane) {  // inclusive
   }
   return v;
 }
-// Of the lane's sequence: cached blocks of split 0 and of the others, number of splits, row chunks with kept rows.
-struct SeqCut {
-  int split0, split, n, chunks;
+// The arithmetic of a cut, the same on the device (a lane per candidate) and in ss_msa_plan_splits (one after the other).
+// Blocks' worth of time that a sequence of U cached blocks takes; at least one, for an empty sequence has a split 0 and
+// so a slot too, also where the step's own rows are set to count for nothing.
+SS_HD int cut_load(const MsaArgs& a, int U) { return max(U + a.new_units, 1); }
+SS_HD int cut_chunks(const MsaArgs& a, int kept) { return (a.g * kept * (1 + a.gamma) + a.chunk_rows - 1) / a.chunk_rows; }
+// Shortest and longest split that is considered, from the sum and the largest of the loads.  Rounding the sum down keeps
+// every candidate worth a look; what does not fit the slots is dropped by its cost (the merge inside the attention
+// kernel takes two splits of a sequence at most).
+struct CutRange {
+  int lo, hi;
 };
-SS_DEV SeqCut plan_uneven(const MsaArgs& a, int lane, int U, int kept) {
-  const bool mine = lane < a.B;
-  const int x = mine ? U + a.new_units : 0;
-  SeqCut r;
-  r.chunks = mine ? (a.g * kept * (1 + a.gamma) + a.chunk_rows - 1) / a.chunk_rows : 0;
-  int x_max = x;
-  for (int off = 32; off > 0; off >>= 1) x_max = max(x_max, __shfl_xor(x_max, off, 64));
-  const int slots_max = a.B * a.n_splits;
-  // rounding the sum down keeps every candidate worth a look; what does not fit the slots is dropped below
-  // (the merge inside the attention kernel takes two splits of a sequence at most)
-  const int fill = (int)((float)wave_sum(x) / (float)slots_max), floor2 = a.max_n == 2 ? (x_max + 1) / 2 : 1;
-  const int lo = max(max(a.min_units, fill), floor2), hi = max(x_max, lo);
-  // lane j's candidate: geometric steps from lo to hi; the last leaves every sequence whole, which always fits
-  int c = lane == 63 ? hi : min(hi, (int)((float)lo * __builtin_amdgcn_exp2f(__log2f((float)hi / (float)lo) * ((float)lane * (1.f / 63.f)))));
-  c = (max(c, lo) + a.groups - 1) / a.groups * a.groups;
+SS_HD CutRange cut_range(const MsaArgs& a, int sum, int most) {
+  const int fill = (int)((float)sum / (float)(a.B * a.n_splits)), floor2 = a.max_n == 2 ? (most + 1) / 2 : 1;
+  const int lo = max(max(a.min_units, fill), floor2);
+  return CutRange{lo, max(most, lo)};
+}
+// Candidate j of 64: geometric steps from lo to hi; the last leaves every sequence whole, which always fits.
+SS_HD int cut_candidate(const MsaArgs& a, int j, CutRange r) {
+#ifdef __HIP_DEVICE_COMPILE__
+  const float up = __builtin_amdgcn_exp2f(__log2f((float)r.hi / (float)r.lo) * ((float)j * (1.f / 63.f)));
+#else
+  const float up = exp2f(log2f((float)r.hi / (float)r.lo) * ((float)j * (1.f / 63.f)));
+#endif
+  const int c = j == 63 ? r.hi : min(r.hi, (int)((float)r.lo * up));
+  return (max(c, r.lo) + a.groups - 1) / a.groups * a.groups;
+}
+// Cost of splits of c blocks; load(i), chunks(i): of sequence i.
+template <class Load, class Chunks>
+SS_HD float cut_cost(const MsaArgs& a, int c, Load load, Chunks chunks) {
   const float rc = 1.f / (float)c;
   int slots = 0, wgs = 0;
   for (int i = 0; i < a.B; ++i) {
-    const int up = __builtin_amdgcn_readlane(x, i) + c - 1;
+    const int up = load(i) + c - 1;
     int q = (int)((float)up * rc);  // off by one at most
     const int rem = up - q * c;
     q += (rem >= c) - (rem < 0);
     slots += q;
-    wgs += ((q * a.Hkv + 7) >> 3) * __builtin_amdgcn_readlane(r.chunks, i);
+    wgs += ((q * a.Hkv + 7) >> 3) * chunks(i);
   }
   const int rounds = (wgs + 31) >> 5;  // of the 32 workgroups an XCD holds; wgs: those of the XCD with the most
-  const float cost = slots <= slots_max ? (float)rounds * (float)(c + 4) : INFINITY;
+  return slots <= a.B * a.n_splits ? (float)rounds * (float)(c + 4) : INFINITY;
+}
+// Of one sequence: cached blocks of split 0 and of the others, number of splits, row chunks with kept rows.
+struct SeqCut {
+  int split0, split, n, chunks;
+};
+SS_HD SeqCut cut_of(const MsaArgs& a, int cut, int U, int chunks) {
+  const int x = cut_load(a, U), q = max(1, (x + cut - 1) / cut), even = (x + q - 1) / q;
+  SeqCut r;
+  r.split = max((even + a.groups - 1) / a.groups, 1) * a.groups;
+  r.split0 = max(0, r.split - a.new_units);
+  r.n = U <= r.split0 ? 1 : 1 + (U - r.split0 + r.split - 1) / r.split;  // <= q
+  r.chunks = chunks;
+  return r;
+}
+SS_DEV SeqCut plan_uneven(const MsaArgs& a, int lane, int U, int kept) {
+  const bool mine = lane < a.B;
+  const int x = mine ? cut_load(a, U) : 0, chunks = mine ? cut_chunks(a, kept) : 0;
+  int x_max = x;
+  for (int off = 32; off > 0; off >>= 1) x_max = max(x_max, __shfl_xor(x_max, off, 64));
+  const int c = cut_candidate(a, lane, cut_range(a, wave_sum(x), x_max));
+  const float cost = cut_cost(a, c, [&](int i) { return __builtin_amdgcn_readlane(x, i); },
+                              [&](int i) { return __builtin_amdgcn_readlane(chunks, i); });
   float best = cost;
   for (int off = 32; off > 0; off >>= 1) best = fminf(best, __shfl_xor(best, off, 64));
   const int win = 63 - __builtin_clzll(__ballot(cost == best));  // the longest splits among equals
-  const int cut = __builtin_amdgcn_readlane(c, win);
-  const int q = max(1, (x + cut - 1) / cut), even = (x + q - 1) / q;
-  r.split = max((even + a.groups - 1) / a.groups, 1) * a.groups;
-  r.split0 = max(0, r.split - a.new_units);
-  r.n = !mine ? 0 : U <= r.split0 ? 1 : 1 + (U - r.split0 + r.split - 1) / r.split;  // <= q
+  SeqCut r = cut_of(a, __builtin_amdgcn_readlane(c, win), U, chunks);
+  if (!mine) r.n = 0;
   return r;
 }
 

@@ -382,6 +382,15 @@ static MsaPlan make_plan(int B, int R, int H, int Hkv, int D, int max_len, int d
   return p;
 }
 
+// The shape and the plan of a call, as the kernels read them.
+static void set_plan(MsaArgs& a, const MsaPlan& plan, int B, int T, int gamma, int H, int Hkv, int D, int max_len, int dtype) {
+  a.B = B; a.T = T; a.gamma = gamma; a.R = T * (1 + gamma); a.H = H; a.Hkv = Hkv; a.g = H / Hkv; a.D = D;
+  a.split_keys = plan.split_keys; a.split0_keys = plan.split0_keys; a.n_splits = plan.n_splits; a.n_qc = plan.n_qc; a.groups = plan.groups; a.stages = plan.stages;
+  a.max_n = plan.n_splits == 2 && dtype == SS_BF16 ? 2 : 0;  // also where the merge kernel does it: the same cut either way
+  a.even_len = max_len - max_len / 8;
+  a.adaptive = plan.adaptive; a.new_units = plan.new_units; a.min_units = plan.min_units; a.chunk_rows = plan.chunk_rows;
+}
+
 // Whether a full call folds its two splits inside the attention kernel (see ss_msa_attention).
 static bool merges_in_kernel(const MsaPlan& plan, int dtype) {
   return g_merge_in_kernel.load() && dtype == SS_BF16 && plan.n_splits == 2;
@@ -493,13 +502,9 @@ static int msa_run(const char* fn, const void* q, const void* k_new, const void*
   char* ws = (char*)(((uintptr_t)workspace + 255) & ~(uintptr_t)255);
   a.part_o = (float*)ws;
   a.part_lse = (float*)(ws + plan.part_o_bytes);
-  a.B = B; a.T = T; a.gamma = gamma; a.R = R; a.H = H; a.Hkv = Hkv; a.g = H / Hkv; a.D = D;
+  set_plan(a, plan, B, T, gamma, H, Hkv, D, max_len, dtype);
   a.page = page_size; a.page_shift = page_size == 16 ? 4 : (page_size == 32 ? 5 : 6);
   a.max_pages = max_pages_per_seq; a.num_pages = num_pages;
-  a.split_keys = plan.split_keys; a.split0_keys = plan.split0_keys; a.n_splits = plan.n_splits; a.n_qc = plan.n_qc; a.groups = plan.groups; a.stages = plan.stages;
-  a.max_n = plan.n_splits == 2 && dtype == SS_BF16 ? 2 : 0;  // also where the merge kernel does it: the same cut either way
-  a.even_len = max_len - max_len / 8;
-  a.adaptive = plan.adaptive; a.new_units = plan.new_units; a.min_units = plan.min_units; a.chunk_rows = plan.chunk_rows;
   a.scale_log2 = scale * 1.4426950408889634f;
   // In-kernel merge (MFMA path, two splits): the second split of a (sequence, head) to finish adds the other's
   // partial rows to its own and writes the output, which saves the merge kernel and its kernel boundary.  With
@@ -556,6 +561,49 @@ int ss_msa_plan(int B, int T, int gamma, int H, int Hkv, int D, int max_seq_len,
   const ss::MsaPlan plan = ss::make_plan(B, T * (1 + gamma), H, Hkv, D, max_seq_len, dtype);
   if (n_splits) *n_splits = plan.n_splits;
   if (n_kernels) *n_kernels = (plan.n_splits > 1 && !ss::merges_in_kernel(plan, dtype)) ? 2 : 1;
+  return SS_OK;
+}
+
+int ss_msa_plan_splits(int B, int T, int gamma, int H, int Hkv, int D, int max_seq_len, int dtype,
+                       const int32_t* seq_lens, const int32_t* n_nodes, int* where, int32_t* n_splits) {
+  using namespace ss;
+  clear_error();
+  const char* fn = "ss_msa_plan_splits";
+  if (int rc = check_shape(fn, B, T, gamma, H, Hkv, D, dtype)) return rc;
+  SS_REQUIRE(B == 0 || seq_lens != nullptr, SS_ERR_INVALID_ARG, "%s: NULL seq_lens", fn);
+  if (max_seq_len < 0) max_seq_len = 0;
+  MsaArgs a = {};
+  set_plan(a, make_plan(B, T * (1 + gamma), H, Hkv, D, max_seq_len, dtype), B, T, gamma, H, Hkv, D, max_seq_len, dtype);
+  a.max_pages = max_seq_len; a.page = 1;  // clamp_len
+  int load[kAdaptiveMaxB], chunks[kAdaptiveMaxB], units[kAdaptiveMaxB];
+  bool even = true;
+  int sum = 0, most = 0;
+  for (int b = 0; a.adaptive && b < B; ++b) {
+    const int kept = n_nodes ? min(max(n_nodes[b], 1), T) : T;
+    even = even && seq_is_even(a, seq_lens[b], kept);
+    units[b] = len_units(seq_lens[b], a);
+    load[b] = cut_load(a, units[b]);
+    chunks[b] = cut_chunks(a, kept);
+    sum += load[b];
+    most = max(most, load[b]);
+  }
+  if (where) *where = !a.adaptive ? 0 : (even ? 1 : 2);
+  if (!n_splits) return SS_OK;
+  if (!a.adaptive || even) {
+    for (int b = 0; b < B; ++b) n_splits[b] = active_splits(clamp_len(seq_lens[b], a), a);
+    return SS_OK;
+  }
+  float best = INFINITY;
+  int cut = 0;
+  for (int j = 0; j < 64; ++j) {
+    const int c = cut_candidate(a, j, cut_range(a, sum, most));
+    const float cost = cut_cost(a, c, [&](int i) { return load[i]; }, [&](int i) { return chunks[i]; });
+    if (cost <= best) {
+      best = cost;
+      cut = c;
+    }
+  }
+  for (int b = 0; b < B; ++b) n_splits[b] = cut_of(a, cut, units[b], chunks[b]).n;
   return SS_OK;
 }
 

@@ -69,3 +69,45 @@ def test_attention_refuses_a_cache_beyond_its_page_offsets():
     rc = lib.ss_msa_attention(one, one, one, one, one, one, 4, pages, one, one, 1, 4, 1, 32, 32, 128, 64, 0.1,
                               api.SS_BF16, 0, one, None, 0, None)
     assert rc == 2 and b"1 TiB" in lib.ss_last_error()   # SS_ERR_UNSUPPORTED
+
+
+# Batches that the device cuts: (B, T, gamma, H, Hkv, D, capacity, lengths, kept nodes or None)
+_CUT_BATCHES = [
+    (8, 32, 4, 32, 8, 128, 8192, [8192, 0, 0, 5000, 2500, 0, 7000, 4097], None),
+    (8, 32, 4, 32, 8, 128, 8192, [0, 5299, 2500, 8192, 3993, 2500, 5000, 2500], [11, 32, 1, 20, 13, 8, 32, 2]),
+    (8, 32, 4, 32, 8, 128, 8192, [0] * 8, None),
+    (2, 24, 3, 32, 8, 128, 16256, [9005, 3001], None),
+    (4, 16, 2, 48, 16, 64, 4096, [1100, 513, 0, 700], None),       # at most two splits each: merged in the attention kernel
+    (64, 8, 2, 4, 1, 64, 8192, [(i * 37) % 600 for i in range(64)], None),
+]
+
+
+def _check_cuts():
+    rng = synth.rng_for(7)
+    for B, T, gamma, H, Hkv, D, cap, lens, kept in _CUT_BATCHES:
+        most, _ = api.ss_msa_plan(B, T, gamma, H, Hkv, D, cap, api.SS_BF16)
+        draws = [(lens, kept)]
+        for _ in range(200):
+            draws.append(([int(x) for x in rng.integers(0, cap + 1, B) * rng.integers(0, 2, B)],
+                          None if rng.integers(0, 2) else [int(x) for x in rng.integers(1, T + 1, B)]))
+        for lens, kept in draws:
+            where, n = api.ss_msa_plan_splits(B, T, gamma, H, Hkv, D, cap, api.SS_BF16, lens, kept)
+            assert where in (1, 2)
+            assert all(k >= 1 for k in n), (lens, kept, n)                      # every sequence has a split 0
+            assert sum(n) <= B * most, (lens, kept, n)                          # the workspace holds that many
+            assert most != 2 or max(n) <= 2, (lens, kept, n)
+
+
+def test_cut_of_an_uneven_batch_fits_the_workspace():
+    import os
+    import subprocess
+    import sys
+    _check_cuts()
+    # the same for every kind of value SS_MSA_SPLIT0_EXTRA takes (read once per process): below -5 the step's own 160
+    # rows count for nothing
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    code = "import sys; sys.path[:0] = [%r, %r]; import test_host_plans as t; t._check_cuts()" % (root, os.path.join(root, "tests"))
+    for extra in (-64, -5, -4, 0, 64):
+        r = subprocess.run([sys.executable, "-c", code], env=dict(os.environ, SS_MSA_SPLIT0_EXTRA=str(extra)), cwd=root,
+                           stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
+        assert r.returncode == 0, (extra, r.stdout[-2000:])
