@@ -170,12 +170,12 @@ int ss_build_mask(const int32_t* parent, int B, int T, int gamma, uint32_t flags
  * workspace: device scratch of at least ss_msa_workspace_bytes(...) bytes with
  * max_seq_len = max_pages_per_seq*page_size.  It holds the per-split partial
  * results and, when two splits are merged inside the attention kernel (see
- * ss_msa_set_merge_in_kernel), their arrival counters.  The counters must be
- * ZERO when a call is enqueued and every call leaves them zero: fill a new
- * workspace with zeros once (ss_msa_workspace_init, or any memset) and it can
- * be used for any number of calls of any shape it is large enough for.  A
- * workspace that was never zeroed gives wrong results for split problems, with
- * no error.  Calls that may run at the same time (different streams, graphs
+ * ss_msa_set_merge_in_kernel), their arrival counters, which have a region of
+ * their own in front, the same for all shapes.  The counters must be ZERO when a
+ * call is enqueued and every call leaves them zero: fill a new workspace with
+ * zeros once (ss_msa_workspace_init, or any memset) and it can be used for any
+ * number of calls of any shape it is large enough for.  A workspace that was
+ * never zeroed gives wrong results for split problems, with no error.  Calls that may run at the same time (different streams, graphs
  * replayed on different streams) need a workspace each; calls that follow each
  * other on one stream can share one.  The library keeps nothing between calls.
  */
@@ -206,9 +206,9 @@ int ss_msa_attention(const void* q, const void* k_new, const void* v_new, const 
  * overlap in time (different streams, graph replays on different streams) RACE
  * and give wrong results; enqueue them on one stream or use ss_msa_attention.
  * Results are those of ss_msa_attention, bit for bit.
- * Errors: those of ss_msa_attention; SS_ERR_UNSUPPORTED if the shape needs more
- * than the array holds (ss_msa_workspace_bytes tells the need), nothing is
- * enqueued then.
+ * Errors: those of ss_msa_attention; SS_ERR_UNSUPPORTED if the shape's partial
+ * results and counters need more than the array holds (the message tells how
+ * much; a workspace is some 256 KB larger), nothing is enqueued then.
  */
 size_t ss_msa_static_scratch_bytes(void);
 int ss_msa_attention_static(const void* q, const void* k_new, const void* v_new,
@@ -222,8 +222,9 @@ int ss_msa_attention_static(const void* q, const void* k_new, const void* v_new,
  * What a full call of a2 with this shape will launch, as currently tuned:
  * *n_splits = number of splits of the cached prefix that a sequence of
  * max_seq_len tokens has (1 = unsplit, no workspace needed; see
- * ss_msa_plan_splits for shorter ones), *n_kernels = 1 if the call is a single kernel (unsplit, or two
- * splits merged inside the attention kernel), 2 if a merge kernel follows.
+ * ss_msa_plan_splits for shorter ones), *n_kernels = 1 if the call is a single
+ * kernel (unsplit, or two splits merged inside the attention kernel), 2 if a
+ * merge kernel follows.
  * Either pointer may be NULL.  Host-only, no GPU work.  Returns SS_OK or the
  * error ss_msa_attention would return for the shape.
  */
@@ -263,8 +264,9 @@ int ss_msa_set_split_keys(int split_keys);
  * split that finishes second adds the other's partial rows to its own and writes
  * `out`; the arithmetic is that of the merge kernel, so the result is the same
  * bit for bit and does not depend on which split finishes first.  The splits
- * find each other through arrival counters at the end of the call's workspace
- * (see a2 for the zero-fill rule).  Returns the previous setting.
+ * find each other through arrival counters in front of the call's workspace
+ * (see a2 for the zero-fill rule).  Calls of more than 8192 (sequence, KV head,
+ * row chunk) items take the second kernel.  Returns the previous setting.
  */
 int ss_msa_set_merge_in_kernel(int on);
 

@@ -153,7 +153,11 @@ SS_DEV SeqCut plan_uneven(const MsaArgs& a, int lane, int U, int kept) {
 
 // Arrival counters of the in-kernel split merge: one per (sequence, KV head, row chunk, query tile of at most
 // kArriveTiles per chunk).
+// They lie in front of the workspace, in a region of the same size for every shape: they have to be zero when a call
+// begins, so no shape may leave anything else where another shape looks for them.  8192 (sequence, KV head, row chunk)
+// items fit, 32 rounds of workgroups; calls of more take the merge kernel (same bits).
 constexpr int kArriveTiles = 8;
+constexpr size_t kArriveRegionBytes = (size_t)8192 * kArriveTiles * sizeof(unsigned int);
 
 // MFMA path (bf16, D = 64 or 128).  Returns SS_OK or an error code.
 int launch_msa_bf16(const MsaArgs& a, hipStream_t stream);

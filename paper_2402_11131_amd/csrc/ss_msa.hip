@@ -266,7 +266,9 @@ static std::atomic<int> g_merge_in_kernel{1};
 struct MsaPlan {
   int split_keys, split0_keys, n_splits, n_qc, groups, stages;
   int adaptive, new_units, min_units, chunk_rows;
-  size_t part_o_bytes, part_lse_bytes, arrive_bytes, table_bytes, total_bytes;
+  size_t arrive_bytes;    // arrival counters of this shape (front of the workspace); 0 = not merged in the attention kernel
+  size_t part_o_at, part_lse_at, table_at, total_bytes;  // places in the workspace
+  size_t scratch_bytes;   // what counts against the limit of ss_msa_attention_static
 };
 
 // Chooses the split length from the shape alone (sequence lengths live on the device).  Every split
@@ -369,16 +371,21 @@ static MsaPlan make_plan(int B, int R, int H, int Hkv, int D, int max_len, int d
   if (p.new_units < 0) p.new_units = 0;
   p.min_units = base >= 256 ? 16 : 8;  // the more rounds a launch has, the less a short split gains it
   p.chunk_rows = dtype == SS_BF16 ? msa_bf16_rows_per_chunk(g * R) : 32;
+  // Workspace: arrival counters (their region is there for every split shape) | partial outputs | log-sum-exps | cuts
+  p.arrive_bytes = 0;
+  p.part_o_at = p.part_lse_at = p.table_at = 0;
+  p.total_bytes = p.scratch_bytes = 256;  // to align the start
   if (p.n_splits > 1) {
-    p.part_o_bytes = align_up((size_t)B * H * p.n_splits * R * D * sizeof(float), 256);
-    p.part_lse_bytes = align_up((size_t)B * H * p.n_splits * R * sizeof(float), 256);
-    p.arrive_bytes = (dtype == SS_BF16 && p.n_splits == 2)
-                         ? align_up((size_t)B * Hkv * p.n_qc * kArriveTiles * sizeof(unsigned int), 256) : 0;
-  } else {
-    p.part_o_bytes = p.part_lse_bytes = p.arrive_bytes = 0;
+    const size_t counters = dtype == SS_BF16 && p.n_splits == 2
+                                ? align_up((size_t)B * Hkv * p.n_qc * kArriveTiles * sizeof(unsigned int), 256) : 0;
+    if (counters <= kArriveRegionBytes) p.arrive_bytes = counters;
+    const size_t rows = (size_t)B * H * p.n_splits * R;
+    p.part_o_at = kArriveRegionBytes;
+    p.part_lse_at = p.part_o_at + align_up(rows * D * sizeof(float), 256);
+    p.table_at = p.part_lse_at + align_up(rows * sizeof(float), 256);
+    p.total_bytes += p.table_at + (p.adaptive ? kAdaptiveMaxB * sizeof(int2) : 0);
+    p.scratch_bytes += p.table_at - kArriveRegionBytes + counters;
   }
-  p.table_bytes = p.adaptive ? kAdaptiveMaxB * sizeof(int2) : 0;
-  p.total_bytes = p.part_o_bytes + p.part_lse_bytes + p.arrive_bytes + p.table_bytes + 256;
   return p;
 }
 
@@ -392,8 +399,8 @@ static void set_plan(MsaArgs& a, const MsaPlan& plan, int B, int T, int gamma, i
 }
 
 // Whether a full call folds its two splits inside the attention kernel (see ss_msa_attention).
-static bool merges_in_kernel(const MsaPlan& plan, int dtype) {
-  return g_merge_in_kernel.load() && dtype == SS_BF16 && plan.n_splits == 2;
+static bool merges_in_kernel(const MsaPlan& plan) {
+  return g_merge_in_kernel.load() && plan.arrive_bytes > 0;
 }
 
 static int check_shape(const char* fn, int B, int T, int gamma, int H, int Hkv, int D, int dtype) {
@@ -434,7 +441,8 @@ static int zero_bytes(unsigned char* p, size_t bytes, hipStream_t st, const char
 // the array; host code reaches it only through the address hipGetSymbolAddress reports for the device that
 // is current, looked up once per device.
 constexpr size_t kStaticScratchBytes = (size_t)32 << 20;
-static __device__ __align__(256) unsigned char g_msa_scratch[kStaticScratchBytes + kAdaptiveMaxB * sizeof(int2)];  // ... and the table of cuts
+// ... of partial rows, the counters' region in front of them and the table of cuts behind
+static __device__ __align__(256) unsigned char g_msa_scratch[kArriveRegionBytes + kStaticScratchBytes + kAdaptiveMaxB * sizeof(int2)];
 constexpr int kMaxDevices = 64;
 static std::mutex g_scratch_mutex;
 static void* g_scratch_ptr[kMaxDevices];  // guarded by g_scratch_mutex
@@ -487,10 +495,9 @@ static int msa_run(const char* fn, const void* q, const void* k_new, const void*
   const int max_len = max_pages_per_seq * page_size;
   const MsaPlan plan = make_plan(B, R, H, Hkv, D, max_len, dtype);
   if (library_scratch) {
-    const size_t need = plan.total_bytes - plan.table_bytes;  // the table has a place of its own behind the array's bytes
-    SS_REQUIRE(need <= workspace_bytes, SS_ERR_UNSUPPORTED,
+    SS_REQUIRE(plan.scratch_bytes <= workspace_bytes, SS_ERR_UNSUPPORTED,
                "%s: this shape needs %zu bytes of scratch memory, the library's array holds %zu; use "
-               "ss_msa_attention with a workspace", fn, need, workspace_bytes);
+               "ss_msa_attention with a workspace", fn, plan.scratch_bytes, workspace_bytes);
   } else {
     SS_REQUIRE(plan.n_splits == 1 || (workspace != nullptr && workspace_bytes >= plan.total_bytes), SS_ERR_WORKSPACE,
                "%s: workspace of %zu bytes needed, %zu given", fn, plan.total_bytes, workspace_bytes);
@@ -500,8 +507,8 @@ static int msa_run(const char* fn, const void* q, const void* k_new, const void*
   a.q = q; a.k_new = k_new; a.v_new = v_new; a.k_cache = k_cache; a.v_cache = v_cache;
   a.block_table = block_table; a.seq_lens = seq_lens; a.parent = parent; a.n_nodes = n_nodes; a.out = out;
   char* ws = (char*)(((uintptr_t)workspace + 255) & ~(uintptr_t)255);
-  a.part_o = (float*)ws;
-  a.part_lse = (float*)(ws + plan.part_o_bytes);
+  a.part_o = (float*)(ws + plan.part_o_at);
+  a.part_lse = (float*)(ws + plan.part_lse_at);
   set_plan(a, plan, B, T, gamma, H, Hkv, D, max_len, dtype);
   a.page = page_size; a.page_shift = page_size == 16 ? 4 : (page_size == 32 ? 5 : 6);
   a.max_pages = max_pages_per_seq; a.num_pages = num_pages;
@@ -510,9 +517,9 @@ static int msa_run(const char* fn, const void* q, const void* k_new, const void*
   // partial rows to its own and writes the output, which saves the merge kernel and its kernel boundary.  With
   // more splits the partial rows would be fetched one split after the other and the merge kernel is faster.
   a.arrive = nullptr;
-  if (merges_in_kernel(plan, dtype) && !(flags & SS_MSA_MERGE_ONLY))
-    a.arrive = (unsigned int*)(ws + plan.part_o_bytes + plan.part_lse_bytes);
-  a.cut_table = plan.adaptive ? (int2*)(ws + plan.part_o_bytes + plan.part_lse_bytes + plan.arrive_bytes) : nullptr;
+  if (merges_in_kernel(plan) && !(flags & SS_MSA_MERGE_ONLY))
+    a.arrive = (unsigned int*)ws;
+  a.cut_table = plan.adaptive ? (int2*)(ws + plan.table_at) : nullptr;
   a.flags = flags;
   hipStream_t st = (hipStream_t)stream;
 
@@ -560,7 +567,7 @@ int ss_msa_plan(int B, int T, int gamma, int H, int Hkv, int D, int max_seq_len,
   if (max_seq_len < 0) max_seq_len = 0;
   const ss::MsaPlan plan = ss::make_plan(B, T * (1 + gamma), H, Hkv, D, max_seq_len, dtype);
   if (n_splits) *n_splits = plan.n_splits;
-  if (n_kernels) *n_kernels = (plan.n_splits > 1 && !ss::merges_in_kernel(plan, dtype)) ? 2 : 1;
+  if (n_kernels) *n_kernels = (plan.n_splits > 1 && !ss::merges_in_kernel(plan)) ? 2 : 1;
   return SS_OK;
 }
 

@@ -33,6 +33,15 @@ def test_attention_workspace_grows_with_the_splits_and_holds_the_counters():
     assert _msa_plan(c4, 4096) == (2, 1)
 
 
+def test_merge_in_the_kernel_stops_where_its_counters_fill_their_region():
+    api.ss_msa_set_split_keys(1024)
+    try:
+        assert api.ss_msa_plan(256, 16, 4, 32, 32, 128, 2048, api.SS_BF16) == (2, 1)      # 8192 items
+        assert api.ss_msa_plan(257, 16, 4, 32, 32, 128, 2048, api.SS_BF16) == (2, 2)      # 8224: the merge kernel
+    finally:
+        api.ss_msa_set_split_keys(0)
+
+
 def test_projection_slices():
     bf, f32 = api.SS_BF16, api.SS_F32
     assert api.ss_linear_rows_splits(320, 11008, 4096, bf) == 4     # down map: few outputs, many features
