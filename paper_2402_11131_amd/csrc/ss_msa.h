@@ -17,15 +17,22 @@ struct MsaArgs {
   const int32_t* parent;
   const int32_t* n_nodes;  // [B] kept nodes per sequence after pruning (rows of the others are not computed), or NULL
   void* out;
-  float* part_o;    // [slots,H,R,D]  per-split outputs, already divided by their own sum; split s of sequence b is
-                    // slot b*S + s, or where the device cuts the sequences (below) the slot after the earlier splits
-  float* part_lse;  // [slots,H,R]    log2-domain log-sum-exp of each split
+  float* part_o;    // [rows,D]  per-split outputs, already divided by their own sum (part_row_of: which row)
+  float* part_lse;  // [rows]    log2-domain log-sum-exp of each split
   int B, T, gamma, R, H, Hkv, g, D;
   int page, page_shift, max_pages, num_pages;
   int split_keys;  // cached tokens per split (multiple of 32; of 64 for the fp32 kernel)
   int split0_keys; // cached tokens of split 0 (MFMA path: shorter, that split also scans the step's own rows)
   int n_splits;    // S: upper bound on splits per sequence
   int n_qc;        // query-row chunks per (sequence, KV head) (MFMA path)
+  int groups;      // wave groups per workgroup the plan asks for (MFMA path)
+  int stages;      // ring stages per wave group the plan asks for (MFMA path)
+  unsigned int* arrive;  // MFMA path, two splits merged inside the kernel: arrival counters [B,Hkv,n_qc,kArriveTiles] in the
+                         // workspace (zero before the call, zero again after it), else NULL
+  float scale_log2;  // softmax scale times log2(e)
+  uint32_t flags;
+  int n_groups, n_stages;  // what the launch has of `groups` and `stages`
+  // last, so that kernels that do not cut read no more of the arguments than they need
   int2* cut_table;  // [B] adaptive calls: splits and first slot of every sequence, which workgroup 0 of the attention
                     // kernel leaves in the workspace for the merge kernel; else NULL
   int adaptive;    // 1: a batch the host's split lengths do not fit is cut anew on the device (plan_uneven)
@@ -34,12 +41,6 @@ struct MsaArgs {
   int max_n;       // most splits per sequence plan_uneven may make (2: merged in the kernel; else 0 = no limit)
   int min_units;   // shortest split plan_uneven considers, in blocks
   int chunk_rows;  // folded query rows per row chunk (MFMA path)
-  int groups;      // wave groups per workgroup the plan asks for (MFMA path)
-  int stages;      // ring stages per wave group the plan asks for (MFMA path)
-  unsigned int* arrive;  // MFMA path, two splits merged inside the kernel: arrival counters [B,Hkv,n_qc,kArriveTiles] in the
-                         // workspace (zero before the call, zero again after it), else NULL
-  float scale_log2;  // softmax scale times log2(e)
-  uint32_t flags;
 };
 
 // A sequence of L cached tokens has active_splits(L) splits; every sequence has at least one (split 0, which
@@ -53,6 +54,14 @@ SS_HD int active_splits(int L, const MsaArgs& a) {
 SS_DEV int kept_nodes(int b, const MsaArgs& a) { return a.n_nodes ? min(max(a.n_nodes[b], 1), a.T) : a.T; }
 SS_DEV int split_begin(int s, const MsaArgs& a) { return s == 0 ? 0 : a.split0_keys + (s - 1) * a.split_keys; }
 SS_DEV int split_len(int s, const MsaArgs& a) { return s == 0 ? a.split0_keys : a.split_keys; }
+
+// Row of the partial results of (sequence, split, query head, query row).  The splits of a sequence's head lie together,
+// [B,H,S,R].  Where the device cuts the sequences (below) it deals out the B*S slots, a sequence's from slot0 on, and
+// they lie by slot, [B*S,H,R].
+template <bool CUTS>
+SS_DEV size_t part_row_of(const MsaArgs& a, int b, int slot0, int s, int h, int r) {
+  return CUTS ? ((size_t)(slot0 + s) * a.H + h) * a.R + r : (((size_t)b * a.H + h) * a.n_splits + s) * a.R + r;
+}
 
 // ---- splits cut on the device.  The host plans from the capacity of the block table; what the sequences really
 // hold (and, after pruning, how many row chunks they have) is known on the device only.  As long as every sequence

@@ -184,7 +184,7 @@ __global__ __launch_bounds__(256) void msa_f32_kernel(MsaArgs a) {
 #pragma unroll
       for (int dd = 0; dd < DL; ++dd) out[lane + 64 * dd] = o[i][dd] * inv;
     } else {
-      const size_t pr = (((size_t)b * a.n_splits + s) * a.H + h) * R + row;
+      const size_t pr = part_row_of<false>(a, b, 0, s, h, row);
 #pragma unroll
       for (int dd = 0; dd < DL; ++dd) a.part_o[pr * D + lane + 64 * dd] = o[i][dd] * inv;
       if (lane == 0) a.part_lse[pr] = m[i] + log2f(l[i]);
@@ -197,9 +197,9 @@ __global__ __launch_bounds__(256) void msa_f32_kernel(MsaArgs a) {
 // out = sum_s w_s * o_s with w_s = 2^(lse_s - max) / sum.  One thread per (sequence, row, head,
 // 4 features).  The partial outputs are fetched four splits at a time without waiting for the
 // log-sum-exps (their addresses do not depend on them) and folded in with a running maximum, so the
-// kernel is one round of independent loads deep for each four splits; what lies in the place of a split that a
-// sequence does not have may be fetched but is not used.
-template <bool BF16>
+// kernel is one round of independent loads deep for each four splits.  CUTS: after an attention kernel that may have
+// cut the batch anew; the table of cuts tells.
+template <bool BF16, bool CUTS>
 __global__ __launch_bounds__(256) void msa_combine_kernel(MsaArgs a) {
   const int dq = a.D >> 2;  // threads per row
   const long t = (long)blockIdx.x * 256 + threadIdx.x;
@@ -210,9 +210,8 @@ __global__ __launch_bounds__(256) void msa_combine_kernel(MsaArgs a) {
   const int r = (item / a.H) % a.R;
   const int b = item / ((long)a.H * a.R);
   if ((r < a.T ? r : (r - a.T) / max(a.gamma, 1)) >= kept_nodes(b, a)) return;  // rows of removed nodes: no partials, not written
-  const size_t stride = (size_t)a.H * a.R, row0 = (size_t)h * a.R + r;  // rows from a slot to the next, row in a slot
-  // The first four splits are fetched where the host's cut puts them, before it is known whether that stands and how
-  // many the sequence has: one round of loads less to wait for.
+  // the rows of part_row_of: the sequence's first, or where the table of cuts tells the slots the workspace's first
+  const size_t stride = CUTS ? (size_t)a.H * a.R : a.R, row0 = CUTS ? (size_t)h * a.R + r : part_row_of<false>(a, b, 0, 0, h, r);
   floatx4 v[4];
   float l[4];
   auto fetch = [&](int slot0, int s0, int n) {
@@ -223,16 +222,21 @@ __global__ __launch_bounds__(256) void msa_combine_kernel(MsaArgs a) {
       l[i] = a.part_lse[row];
     }
   };
-  fetch(b * a.n_splits, 0, a.n_splits);
-  int n_active, slot0 = b * a.n_splits;
-  if (BF16 && a.cut_table) {
+  // The first four splits are fetched where the host's cut puts them, before it is known whether that stands and how many
+  // the sequence has: one round of loads less to wait for (0.2 us of 4.8; what lies in the place of a split that the
+  // sequence does not have is not used).  The empty asm keeps the compiler from moving the loads behind the test.
+  fetch(CUTS ? b * a.n_splits : 0, 0, a.n_splits);
+  int n_active, slot0 = 0;
+  if (CUTS) {
     const int2 cut = a.cut_table[b];
     n_active = min(max(cut.x, 1), a.B * a.n_splits);  // clamped: whatever the workspace holds, what is read lies in it
     slot0 = min(max(cut.y, 0), a.B * a.n_splits - n_active);
-    if (slot0 != b * a.n_splits || n_active > a.n_splits) fetch(slot0, 0, n_active);
   } else {
     n_active = active_splits(clamp_len(a.seq_lens[b], a), a);
   }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(v[i]), "+v"(l[i]));
+  if (CUTS && (slot0 != b * a.n_splits || n_active > a.n_splits)) fetch(slot0, 0, n_active);
   float m = -INFINITY, wsum = 0.f;
   floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
   for (int s0 = 0; s0 < n_active; s0 += 4) {
@@ -543,8 +547,8 @@ static int msa_run(const char* fn, const void* q, const void* k_new, const void*
   if (plan.n_splits > 1 && !(flags & SS_MSA_PARTIALS_ONLY) && a.arrive == nullptr) {
     const long threads = (long)B * R * H * (D / 4);
     dim3 grid((unsigned)((threads + 255) / 256));
-    if (dtype == SS_F32) hipLaunchKernelGGL(msa_combine_kernel<false>, grid, dim3(256), 0, st, a);
-    else hipLaunchKernelGGL(msa_combine_kernel<true>, grid, dim3(256), 0, st, a);
+    auto kern = dtype == SS_F32 ? msa_combine_kernel<false, false> : plan.adaptive ? msa_combine_kernel<true, true> : msa_combine_kernel<true, false>;
+    hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, a);
     if (int rc = check_launch(fn)) return rc;
   }
   return SS_OK;

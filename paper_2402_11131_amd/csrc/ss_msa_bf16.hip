@@ -195,12 +195,16 @@ SS_DEV const MsaArgs& reread_args(const MsaArgs& args) {
 
 // NW = waves (query tiles) per group; it only fixes how the 1 KB load slots of a unit are dealt to
 // the waves of a group.  The number of groups and the ring depth are launch parameters.
+// CUTS: the device may cut the batch anew (several row chunks and long splits, see plan_uneven).  An instance of its own,
+// so that no other launch pays for it: with one instance for all launches of several row chunks those that are never cut
+// took 4 % longer (one sequence of 900 tokens, 8 KV heads of 4 query heads, 96 rows: 20.8 against 20.0 us with the merge
+// kernel).
 // STREAM: the cache is loaded with the streaming hint.  Right when a (sequence, KV head, split) has one row
 // chunk, so that every byte of the cache is wanted by exactly one workgroup; with several row chunks (long GQA
 // trees) the chunks share K/V through the L2 and the hint undoes that (measured: +25 % time).
-template <int D, int NW, bool STREAM>
-__global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves / NW : kMaxGroups)) void msa_bf16_kernel(MsaArgs args, int n_groups, int n_stages) {
-  constexpr bool CUTS = !STREAM;               // the device may cut the batch anew (several row chunks)
+template <int D, int NW, bool STREAM, bool CUTS>
+__global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves / NW : kMaxGroups)) void msa_bf16_kernel(MsaArgs args) {
+  const int n_groups = args.n_groups, n_stages = args.n_stages;
   constexpr int KS = D / 32, DT = D / 16;
   constexpr int K_BYTES = 32 * D * 2;          // K rows of a unit (V takes the same)
   constexpr int STAGE_BYTES = 2 * K_BYTES;
@@ -229,7 +233,9 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = w / NW, wt = w % NW;  // wave group, query tile of this wave
   const bool loader = wt < LW;
-  const int wl = loader ? wt : 0;
+  // Only loading waves use it.  The mask tells the compiler its range: without it the scalar unit chose between the two
+  // halves of a unit at every load of the main loop (2 % of launches of 8 splits of 256 tokens).
+  const int wl = wt & (LW - 1);
   unsigned char* my_stages = stages + (size_t)grp * n_stages * STAGE_BYTES;
   const uint32_t lds_stages = (uint32_t)(uintptr_t)my_stages;
   const uint32_t new_stage = lds_stages + (uint32_t)(n_stages - 1) * STAGE_BYTES;
@@ -244,22 +250,29 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
   // reaches the scalar unit through a lane read.
   // What is kept is the page's offset in the cache in units of 256 bytes (a page of one head is at least
   // 16 x 64 x 2 bytes, and 2^32 such units are 1 TB), so that the scalar unit needs a shift, not a 64-bit product.
+  // The ids are loaded by one function and turned into offsets by another, and the parents are clamped where they are
+  // stored: what is computed from a load is computed after the wait for the whole trip, wherever the compiler would
+  // put it (in front of the loads of the queries it made a launch of 48 us 0.8 us longer).
   uint32_t tab_a = 0, tab_b = 0;
   const int32_t* my_table;
-  auto refill_pages = [&](const MsaArgs& a, int jbase) {
-    const uint32_t page_units = (uint32_t)((size_t)a.Hkv * a.page * D / 128);
-    const int key_cap = max(a.max_pages * a.page - 32, 0) & ~31;  // last 32-key block the table covers
+  const uint32_t page_units = (uint32_t)((size_t)args.Hkv * args.page * D / 128);
+  const int key_cap = max(args.max_pages * args.page - 32, 0) & ~31;  // last 32-key block the table covers
+  auto load_pages = [&](const MsaArgs& a, int jbase) {
     const int kb = min(k0 + 32 * (grp + (jbase + lane) * n_groups), key_cap);
-    tab_a = (uint32_t)min(max(my_table[kb >> a.page_shift], 0), a.num_pages - 1) * page_units;
-    tab_b = (uint32_t)min(max(my_table[min((kb + 16) >> a.page_shift, a.max_pages - 1)], 0), a.num_pages - 1) * page_units;
+    tab_a = (uint32_t)my_table[kb >> a.page_shift];
+    tab_b = (uint32_t)my_table[min((kb + 16) >> a.page_shift, a.max_pages - 1)];
+  };
+  auto page_offsets = [&](const MsaArgs& a) {
+    tab_a = (uint32_t)min(max((int)tab_a, 0), a.num_pages - 1) * page_units;
+    tab_b = (uint32_t)min(max((int)tab_b, 0), a.num_pages - 1) * page_units;
   };
   // this wave's query tile: MFMA B operands (lane (lq, lg) holds features 8*(4*ks+lg).. of folded query row f)
   // Rows of nodes that pruning removed are neither computed nor written: the folded row index runs over the
   // kept rows only (per query head the n_kept main rows, then the n_kept*gamma stream rows of those nodes), so
   // the kept rows fill the first row chunks and the workgroups of the others leave at once.
   int L_raw, n_kept, R_kept, par_v, q_r, q_h;
-  bool f_valid, has_new;  // every sequence has a split 0, which scans the step's own rows
-  bf16x8 Qr[KS];
+  bool f_valid;
+  uintx4 Qraw[KS];
 
   // Rows c0 .. c0+31 of the step's own block -> LDS stage at st_addr: K rows as above, V rows token-major
   // (row r at 2*D*r, chunk position p holding chunk p ^ 2*(r&3)) for the transposing operand read.  Rows past
@@ -282,46 +295,33 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
     }
   };
 
-  {
-  const MsaArgs& a = args;
   // ---- which piece of work: XCD-aware order.  Workgroup ids go round-robin over
   // the 8 XCDs, so ids that are equal mod 8 share an L2: the query chunks of one
   // (sequence, KV head, split) are given such ids and read K/V through one L2.
-  const int G = a.B * a.Hkv * a.n_splits;
+  const int G = args.B * args.Hkv * args.n_splits;
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  qc = slot % a.n_qc;
-  int group = (slot / a.n_qc) * 8 + xcd;
+  qc = slot % args.n_qc;
+  int group = (slot / args.n_qc) * 8 + xcd;
   const bool spare = group >= G;  // has a piece at most where the device cuts the sequences
-  if (spare && !(CUTS && a.adaptive)) return;
-  group = min(group, G - 1);
-  s = group % a.n_splits;
-  hk = (group / a.n_splits) % a.Hkv;
-  b = group / (a.n_splits * a.Hkv);
-  split0_keys = a.split0_keys;
-  split_keys = a.split_keys;
-  slot0 = b * a.n_splits;
+  if (spare && !CUTS) return;
+  if (CUTS) group = min(group, G - 1);
+  s = group % args.n_splits;
+  hk = (group / args.n_splits) % args.Hkv;
+  b = group / (args.n_splits * args.Hkv);
+  split0_keys = args.split0_keys;
+  split_keys = args.split_keys;
+  slot0 = b * args.n_splits;
 
-  // Split 0's first block of the step's own rows travels with the first round trip (its addresses need
-  // nothing from memory), into the last ring stage, which the main loop does not fill before its first barrier.
-  // Where the device may cut the sequences, the lengths of all of them travel with the first trip, which goes out for
-  // the host's cut: if that stands nothing is lost.  Otherwise one wave cuts anew and finds this workgroup's piece,
-  // and the trip is made again.  Pieces keep the order above: those of one sequence together, the splits of a head
-  // next to each other, the live row chunks of a (sequence, KV head, split) on one XCD.
-  int lane_len = 0, lane_kept = a.T;
-  if (CUTS && a.adaptive && lane < a.B) {
-    lane_len = a.seq_lens[lane];
-    lane_kept = kept_nodes(lane, a);
-  }
-#pragma unroll 1
-  for (bool first = true;; first = false) {
-    const MsaArgs& a = reread_args<CUTS>(args);
+  auto first_trip = [&](const MsaArgs& a) {
     k0 = s == 0 ? 0 : split0_keys + (s - 1) * split_keys;
     my_table = a.block_table + (size_t)b * a.max_pages;
-    refill_pages(a, 0);
+    load_pages(a, 0);
     L_raw = a.seq_lens[b];
     n_kept = kept_nodes(b, a);
-    par_v = tid < a.T ? clamp_parent(a.parent[(size_t)b * a.T + tid], tid) : 0;
+    par_v = tid < a.T ? a.parent[(size_t)b * a.T + tid] : 0;
     R_kept = n_kept * (1 + a.gamma);
+  };
+  auto load_queries = [&](const MsaArgs& a) {
     const int f = qc * (16 * NW) + 16 * wt + lq;
     f_valid = f < a.g * R_kept;
     const int f_row = f_valid ? f % R_kept : 0;
@@ -329,76 +329,25 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
     q_h = hk * a.g + (f_valid ? f / R_kept : 0);
     const uint16_t* qp = (const uint16_t*)a.q + (((size_t)b * a.R + q_r) * a.H + q_h) * D + lg * 8;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      uintx4 u = uintx4{0u, 0u, 0u, 0u};
-      if (f_valid) u = ld16(qp + 32 * ks);
-      Qr[ks] = as_bf16x8(u);
-    }
-    has_new = s == 0 && !(spare && n_active == 0) && qc * (16 * NW) < a.g * R_kept;
-    if (has_new && loader && grp < (a.R + 31) >> 5) dma_new(a, 32 * grp, new_stage);
-    if (!CUTS || !first || !a.adaptive) break;
-    const bool even = plan_is_even(a, lane, lane_len, lane_kept);
-    if (even) {
-      if (blockIdx.x == 0 && w == 0 && lane < a.B)
-        a.cut_table[lane] = make_int2(active_splits(clamp_len(lane_len, a), a), lane * a.n_splits);
-      if (spare) return;
-      break;
-    }
-    const int U = len_units(lane_len, a);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing of the abandoned trip is under way to LDS
-    if (w == 0) {
-      const MsaArgs& a = reread_args<CUTS>(args);
-      const SeqCut r = plan_uneven(a, lane, U, lane_kept);
-      const int slots = wave_scan(r.n, lane), groups0 = (slots - r.n) * a.Hkv;  // pieces of earlier sequences
-      const int skip = (groups0 + 7 - xcd) >> 3;    // this XCD takes the pieces that are xcd mod 8
-      const int here = (((slots * a.Hkv + 7 - xcd) >> 3) - skip) * r.chunks;
-      const int upto = wave_scan(here, lane);
-      const int bb = __popcll(__ballot(upto <= slot));
-      if (blockIdx.x == 0 && lane < a.B) a.cut_table[lane] = make_int2(r.n, slots - r.n);
-      if (lane == 0) cut[0] = bb;  // 64: none
-      if (lane == bb) {
-        const int at = slot - (upto - here);
-        const int piece = 8 * (skip + at / r.chunks) + xcd - groups0;
-        cut[1] = piece % r.n;
-        cut[2] = piece / r.n;
-        cut[3] = at % r.chunks;
-        cut[4] = r.n;
-        cut[5] = 32 * r.split0;
-        cut[6] = 32 * r.split;
-        cut[7] = slots - r.n;
-      }
-    }
-    __syncthreads();
-    b = __builtin_amdgcn_readfirstlane(cut[0]);
-    if (b >= 64) return;
-    s = __builtin_amdgcn_readfirstlane(cut[1]);
-    hk = __builtin_amdgcn_readfirstlane(cut[2]);
-    qc = __builtin_amdgcn_readfirstlane(cut[3]);
-    n_active = __builtin_amdgcn_readfirstlane(cut[4]);
-    split0_keys = __builtin_amdgcn_readfirstlane(cut[5]);
-    split_keys = __builtin_amdgcn_readfirstlane(cut[6]);
-    slot0 = __builtin_amdgcn_readfirstlane(cut[7]);
-    __syncthreads();  // `cut` is free: the tree's parents go there
+    for (int ks = 0; ks < KS; ++ks) Qraw[ks] = ld16(qp + 32 * ks);
+  };
+  int lane_len = 0, lane_kept = args.T;  // CUTS: of the lane's sequence
+  if (CUTS && lane < args.B) {
+    lane_len = args.seq_lens[lane];
+    lane_kept = kept_nodes(lane, args);
   }
-  }
+  first_trip(args);
+  if (!CUTS && qc * (16 * NW) >= args.g * R_kept) return;
+  load_queries(args);
 
   const MsaArgs& a = reread_args<CUTS>(args);
   const int R = a.R, T = a.T, F = a.g * R;
   const float c = a.scale_log2;
   const size_t page_stride = (size_t)a.Hkv * a.page * D;  // elements per physical page (K and V alike)
-  const uint16_t* k_head = (const uint16_t*)a.k_cache + (size_t)hk * a.page * D;  // this head inside page 0
-  const uint16_t* v_head = (const uint16_t*)a.v_cache + (size_t)hk * a.page * D;
+  const uint16_t *k_head, *v_head;  // this head inside page 0
   const int pmask = a.page - 1;
   const int n_new_units = (R + 31) >> 5;
 
-  // ---- what there is to do.  The sequence length arrives with the page ids.
-  if (qc * (16 * NW) >= a.g * R_kept) return;
-  const int L = clamp_len(L_raw, a);
-  if (n_active == 0) {
-    n_active = active_splits(L, a);
-    if (s >= n_active) return;
-  }
-  const int k1 = max(k0, min(L, k0 + (s == 0 ? split0_keys : split_keys)));
   floatx4 O[DT];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) O[dt] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -493,6 +442,74 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
     }
   };
 
+  // Split 0's first block of the step's own rows travels with the first round trip (its addresses need
+  // nothing from memory), into the last ring stage, which the main loop does not fill before its first barrier.
+  // Every sequence has a split 0, which scans them.
+  bool has_new = s == 0 && !spare && qc * (16 * NW) < a.g * R_kept;
+  if (has_new && loader && grp < n_new_units) dma_new(a, 32 * grp, new_stage);
+
+  // ---- where the device may cut the sequences: the lengths of all of them travel with the first trip, which goes out for
+  // the host's cut: if that stands little is lost.  Otherwise one wave cuts anew and finds this workgroup's piece, and the
+  // trip is made again.  Pieces keep the order above: those of one sequence together, the splits of a head next to each
+  // other, the live row chunks of a (sequence, KV head, split) on one XCD.
+  if constexpr (CUTS) {
+    if (plan_is_even(a, lane, lane_len, lane_kept)) {
+      if (blockIdx.x == 0 && w == 0 && lane < a.B)
+        a.cut_table[lane] = make_int2(active_splits(clamp_len(lane_len, a), a), lane * a.n_splits);
+      if (spare) return;
+    } else {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing of the abandoned trip is under way to LDS
+      if (w == 0) {
+        const MsaArgs& a = reread_args<CUTS>(args);
+        const SeqCut r = plan_uneven(a, lane, len_units(lane_len, a), lane_kept);
+        const int slots = wave_scan(r.n, lane), groups0 = (slots - r.n) * a.Hkv;  // pieces of earlier sequences
+        const int skip = (groups0 + 7 - xcd) >> 3;    // this XCD takes the pieces that are xcd mod 8
+        const int here = (((slots * a.Hkv + 7 - xcd) >> 3) - skip) * r.chunks;
+        const int upto = wave_scan(here, lane);
+        const int bb = __popcll(__ballot(upto <= slot));
+        if (blockIdx.x == 0 && lane < a.B) a.cut_table[lane] = make_int2(r.n, slots - r.n);
+        if (lane == 0) cut[0] = bb;  // 64: none
+        if (lane == bb) {
+          const int at = slot - (upto - here);
+          const int piece = 8 * (skip + at / r.chunks) + xcd - groups0;
+          cut[1] = piece % r.n;
+          cut[2] = piece / r.n;
+          cut[3] = at % r.chunks;
+          cut[4] = r.n;
+          cut[5] = 32 * r.split0;
+          cut[6] = 32 * r.split;
+          cut[7] = slots - r.n;
+        }
+      }
+      __syncthreads();
+      b = __builtin_amdgcn_readfirstlane(cut[0]);
+      if (b >= 64) return;
+      s = __builtin_amdgcn_readfirstlane(cut[1]);
+      hk = __builtin_amdgcn_readfirstlane(cut[2]);
+      qc = __builtin_amdgcn_readfirstlane(cut[3]);
+      n_active = __builtin_amdgcn_readfirstlane(cut[4]);
+      split0_keys = __builtin_amdgcn_readfirstlane(cut[5]);
+      split_keys = __builtin_amdgcn_readfirstlane(cut[6]);
+      slot0 = __builtin_amdgcn_readfirstlane(cut[7]);
+      __syncthreads();  // `cut` is free: the tree's parents go there
+      const MsaArgs& a = reread_args<CUTS>(args);
+      first_trip(a);
+      load_queries(a);
+      has_new = s == 0 && qc * (16 * NW) < a.g * R_kept;
+      if (has_new && loader && grp < n_new_units) dma_new(a, 32 * grp, new_stage);
+    }
+  }
+  k_head = (const uint16_t*)a.k_cache + (size_t)hk * a.page * D;
+  v_head = (const uint16_t*)a.v_cache + (size_t)hk * a.page * D;
+  // ---- what there is to do.  The sequence length arrives with the page ids; what needs neither is done before (with
+  // the length looked at first, launches of a few microseconds took 2 % longer).
+  const int L = clamp_len(L_raw, a);
+  if (CUTS && qc * (16 * NW) >= a.g * R_kept) return;
+  if (n_active == 0) {
+    n_active = active_splits(L, a);
+    if (s >= n_active) return;
+  }
+  const int k1 = max(k0, min(L, k0 + (s == 0 ? split0_keys : split_keys)));
   // Units of this split: full 32-key blocks of the prefix (ring-buffered main loop of n_main iterations,
   // one block per group and iteration; group grp has n_mine of them) and its ragged last block.
   const int n_full = (k1 - k0) >> 5;
@@ -505,7 +522,13 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
   // all of them too.
   asm volatile("s_waitcnt vmcnt(0)" : "+v"(tab_a), "+v"(tab_b), "+v"(par_v)::"memory");
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(Qr[ks]));
+  for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(Qraw[ks]));
+  page_offsets(a);
+  // padding rows fetched row 0 and become zeros here (a load under a condition, with zeros otherwise, made the compiler
+  // wait in the middle of the trip)
+  bf16x8 Qr[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) Qr[ks] = as_bf16x8(f_valid ? Qraw[ks] : uintx4{0u, 0u, 0u, 0u});
 
   // ---- second round trip: the first blocks of the prefix.
   const int n_pre = min(n_mine, n_stages - 1);
@@ -513,7 +536,7 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
     for (int i = 0; i < n_pre; ++i)
       dma_main(grp + i * n_groups, __builtin_amdgcn_readlane(tab_a, i), __builtin_amdgcn_readlane(tab_b, i),
                lds_stages + (uint32_t)i * STAGE_BYTES);
-  if (tid < T) par[tid] = par_v;
+  if (tid < T) par[tid] = clamp_parent(par_v, tid);
   __syncthreads();
   compute_anc(par, T, anc, tid);
   __syncthreads();
@@ -645,7 +668,10 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
       __syncthreads();
       const int jl = it + n_stages - 1;
       if (loader && jl < n_mine) {
-        if ((jl & 63) == 0) refill_pages(a, jl);
+        if ((jl & 63) == 0) {
+          load_pages(a, jl);
+          page_offsets(a);
+        }
         dma_main(grp + jl * n_groups, __builtin_amdgcn_readlane(tab_a, jl & 63), __builtin_amdgcn_readlane(tab_b, jl & 63),
                  lds_stages + (uint32_t)st_fill * STAGE_BYTES);
       }
@@ -705,7 +731,7 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
   const bool prefetched = others_ready && n_active == 2 && f_valid;
   float l_other = -INFINITY;
   floatx4 o_other[DT];
-  auto part_row = [&](int sp) { return ((size_t)(slot0 + sp) * a.H + q_h) * R + q_r; };
+  auto part_row = [&](int sp) { return part_row_of<CUTS>(a, b, slot0, sp, q_h, q_r); };
   const size_t pr_other = part_row(s_other);
   if (prefetched) ld_row_device<DT>(a.part_lse + pr_other, a.part_o + pr_other * D + 4 * lg, l_other, o_other);
 
@@ -834,7 +860,7 @@ static int stages_for(int n_groups, int wanted, size_t stage_bytes, int lpb) {
   return n < 2 ? 2 : n;
 }
 
-template <int D, int NW, bool STREAM>
+template <int D, int NW, bool STREAM, bool CUTS>
 static int launch_dns(const MsaArgs& a, hipStream_t stream) {
   const int n_groups = groups_for(NW, a.groups);
   const int G = a.B * a.Hkv * a.n_splits;
@@ -848,7 +874,7 @@ static int launch_dns(const MsaArgs& a, hipStream_t stream) {
   if (merge_bytes > lds) lds = merge_bytes;
   lds += SS_MAX_T * 4 + SS_MAX_T * 8 + (size_t)n_groups * NW * 32 * 4;
   SS_REQUIRE(lds <= 160 * 1024, SS_ERR_UNSUPPORTED, "ss_msa_attention: %zu bytes of LDS needed", lds);
-  auto kern = msa_bf16_kernel<D, NW, STREAM>;
+  auto kern = msa_bf16_kernel<D, NW, STREAM, CUTS>;
   static std::once_flag attr_once;
   static hipError_t attr_err = hipSuccess;
   std::call_once(attr_once, [&]() {
@@ -856,13 +882,20 @@ static int launch_dns(const MsaArgs& a, hipStream_t stream) {
   });
   if (attr_err != hipSuccess)
     SS_FAIL(SS_ERR_HIP, "ss_msa_attention: hipFuncSetAttribute: %s", hipGetErrorString(attr_err));
-  hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(64 * NW * n_groups), lds, stream, a, n_groups, n_stages);
+  MsaArgs launch = a;
+  launch.n_groups = n_groups;
+  launch.n_stages = n_stages;
+  hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(64 * NW * n_groups), lds, stream, launch);
   return check_launch("ss_msa_attention");
 }
 
+// Chunks of 16 and 32 rows are all of a KV head's rows (msa_bf16_rows_per_chunk).
 template <int D, int NW>
 static int launch_dn(const MsaArgs& a, hipStream_t stream) {
-  return a.n_qc == 1 ? launch_dns<D, NW, true>(a, stream) : launch_dns<D, NW, false>(a, stream);
+  if constexpr (NW > 2) {
+    if (a.n_qc > 1) return a.adaptive ? launch_dns<D, NW, false, true>(a, stream) : launch_dns<D, NW, false, false>(a, stream);
+  }
+  return launch_dns<D, NW, true, false>(a, stream);
 }
 
 template <int D>
