@@ -67,11 +67,12 @@ SS_DEV size_t part_row_of(const MsaArgs& a, int b, int slot0, int s, int h, int 
 // hold (and, after pruning, how many row chunks they have) is known on the device only.  As long as every sequence
 // fills at least 7/8 of the capacity and no node was removed, the host's lengths are within that much of the best
 // and are used as they are.  Otherwise the lengths are chosen here, by one wavefront, from 64 candidates: the one
-// with the least (rounds of 256 workgroups) x (blocks per workgroup + 4, its fixed cost), among those whose splits
-// fit the B x S slots of the workspace.  Lane b holds sequence b, so this is for B <= kAdaptiveMaxB.
-// Measured with the merge kernel, per layer: two sequences of 9005 and 3001 tokens (8 KV heads of 4 query heads, 24
-// nodes) in a table of 1.8 times the capacity 63 -> 48 us; eight of 2000..8192 tokens with a third to two thirds of
-// 32 nodes kept 217 -> 168 us.
+// with the least (rounds of the 32 workgroups an XCD holds) x (blocks per workgroup + 4, its fixed cost), among those
+// whose splits fit the B x S slots of the workspace.  Lane b holds sequence b, so this is for B <= kAdaptiveMaxB.
+// Measured with the merge kernel, host's cut against this: two sequences of 9005 and 3001 tokens (8 KV heads of 4 query
+// heads, 24 nodes) in a table of 1.8 times the capacity 59.7 and 43.3 us; eight of 2000..8192 tokens with a third to two
+// thirds of 32 nodes kept 179 and 135 us; three of 16000, 9005 and 3001 with 4 KV heads 126 and 77 us (84 with the pieces
+// of a sequence rounded up to whole eights).
 constexpr int kAdaptiveMaxB = 64;
 SS_HD int len_units(int L, const MsaArgs& a) { return (clamp_len(L, a) + 31) >> 5; }
 SS_HD bool seq_is_even(const MsaArgs& a, int len, int kept) { return len >= a.even_len && kept == a.T; }
@@ -119,16 +120,20 @@ SS_HD int cut_candidate(const MsaArgs& a, int j, CutRange r) {
 template <class Load, class Chunks>
 SS_HD float cut_cost(const MsaArgs& a, int c, Load load, Chunks chunks) {
   const float rc = 1.f / (float)c;
-  int slots = 0, wgs = 0;
+  int slots = 0, xcd0 = 0, all = 0;
   for (int i = 0; i < a.B; ++i) {
     const int up = load(i) + c - 1;
     int q = (int)((float)up * rc);  // off by one at most
     const int rem = up - q * c;
     q += (rem >= c) - (rem < 0);
+    const int before = slots * a.Hkv, after = before + q * a.Hkv;  // pieces, dealt to the XCDs in turn
     slots += q;
-    wgs += ((q * a.Hkv + 7) >> 3) * chunks(i);
+    xcd0 += (((after + 7) >> 3) - ((before + 7) >> 3)) * chunks(i);
+    all += (after - before) * chunks(i);
   }
-  const int rounds = (wgs + 31) >> 5;  // of the 32 workgroups an XCD holds; wgs: those of the XCD with the most
+  // Rounds of the 32 workgroups an XCD holds, on the XCD with the most: XCD 0 has as many pieces as any, and where the
+  // sequences' row chunks differ at least the average.
+  const int rounds = (max(xcd0, (all + 7) >> 3) + 31) >> 5;
   return slots <= a.B * a.n_splits ? (float)rounds * (float)(c + 4) : INFINITY;
 }
 // Of one sequence: cached blocks of split 0 and of the others, number of splits, row chunks with kept rows.

@@ -120,3 +120,33 @@ def test_cut_of_an_uneven_batch_fits_the_workspace():
         r = subprocess.run([sys.executable, "-c", code], env=dict(os.environ, SS_MSA_SPLIT0_EXTRA=str(extra)), cwd=root,
                            stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
         assert r.returncode == 0, (extra, r.stdout[-2000:])
+
+
+def _cut_by_hand(B, T, gamma, H, Hkv, n_slots, chunk_rows, groups, lens, n=None):
+    """Cost of a cut by its own rule, rounds of the busiest XCD (workgroups are dealt to eight XCDs in turn, 32 at a
+    time) x (blocks of the longest split + 4): of the cut n, or the least of all split lengths."""
+    new = -(-T * (1 + gamma) // 32) + 2
+    load = [-(-x // 32) + new for x in lens]
+    chunks = -(-(H // Hkv) * T * (1 + gamma) // chunk_rows)
+
+    def cost(c, n):
+        return -(-(-(-sum(n) * Hkv // 8) * chunks) // 32) * (c + 4)
+    if n is not None:
+        return cost(max(-(-(-(-x // k)) // groups) * groups for x, k in zip(load, n)), n)
+    cuts = [(c, [-(-x // c) for x in load]) for c in range(8, max(load) + groups, groups)]
+    return min(cost(c, n) for c, n in cuts if sum(n) <= n_slots)
+
+
+def test_cut_counts_the_workgroups_of_the_busiest_xcd():
+    # four KV heads: the pieces of two sequences share the rounds of the eight XCDs
+    rng = synth.rng_for(11)
+    for B, T, gamma, H, Hkv, cap, chunk_rows, groups in ((2, 24, 3, 32, 4, 16256, 128, 2), (3, 24, 3, 32, 4, 16256, 128, 2),
+                                                         (5, 8, 3, 24, 4, 16384, 64, 3), (2, 24, 3, 32, 8, 16256, 128, 2)):
+        most, _ = api.ss_msa_plan(B, T, gamma, H, Hkv, 128, cap, api.SS_BF16)
+        for _ in range(100):
+            lens = [int(x) for x in rng.integers(cap // 8, cap // 2, B)]
+            where, n = api.ss_msa_plan_splits(B, T, gamma, H, Hkv, 128, cap, api.SS_BF16, lens)
+            assert where == 2
+            args = (B, T, gamma, H, Hkv, B * most, chunk_rows, groups, lens)
+            # 64 candidates between 8 and some 300 blocks lie 6 % apart, and are rounded up to whole wave groups
+            assert _cut_by_hand(*args, n=n) <= 1.15 * _cut_by_hand(*args), (lens, n)
