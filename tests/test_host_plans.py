@@ -150,3 +150,12 @@ def test_cut_counts_the_workgroups_of_the_busiest_xcd():
             args = (B, T, gamma, H, Hkv, B * most, chunk_rows, groups, lens)
             # 64 candidates between 8 and some 300 blocks lie 6 % apart, and are rounded up to whole wave groups
             assert _cut_by_hand(*args, n=n) <= 1.15 * _cut_by_hand(*args), (lens, n)
+
+
+def test_shapes_of_the_uneven_batches_are_of_the_kind_they_stand_for():
+    import test_gpu_msa_uneven as t
+    for name in t.CASES:
+        where, _ = api.ss_msa_plan_splits(*t._shape(name), t.CASES[name][7])
+        assert where == (2 if name in t.CUT else 0), name
+    plans = [api.ss_msa_plan(*t._shape(name)) for name in t.CUT]
+    assert (2, 1) in plans and any(n > 2 for n, _ in plans)      # merged in the attention kernel, and by the merge kernel
