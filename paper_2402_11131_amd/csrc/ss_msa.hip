@@ -20,10 +20,10 @@ namespace ss {
 //
 // Small problems are all latency: a tile's values are fetched into registers while the tile before is computed, with
 // one page lookup per lane (the wave's other lanes' rows come by lane reads), and operands leave LDS four at a time.
-// RW = 8, or 2 where chunks of 32 rows would be too few workgroups (see the launch).  One layer of
-// 4 heads of 64, 128 cached tokens, 32 rows: 45.6 us before, with eight rows per wave,
-// a lookup and an uncovered load per value; with the fp32 LM head (1000 ids) the whole step 91 -> 28 us, and where RW
-// is 8 either way (4 sequences of 500..1000 tokens, 192 rows, 8 heads) the attention 174 -> 106 us.
+// RW = 8, or 2 (see the launch).  One layer of 4 heads of 64, 128 cached tokens, 32 rows: 45.6 us before, with eight rows
+// per wave, a lookup and an uncovered load per value; with the fp32 LM head (1000 ids) the whole step 91 -> 28 us, and
+// where RW is 8 either way (4 sequences of 500..1000 tokens, 192 rows, 8 heads) the attention 174 -> 106 us.  Heads of
+// 128: 16 of them over 8192 tokens 397 -> 184 us, 256 over 1000 tokens with 192 rows 5185 -> 1876 us.
 template <int D, int RW>
 __global__ __launch_bounds__(256) void msa_f32_kernel(MsaArgs a) {
   constexpr int RC = 4 * RW, KT = 64, DL = D / 64;
@@ -532,13 +532,15 @@ static int msa_run(const char* fn, const void* q, const void* k_new, const void*
   if (flags & SS_MSA_MERGE_ONLY) {
     // the attention kernel ran in an earlier call with SS_MSA_PARTIALS_ONLY
   } else if (dtype == SS_F32) {
-    // Rows per workgroup of the fp32 kernel: 8 instead of 32 while chunks of 32 are at most 64 workgroups a split, so
-    // that four times as many still fit the chip at once (they read K and V four times as often, from the L2).
-    const bool few = (long)B * H * plan.n_qc <= 64;
+    // Rows per workgroup of the fp32 kernel, by the workgroups that chunks of 32 rows and the splits really make.  D = 64:
+    // 8 while those are fewer than 512 (us with 8 and with 32 rows; 128: 32 and 64, 256: 46 and 66, 384: 67 and 81, 512: 75
+    // and 71 or 124 and 113, 768: 174 and 129): smaller workgroups hide more latency but read K and V four times as often.
+    // D = 128: always 8, two workgroups per compute unit (75 KB of LDS) where of 32 rows (93 KB) only one fits (256: 99 and
+    // 119, 512: 184 and 236, 1536 over 1000 tokens: 1876 and 2431, 4608 with 576 rows: 5586 and 6738).
+    const bool few = D == 128 || (long)B * H * plan.n_qc * plan.n_splits < 512;
     dim3 grid(few ? ceil_div(R, 8) : plan.n_qc, plan.n_splits, B * H);
     SS_REQUIRE((long)B * H <= 65535 && plan.n_splits <= 65535, SS_ERR_UNSUPPORTED, "%s: grid too large", fn);
-    auto kern = D == 64 ? (few ? msa_f32_kernel<64, 2> : msa_f32_kernel<64, 8>)
-                        : (few ? msa_f32_kernel<128, 2> : msa_f32_kernel<128, 8>);
+    auto kern = D == 128 ? msa_f32_kernel<128, 2> : few ? msa_f32_kernel<64, 2> : msa_f32_kernel<64, 8>;
     hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, a);
     if (int rc = check_launch(fn)) return rc;
   } else {

@@ -11,7 +11,19 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-# 64 workgroups of 32 rows are cut into smaller ones, 65 and more are not
+# Heads of 64: 511 workgroups of 32 rows (chunks, splits and heads) are cut into smaller ones, 512 and more are not
+@pytest.mark.parametrize("B,H,R,L,keys,wgs", [(7, 73, 32, 70, 0, 511), (8, 64, 32, 70, 0, 512), (4, 16, 32, 448, 64, 448), (4, 16, 32, 512, 64, 512),
+                                             (4, 16, 33, 193, 64, 512), (3, 9, 33, 500, 64, 432)])
+def test_attention_at_the_choice_of_rows(B, H, R, L, keys, wgs):
+    before = api.ss_msa_set_split_keys(keys)
+    try:
+        n, _ = api.ss_msa_plan(B, R, 0, H, H, 64, -(-L // 16) * 16, api.SS_F32)
+        assert B * H * -(-R // 32) * n == wgs
+        test_attention(B, H, H, 64, R, 0, L)
+    finally:
+        api.ss_msa_set_split_keys(before)
+
+
 @pytest.mark.parametrize("B,H,Hkv,D,T,gamma,L", [(4, 16, 4, 64, 8, 3, 70), (5, 13, 13, 64, 8, 3, 70), (2, 4, 2, 128, 11, 2, 1),
                                                  (9, 4, 4, 128, 17, 1, 129), (1, 2, 1, 128, 1, 0, 0), (3, 4, 4, 64, 5, 1, 700)])
 def test_attention(B, H, Hkv, D, T, gamma, L):
