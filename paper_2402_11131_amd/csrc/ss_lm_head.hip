@@ -73,8 +73,8 @@ SS_DEV int key_id(uint64_t k) { return k == 0 ? INT_MAX : (int)(0xffffffffu - (u
 //
 // Workgroup tile BM (32 or 8) rows x 64 vocabulary columns, feature chunks of 64 through LDS (rows padded by 16
 // bytes: 16-byte reads of 16 lanes meet 64 different banks), the next chunk on its way to registers meanwhile;
-// thread (wave w, lane c) accumulates rows w, w+4, ... of column c.  8 rows where tiles of 32 would be fewer than 256
-// workgroups: 32 rows x 256 features x 1000 ids took 40.4 us in 16 workgroups with nothing in flight (the step it
+// thread (wave w, lane c) accumulates rows w, w+4, ... of column c.  8 rows where tiles of 32 would be few (see
+// launch_lm_f32): 32 rows x 256 features x 1000 ids took 40.4 us in 16 workgroups with nothing in flight (the step it
 // is half of: 91 -> 28 us).
 //
 // MODE 0: top-K search.  MODE 1: the plain projection, the tile is written to y.  MODE 2: (max, sum of
@@ -880,13 +880,19 @@ static LmFlavour lm_choose(int N, int V, LmArgs* a, bool six_waves_ok = false) {
   return best;
 }
 
+// plan_rows: rows that are likely computed (all N, or what the caller says of the listed ones).
 template <int MODE>
-static int launch_lm_f32(const char* fn, hipStream_t st, const LmArgs& a) {
+static int launch_lm_f32(const char* fn, hipStream_t st, const LmArgs& a, int plan_rows) {
   const int chunks = ceil_div(a.N, 32);
   SS_REQUIRE(chunks <= 65535, SS_ERR_UNSUPPORTED, "%s: N too large", fn);
-  // eight rows per workgroup while tiles of 32 leave the chip partly empty (see the kernel)
-  if ((long)a.n_tiles * chunks < 256) hipLaunchKernelGGL((lm_head_f32_kernel<MODE, 8>), dim3(a.n_tiles, ceil_div(a.N, 8)), dim3(256), 0, st, a);
-  else hipLaunchKernelGGL((lm_head_f32_kernel<MODE, 32>), dim3(a.n_tiles, chunks), dim3(256), 0, st, a);
+  // Eight rows per workgroup while they are at most 3200 (us with 8 and with 32 rows per workgroup, the latter's number; 625:
+  // 54 and 70, 640: 178 and 287, 790: 34 and 38; then 960: 256 and 297, 1000: 82 and 75, 1020: 37 and 33: they hide more
+  // latency but read W four times as often), and for eight rows or fewer, where 32 are mostly padding (4000: 100 and 356).
+  const int eights = ceil_div(a.N, 8);
+  if (eights <= 65535 && (plan_rows <= 8 || (long)a.n_tiles * ceil_div(plan_rows, 8) <= 3200))
+    hipLaunchKernelGGL((lm_head_f32_kernel<MODE, 8>), dim3(a.n_tiles, eights), dim3(256), 0, st, a);
+  else
+    hipLaunchKernelGGL((lm_head_f32_kernel<MODE, 32>), dim3(a.n_tiles, chunks), dim3(256), 0, st, a);
   return check_launch(fn);
 }
 
@@ -1026,7 +1032,7 @@ static int lm_candidates(const char* fn, const void* hidden, const void* W, int 
   a.live_rows = sel.rows; a.n_live = sel.n;
   a.n_ksplit = 1; a.part = nullptr;
   if (dtype == SS_F32) {
-    if (int rc = launch_lm_f32<0>(fn, st, a)) return rc;
+    if (int rc = launch_lm_f32<0>(fn, st, a, plan_n(sel, N))) return rc;
   } else {
     LmFlavour f = lm_choose(plan_n(sel, N), V, &a);
     lm_flavour_override(false, plan_n(sel, N), V, &f, &a);
@@ -1169,7 +1175,7 @@ int ss_lm_head_logsumexp(const void* hidden, const void* W, int N, int d, int V,
   a.n_ksplit = 1; a.part = nullptr;
   hipStream_t st = (hipStream_t)stream;
   if (dtype == SS_F32) {
-    if (int rc = launch_lm_f32<2>(fn, st, a)) return rc;
+    if (int rc = launch_lm_f32<2>(fn, st, a, N)) return rc;
   } else {
     LmFlavour f = lm_choose(N, V, &a);
     lm_flavour_override(false, N, V, &f, &a);
@@ -1200,7 +1206,7 @@ static int linear_run(const char* fn, const void* x, const void* W, int N, int d
   a.y = y;
   hipStream_t st = (hipStream_t)stream;
   if (dtype == SS_F32) {
-    if (int rc = launch_lm_f32<1>(fn, st, a)) return rc;
+    if (int rc = launch_lm_f32<1>(fn, st, a, plan_n(sel, N))) return rc;
   } else {
     LmFlavour f = lm_choose(plan_n(sel, N), V, &a, true);
     lm_flavour_override(true, plan_n(sel, N), V, &f, &a);

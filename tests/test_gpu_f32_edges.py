@@ -37,7 +37,7 @@ def test_attention(B, H, Hkv, D, T, gamma, L):
     assert rel_err(to_np_f32(got), want) <= 1e-5     # the fp32 path's tolerance
 
 
-# 255 and 256 tiles of 64 ids x 32 rows; features and ids with remainders
+# Features and ids with remainders
 @pytest.mark.parametrize("N,d,V", [(1, 1, 1), (7, 63, 65), (33, 65, 64 * 127 + 1), (32, 64, 64 * 255), (32, 64, 64 * 255 + 1), (70, 130, 6000)])
 def test_projection(N, d, V):
     rng = synth.rng_for(N + d + V)
@@ -46,3 +46,23 @@ def test_projection(N, d, V):
     want = x.astype(np.float64) @ W.astype(np.float64).T
     bound = (d + 1) * 2.0 ** -24 * (np.abs(x).astype(np.float64) @ np.abs(W).astype(np.float64).T)   # d rounded steps
     assert (np.abs(got - want) <= bound).all()
+
+
+# 3200 workgroups of eight rows and one more; of listed rows the launch is shaped for plan_rows, whatever their number
+@pytest.mark.parametrize("N,V,plan,live", [(64, 64 * 400, 64, 64), (64, 64 * 400 + 1, 64, 64), (8, 64 * 3201, 8, 8), (70, 6400, 8, 70), (70, 6400, 70, 9),
+                                           (300, 64 * 100, 40, 33)])
+def test_projection_of_listed_rows(N, V, plan, live):
+    d = 67
+    rng = synth.rng_for(N + V + plan)
+    x, W = rng.standard_normal((N, d), np.float32), rng.standard_normal((V, d), np.float32)
+    rows = np.sort(rng.permutation(N)[:live]).astype(np.int32)
+    listed = torch.zeros(N, dtype=torch.int32)
+    listed[:live] = torch.from_numpy(rows)
+    y = torch.full((N, V), 3.0, device=DEV)
+    api.ss_linear_rows(torch.from_numpy(x).to(DEV), torch.from_numpy(W).to(DEV), y, plan_rows=plan,
+                       live=(listed.to(DEV), torch.tensor([live], dtype=torch.int32, device=DEV)))
+    got = y.cpu().numpy()
+    want = x[rows].astype(np.float64) @ W.astype(np.float64).T
+    bound = (d + 1) * 2.0 ** -24 * (np.abs(x[rows]).astype(np.float64) @ np.abs(W).astype(np.float64).T)   # d rounded steps
+    assert (np.abs(got[rows] - want) <= bound).all()
+    assert (np.delete(got, rows, axis=0) == 3.0).all()
