@@ -233,7 +233,8 @@ int ss_msa_plan(int B, int T, int gamma, int H, int Hkv, int D, int max_seq_len,
 
 /*
  * How a2 would split sequences of these lengths.  Without pruning and with every
- * sequence at 7/8 of max_seq_len or more the split lengths are ss_msa_plan's.
+ * sequence at 7/8 of max_seq_len or more (large launches: with 7/8 of the whole
+ * batch's work) the split lengths are ss_msa_plan's.
  * Otherwise launches with several row chunks and long splits choose the lengths
  * on the device, from the lengths and kept nodes of the whole batch: the
  * boundaries, and so the rounding, of one sequence's result then depend on the

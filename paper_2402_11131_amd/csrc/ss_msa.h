@@ -37,6 +37,7 @@ struct MsaArgs {
                     // kernel leaves in the workspace for the merge kernel; else NULL
   int adaptive;    // 1: a batch the host's split lengths do not fit is cut anew on the device (plan_uneven)
   int even_len;    // 7/8 of the capacity, in tokens
+  float even_work; // 7/8 of the whole plan's blocks times row chunks, or 0: not looked at (plan_is_even)
   int new_units;   // blocks' worth of time that scanning the step's own rows costs split 0
   int max_n;       // most splits per sequence plan_uneven may make (2: merged in the kernel; else 0 = no limit)
   int min_units;   // shortest split plan_uneven considers, in blocks
@@ -64,11 +65,12 @@ SS_DEV size_t part_row_of(const MsaArgs& a, int b, int slot0, int s, int h, int 
 }
 
 // ---- splits cut on the device.  The host plans from the capacity of the block table; what the sequences really
-// hold (and, after pruning, how many row chunks they have) is known on the device only.  As long as every sequence
-// fills at least 7/8 of the capacity and no node was removed, the host's lengths are within that much of the best
-// and are used as they are.  Otherwise the lengths are chosen here, by one wavefront, from 64 candidates: the one
-// with the least (rounds of the 32 workgroups an XCD holds) x (blocks per workgroup + 4, its fixed cost), among those
-// whose splits fit the B x S slots of the workspace.  Lane b holds sequence b, so this is for B <= kAdaptiveMaxB.
+// hold (and, after pruning, how many row chunks they have) is known on the device only.  Where the
+// host's cut stands (plan_is_even) it is used as it is.  Otherwise the lengths are chosen here, by one wavefront, from 64
+// candidates: the one with the least (rounds of the 32 workgroups an XCD holds) x (blocks per workgroup + 4, its fixed
+// cost), among those whose splits fit the B x S slots of the workspace.  (Fixed costs of 0, 2, 8, 16 instead of 4: 20
+// random batches of fewer than 256 items within 0.2 %, four of 320 items +2.4, 0, -1.4, -3.3 %.)  Lane b holds sequence b,
+// so this is for B <= kAdaptiveMaxB.
 // Measured with the merge kernel, host's cut against this: two sequences of 9005 and 3001 tokens (8 KV heads of 4 query
 // heads, 24 nodes) in a table of 1.8 times the capacity 59.7 and 43.3 us; eight of 2000..8192 tokens with a third to two
 // thirds of 32 nodes kept 179 and 135 us; three of 16000, 9005 and 3001 with 4 KV heads 126 and 77 us (84 with the pieces
@@ -76,9 +78,6 @@ SS_DEV size_t part_row_of(const MsaArgs& a, int b, int slot0, int s, int h, int 
 constexpr int kAdaptiveMaxB = 64;
 SS_HD int len_units(int L, const MsaArgs& a) { return (clamp_len(L, a) + 31) >> 5; }
 SS_HD bool seq_is_even(const MsaArgs& a, int len, int kept) { return len >= a.even_len && kept == a.T; }
-SS_DEV bool plan_is_even(const MsaArgs& a, int lane, int len, int kept) {
-  return __all(lane >= a.B || seq_is_even(a, len, kept));
-}
 SS_DEV int wave_sum(int v) {
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
   return v;
@@ -148,6 +147,21 @@ SS_HD SeqCut cut_of(const MsaArgs& a, int cut, int U, int chunks) {
   r.n = U <= r.split0 ? 1 : 1 + (U - r.split0 + r.split - 1) / r.split;  // <= q
   r.chunks = chunks;
   return r;
+}
+// The host's cut stands when every sequence fills 7/8 of the capacity and no node was removed.  With 256 items or more
+// also when what there is to do, blocks times row chunks over all sequences, is 7/8 of what the host planned for: each
+// round of workgroups pays 2.6 us for cutting anew, and only that much less work makes up for it (eight sequences of up to
+// 8192 tokens, 160 rows, 320 items in 5 rounds, us with the host's and with the device's cut: all full 246 and 259, at 9/10
+// 237 and 241, at 7/8 236 and 235, at 0.7 234 and 209; one of them at 1/2, the others full 240 and 253).  With fewer items
+// the device's cut is the better one full or not (48 items over 16384 tokens 112 and 75, 96 over 8192 114 and 86; one
+// of two sequences at 0.8 105 and 72): the host's plan does not count rounds there.
+SS_HD float seq_work(const MsaArgs& a, int len, int kept) { return (float)len_units(len, a) * (float)cut_chunks(a, kept); }
+SS_DEV bool plan_is_even(const MsaArgs& a, int lane, int len, int kept) {
+  if (__all(lane >= a.B || seq_is_even(a, len, kept))) return true;
+  if (a.even_work == 0.f) return false;
+  float work = lane < a.B ? seq_work(a, len, kept) : 0.f;
+  for (int off = 32; off > 0; off >>= 1) work += __shfl_xor(work, off, 64);
+  return __all(work >= a.even_work);  // the same in every lane, and known to be
 }
 SS_DEV SeqCut plan_uneven(const MsaArgs& a, int lane, int U, int kept) {
   const bool mine = lane < a.B;

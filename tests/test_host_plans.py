@@ -152,6 +152,22 @@ def test_cut_counts_the_workgroups_of_the_busiest_xcd():
             assert _cut_by_hand(*args, n=n) <= 1.15 * _cut_by_hand(*args), (lens, n)
 
 
+def test_cut_stands_where_little_less_than_planned_is_to_do():
+    shape = lambda B, T: (B, T, 4, 32, 8, 128, 8192, api.SS_BF16)
+    where = lambda B, T, lens, kept=None: api.ss_msa_plan_splits(*shape(B, T), lens, kept)[0]
+    full = [8192] * 7
+    assert where(8, 32, full + [8192]) == 1
+    # 320 items: the whole batch's work counts
+    assert where(8, 32, full + [4096]) == 1 and where(8, 32, full + [0]) == 1
+    assert where(8, 32, [7168] * 8) == 1 and where(8, 32, [7136] * 8) == 2     # 7/8 of the capacity, and a block less
+    assert where(8, 32, [8192] * 6 + [4096, 0]) == 2
+    assert where(8, 32, full + [8192], [32] * 7 + [1]) == 1                    # one sequence pruned to one chunk of five
+    assert where(8, 32, full + [8192], [26] * 8) == 1                          # fewer nodes, the same five chunks
+    assert where(8, 32, full + [8192], [25] * 8) == 2                          # four chunks
+    # 160 items: one sequence that is short
+    assert where(4, 32, [8192] * 4) == 1 and where(4, 32, [8192] * 3 + [7000]) == 2
+
+
 def test_shapes_of_the_uneven_batches_are_of_the_kind_they_stand_for():
     import test_gpu_msa_uneven as t
     for name in t.CASES:
