@@ -37,7 +37,7 @@ struct MsaArgs {
                     // kernel leaves in the workspace for the merge kernel; else NULL
   int adaptive;    // 1: a batch the host's split lengths do not fit is cut anew on the device (plan_uneven)
   int even_len;    // 7/8 of the capacity, in tokens
-  float even_work; // 7/8 of the whole plan's blocks times row chunks, or 0: not looked at (plan_is_even)
+  int even_work;   // 7/8 of the whole plan's blocks times row chunks, or 0: not looked at (plan_is_even)
   int new_units;   // blocks' worth of time that scanning the step's own rows costs split 0
   int max_n;       // most splits per sequence plan_uneven may make (2: merged in the kernel; else 0 = no limit)
   int min_units;   // shortest split plan_uneven considers, in blocks
@@ -155,13 +155,16 @@ SS_HD SeqCut cut_of(const MsaArgs& a, int cut, int U, int chunks) {
 // 237 and 241, at 7/8 236 and 235, at 0.7 234 and 209; one of them at 1/2, the others full 240 and 253).  With fewer items
 // the device's cut is the better one full or not (48 items over 16384 tokens 112 and 75, 96 over 8192 114 and 86; one
 // of two sequences at 0.8 105 and 72): the host's plan does not count rounds there.
-SS_HD float seq_work(const MsaArgs& a, int len, int kept) { return (float)len_units(len, a) * (float)cut_chunks(a, kept); }
+// Every wave comes to this before it knows its piece, so the sum is the scalar unit's (a lane read and an add per sequence)
+// and the division by the chunk's rows one by a constant.
+template <int CHUNK_ROWS>
 SS_DEV bool plan_is_even(const MsaArgs& a, int lane, int len, int kept) {
   if (__all(lane >= a.B || seq_is_even(a, len, kept))) return true;
-  if (a.even_work == 0.f) return false;
-  float work = lane < a.B ? seq_work(a, len, kept) : 0.f;
-  for (int off = 32; off > 0; off >>= 1) work += __shfl_xor(work, off, 64);
-  return __all(work >= a.even_work);  // the same in every lane, and known to be
+  if (a.even_work == 0) return false;
+  const int work = len_units(len, a) * ((a.g * kept * (1 + a.gamma) + CHUNK_ROWS - 1) / CHUNK_ROWS);
+  int sum = 0;
+  for (int i = 0; i < a.B; ++i) sum += __builtin_amdgcn_readlane(work, i);
+  return sum >= a.even_work;
 }
 SS_DEV SeqCut plan_uneven(const MsaArgs& a, int lane, int U, int kept) {
   const bool mine = lane < a.B;

@@ -402,7 +402,8 @@ static void set_plan(MsaArgs& a, const MsaPlan& plan, int B, int T, int gamma, i
   a.split_keys = plan.split_keys; a.split0_keys = plan.split0_keys; a.n_splits = plan.n_splits; a.n_qc = plan.n_qc; a.groups = plan.groups; a.stages = plan.stages;
   a.max_n = plan.n_splits == 2 && dtype == SS_BF16 ? 2 : 0;  // also where the merge kernel does it: the same cut either way
   a.even_len = max_len - max_len / 8;
-  a.even_work = (long)B * Hkv * plan.n_qc >= 256 ? 0.875f * (float)B * (float)ceil_div(max_len, 32) * (float)plan.n_qc : 0.f;
+  const double whole = (double)B * ceil_div(max_len, 32) * plan.n_qc;
+  a.even_work = (long)B * Hkv * plan.n_qc >= 256 && whole < INT_MAX ? (int)ceil(0.875 * whole) : 0;
   a.adaptive = plan.adaptive; a.new_units = plan.new_units; a.min_units = plan.min_units; a.chunk_rows = plan.chunk_rows;
 }
 
@@ -594,19 +595,19 @@ int ss_msa_plan_splits(int B, int T, int gamma, int H, int Hkv, int D, int max_s
   a.max_pages = max_seq_len; a.page = 1;  // clamp_len
   int load[kAdaptiveMaxB], chunks[kAdaptiveMaxB], units[kAdaptiveMaxB];
   bool even = true;
-  float work = 0.f;
+  int work = 0;  // at most the whole plan's, which even_work is set for only where it fits
   int sum = 0, most = 0;
   for (int b = 0; a.adaptive && b < B; ++b) {
     const int kept = n_nodes ? min(max(n_nodes[b], 1), T) : T;
     even = even && seq_is_even(a, seq_lens[b], kept);
     units[b] = len_units(seq_lens[b], a);
-    work += seq_work(a, seq_lens[b], kept);
     load[b] = cut_load(a, units[b]);
     chunks[b] = cut_chunks(a, kept);
+    if (a.even_work > 0) work += units[b] * chunks[b];
     sum += load[b];
     most = max(most, load[b]);
   }
-  even = even || (a.even_work > 0.f && work >= a.even_work);
+  even = even || (a.even_work > 0 && work >= a.even_work);
   if (where) *where = !a.adaptive ? 0 : (even ? 1 : 2);
   if (!n_splits) return SS_OK;
   if (!a.adaptive || even) {

@@ -453,7 +453,7 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
   // trip is made again.  Pieces keep the order above: those of one sequence together, the splits of a head next to each
   // other, the live row chunks of a (sequence, KV head, split) on one XCD.
   if constexpr (CUTS) {
-    if (plan_is_even(a, lane, lane_len, lane_kept)) {
+    if (plan_is_even<16 * NW>(a, lane, lane_len, lane_kept)) {
       if (blockIdx.x == 0 && w == 0 && lane < a.B)
         a.cut_table[lane] = make_int2(active_splits(clamp_len(lane_len, a), a), lane * a.n_splits);
       if (spare) return;
