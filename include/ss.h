@@ -175,9 +175,13 @@ int ss_build_mask(const int32_t* parent, int B, int T, int gamma, uint32_t flags
  * call is enqueued and every call leaves them zero: fill a new workspace with
  * zeros once (ss_msa_workspace_init, or any memset) and it can be used for any
  * number of calls of any shape it is large enough for.  A workspace that was
- * never zeroed gives wrong results for split problems, with no error.  Calls that may run at the same time (different streams, graphs
- * replayed on different streams) need a workspace each; calls that follow each
+ * never zeroed gives wrong results for split problems, with no error.  Calls
+ * that may run at the same time (different streams, graphs replayed on
+ * different streams) need a workspace each; calls that follow each
  * other on one stream can share one.  The library keeps nothing between calls.
+ * A sequence's result may depend on the other sequences' lengths and kept nodes
+ * as far as the order of floating-point sums goes: they share in the choice of
+ * where its cached prefix is split (see ss_msa_plan_splits).
  */
 size_t ss_msa_workspace_bytes(int B, int T, int gamma, int H, int Hkv, int D, int max_seq_len,
                               int dtype);
