@@ -42,6 +42,8 @@ struct MsaArgs {
   int max_n;       // most splits per sequence plan_uneven may make (2: merged in the kernel; else 0 = no limit)
   int min_units;   // shortest split plan_uneven considers, in blocks
   int chunk_rows;  // folded query rows per row chunk (MFMA path)
+  int xcd_slots;   // workgroups an XCD holds at a time
+  float cut_fixed, cut_piece;  // what a round and a piece cost beside their blocks, in blocks (cut_cost)
 };
 
 // A sequence of L cached tokens has active_splits(L) splits; every sequence has at least one (split 0, which
@@ -67,10 +69,12 @@ SS_DEV size_t part_row_of(const MsaArgs& a, int b, int slot0, int s, int h, int 
 // ---- splits cut on the device.  The host plans from the capacity of the block table; what the sequences really
 // hold (and, after pruning, how many row chunks they have) is known on the device only.  Where the
 // host's cut stands (plan_is_even) it is used as it is.  Otherwise the lengths are chosen here, by one wavefront, from 64
-// candidates: the one with the least (rounds of the 32 workgroups an XCD holds) x (blocks per workgroup + 4, its fixed
-// cost), among those whose splits fit the B x S slots of the workspace.  (Fixed costs of 0, 2, 8, 16 instead of 4: 20
-// random batches of fewer than 256 items within 0.2 %, four of 320 items +2.4, 0, -1.4, -3.3 %.)  Lane b holds sequence b,
-// so this is for B <= kAdaptiveMaxB.
+// candidates: the one with the least (rounds of the workgroups an XCD holds) x (blocks per workgroup + a fixed cost) + what
+// the pieces' partial results cost, among those whose splits fit the B x S slots of the workspace.  16 rows per wave, 32
+// workgroups: a fixed cost of 4 (0, 2, 8, 16 instead: 20 random batches of fewer than 256 items within 0.2 %, four of 320
+// items +2.4, 0, -1.4, -3.3 %).  32 rows per wave, 64 workgroups: 8, and a fiftieth per piece (two sequences of 9005 and
+// 3001 tokens in a table of 1.8 times the capacity, 8 KV heads, 384 rows: 47.3 us with 4 and nothing per piece, 44.6; four
+// sequences 67.2 and 61.9).  Lane b holds sequence b, so this is for B <= kAdaptiveMaxB.
 // Measured with the merge kernel, host's cut against this: two sequences of 9005 and 3001 tokens (8 KV heads of 4 query
 // heads, 24 nodes) in a table of 1.8 times the capacity 59.7 and 43.3 us; eight of 2000..8192 tokens with a third to two
 // thirds of 32 nodes kept 179 and 135 us; three of 16000, 9005 and 3001 with 4 KV heads 126 and 77 us (84 with the pieces
@@ -130,10 +134,10 @@ SS_HD float cut_cost(const MsaArgs& a, int c, Load load, Chunks chunks) {
     xcd0 += (((after + 7) >> 3) - ((before + 7) >> 3)) * chunks(i);
     all += (after - before) * chunks(i);
   }
-  // Rounds of the 32 workgroups an XCD holds, on the XCD with the most: XCD 0 has as many pieces as any, and where the
+  // Rounds of the workgroups an XCD holds, on the XCD with the most: XCD 0 has as many pieces as any, and where the
   // sequences' row chunks differ at least the average.
-  const int rounds = (max(xcd0, (all + 7) >> 3) + 31) >> 5;
-  return slots <= a.B * a.n_splits ? (float)rounds * (float)(c + 4) : INFINITY;
+  const int rounds = (max(xcd0, (all + 7) >> 3) + a.xcd_slots - 1) >> (a.xcd_slots == 32 ? 5 : 6);
+  return slots <= a.B * a.n_splits ? (float)rounds * ((float)c + a.cut_fixed) + (float)all * a.cut_piece : INFINITY;
 }
 // Of one sequence: cached blocks of split 0 and of the others, number of splits, row chunks with kept rows.
 struct SeqCut {
@@ -194,5 +198,10 @@ constexpr size_t kArriveRegionBytes = (size_t)8192 * kArriveTiles * sizeof(unsig
 int launch_msa_bf16(const MsaArgs& a, hipStream_t stream);
 // Query rows per workgroup chunk the MFMA path uses for F = g*R folded rows.
 int msa_bf16_rows_per_chunk(int F);
+
+// The same with 32 query rows per wave (D = 128, more than 80 folded rows).
+constexpr int kWideSlots = 512;  // workgroups the chip holds at a time: two per compute unit
+int launch_msa_bf16_wide(const MsaArgs& a, hipStream_t stream);
+int msa_bf16_wide_rows(int F);
 
 }  // namespace ss

@@ -270,6 +270,7 @@ static std::atomic<int> g_merge_in_kernel{1};
 struct MsaPlan {
   int split_keys, split0_keys, n_splits, n_qc, groups, stages;
   int adaptive, new_units, min_units, chunk_rows;
+  bool wide;              // MFMA path: the kernel with 32 query rows per wave
   size_t arrive_bytes;    // arrival counters of this shape (front of the workspace); 0 = not merged in the attention kernel
   size_t part_o_at, part_lse_at, table_at, total_bytes;  // places in the workspace
   size_t scratch_bytes;   // what counts against the limit of ss_msa_attention_static
@@ -297,14 +298,32 @@ static int split0_extra_blocks() {
   return v;
 }
 
-static MsaPlan make_plan(int B, int R, int H, int Hkv, int D, int max_len, int dtype) {
+// Whether the kernel with 32 query rows per wave takes the call.  It halves the LDS reads and barriers per score, but its
+// workgroups take 96 or 128 rows and start up more slowly, so it is the better one where that pads few rows and where there
+// is much to do: from 75 blocks of 32 tokens per workgroup that the chip holds on, by the block table.  Measured, us per
+// layer with 16 and with 32 rows per wave (8 KV heads of 128, 640 rows): 8 x 32768 tokens 818 and 725, 8 x 8192 250 and 219,
+// 4 x 16384 290 and 200, 4 x 8192 (80 blocks) 162 and 115, 8 x 4096 (80) 160 and 133; 384 rows: 8 x 8192 (96) 165 and 146,
+// 2 x 16209 (47; 9005 and 3001 of them used) 46 and 45, 2 x 8000 (640 rows, 4 heads: 20) 41 and 44; 96 rows, one chunk
+// instead of two of 48: 16 x 32 heads x 4096 (128) 275 and 241, a quarter of that 60 and 59.  320 rows (384 with padding)
+// 8 x 8192 128 and 136; 120 rows, a single chunk either way, 260 and 263.  Heads of 64 have half the products per
+// exponential and gain nothing: 400 rows 8 x 8192 128 and 125, 16384 214 and 226.
+static bool wide_fits(int B, int R, int H, int Hkv, int D, int len) {
+  const int F = (H / Hkv) * R;
+  if (D != 128 || F <= 80 || (F > 96 && F <= 128) || H >= (1 << 20)) return false;
+  const int rows = msa_bf16_wide_rows(F), chunks = ceil_div(F, rows);
+  const int rows16 = msa_bf16_rows_per_chunk(F), pad16 = ceil_div(F, rows16) * rows16;
+  return 10L * chunks * rows <= 11L * pad16 && (double)B * Hkv * chunks * ceil_div(len, 32) >= 75.0 * kWideSlots;
+}
+
+static MsaPlan make_plan(int B, int R, int H, int Hkv, int D, int max_len, int dtype, bool allow_wide = true) {
   MsaPlan p;
   const int g = H / Hkv;
+  p.wide = allow_wide && dtype == SS_BF16 && wide_fits(B, R, H, Hkv, D, max_len);
   int base;
   p.groups = 1;
   p.stages = 2;
   if (dtype == SS_BF16) {
-    const int rows = msa_bf16_rows_per_chunk(g * R);
+    const int rows = p.wide ? msa_bf16_wide_rows(g * R) : msa_bf16_rows_per_chunk(g * R);
     p.n_qc = ceil_div(g * R, rows);
     base = B * Hkv * p.n_qc;
   } else {
@@ -317,7 +336,7 @@ static MsaPlan make_plan(int B, int R, int H, int Hkv, int D, int max_len, int d
   int split_keys = g_split_keys_override.load();
   const bool overridden = split_keys > 0;
   int want_wgs = 512;
-  if (dtype == SS_BF16) {
+  if (dtype == SS_BF16 && !p.wide) {
     if (base < 512) {
       p.groups = 2;
       p.stages = 3;
@@ -329,7 +348,8 @@ static MsaPlan make_plan(int B, int R, int H, int Hkv, int D, int max_len, int d
     if (p.n_qc > 1) p.groups = msa_bf16_rows_per_chunk(g * R) == 128 ? 2 : 3;  // 16 or 15 waves per workgroup
   }
   if (split_keys <= 0) {
-    int n = ceil_div(want_wgs, base);
+    // (32 rows per wave: two workgroups fit a compute unit, and one more than that makes a second round)
+    int n = p.wide ? (kWideSlots / base < 1 ? 1 : kWideSlots / base) : ceil_div(want_wgs, base);
     const int n_cap = len / 256 < 1 ? 1 : len / 256;
     if (n > n_cap) n = n_cap;
     if (dtype == SS_BF16 && p.n_qc > 1 && base >= 256) {
@@ -340,6 +360,8 @@ static MsaPlan make_plan(int B, int R, int H, int Hkv, int D, int max_len, int d
       int best_n = 1;
       double best_waste = 0.0;
       for (int cand = 1; cand <= 8 && (cand == 1 || len / cand >= 1024); ++cand) {
+        // (32 rows per wave, two workgroups per compute unit, the same: 1, 2, 3, 4, 5, 8 splits 882, 896, 773, 782, 813,
+        // 793 us)
         const double wgs = (double)base * cand, waste = ceil(wgs / 256.0) * 256.0 / wgs;
         if (cand == 1 || waste < best_waste - 1e-9) {
           best_n = cand;
@@ -377,13 +399,13 @@ static MsaPlan make_plan(int B, int R, int H, int Hkv, int D, int max_len, int d
   // and 25 with 16; batches of fewer than 256 items 0.5 % between the two and 5 % slower with 32; four batches of 320
   // items the same with 8 and 16 and 5 % faster with 32 (two of them; the others the same).
   p.min_units = base >= 256 ? 16 : 8;
-  p.chunk_rows = dtype == SS_BF16 ? msa_bf16_rows_per_chunk(g * R) : 32;
+  p.chunk_rows = dtype != SS_BF16 ? 32 : p.wide ? msa_bf16_wide_rows(g * R) : msa_bf16_rows_per_chunk(g * R);
   // Workspace: arrival counters (their region is there for every split shape) | partial outputs | log-sum-exps | cuts
   p.arrive_bytes = 0;
   p.part_o_at = p.part_lse_at = p.table_at = 0;
   p.total_bytes = p.scratch_bytes = 256;  // to align the start
   if (p.n_splits > 1) {
-    const size_t counters = dtype == SS_BF16 && p.n_splits == 2
+    const size_t counters = dtype == SS_BF16 && !p.wide && p.n_splits == 2
                                 ? align_up((size_t)B * Hkv * p.n_qc * kArriveTiles * sizeof(unsigned int), 256) : 0;
     if (counters <= kArriveRegionBytes) p.arrive_bytes = counters;
     const size_t rows = (size_t)B * H * p.n_splits * R;
@@ -400,11 +422,12 @@ static MsaPlan make_plan(int B, int R, int H, int Hkv, int D, int max_len, int d
 static void set_plan(MsaArgs& a, const MsaPlan& plan, int B, int T, int gamma, int H, int Hkv, int D, int max_len, int dtype) {
   a.B = B; a.T = T; a.gamma = gamma; a.R = T * (1 + gamma); a.H = H; a.Hkv = Hkv; a.g = H / Hkv; a.D = D;
   a.split_keys = plan.split_keys; a.split0_keys = plan.split0_keys; a.n_splits = plan.n_splits; a.n_qc = plan.n_qc; a.groups = plan.groups; a.stages = plan.stages;
-  a.max_n = plan.n_splits == 2 && dtype == SS_BF16 ? 2 : 0;  // also where the merge kernel does it: the same cut either way
+  a.max_n = plan.n_splits == 2 && dtype == SS_BF16 && !plan.wide ? 2 : 0;  // also where the merge kernel does it: the same cut either way
   a.even_len = max_len - max_len / 8;
   const double whole = (double)B * ceil_div(max_len, 32) * plan.n_qc;
   a.even_work = (long)B * Hkv * plan.n_qc >= 256 && whole < INT_MAX ? (int)ceil(0.875 * whole) : 0;
   a.adaptive = plan.adaptive; a.new_units = plan.new_units; a.min_units = plan.min_units; a.chunk_rows = plan.chunk_rows;
+  a.xcd_slots = plan.wide ? kWideSlots / 8 : 32; a.cut_fixed = plan.wide ? 8.f : 4.f; a.cut_piece = plan.wide ? 0.02f : 0.f;
 }
 
 // Whether a full call folds its two splits inside the attention kernel (see ss_msa_attention).
@@ -502,7 +525,10 @@ static int msa_run(const char* fn, const void* q, const void* k_new, const void*
 
   const int R = T * (1 + gamma);
   const int max_len = max_pages_per_seq * page_size;
-  const MsaPlan plan = make_plan(B, R, H, Hkv, D, max_len, dtype);
+  MsaPlan plan = make_plan(B, R, H, Hkv, D, max_len, dtype);
+  // A workspace that only the other kernel's splits fit stays good.
+  if (plan.wide && plan.n_splits > 1 && (workspace == nullptr || workspace_bytes < (library_scratch ? plan.scratch_bytes : plan.total_bytes)))
+    plan = make_plan(B, R, H, Hkv, D, max_len, dtype, false);
   if (library_scratch) {
     SS_REQUIRE(plan.scratch_bytes <= workspace_bytes, SS_ERR_UNSUPPORTED,
                "%s: this shape needs %zu bytes of scratch memory, the library's array holds %zu; use "
@@ -549,7 +575,7 @@ static int msa_run(const char* fn, const void* q, const void* k_new, const void*
     hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, a);
     if (int rc = check_launch(fn)) return rc;
   } else {
-    if (int rc = launch_msa_bf16(a, st)) return rc;
+    if (int rc = plan.wide ? launch_msa_bf16_wide(a, st) : launch_msa_bf16(a, st)) return rc;
   }
   if (plan.n_splits > 1 && !(flags & SS_MSA_PARTIALS_ONLY) && a.arrive == nullptr) {
     const long threads = (long)B * R * H * (D / 4);
