@@ -654,10 +654,16 @@ __global__ __launch_bounds__(64) void lm_head_reduce_kernel(LmArgs a) {
 }
 
 // ------------------------------------------------------------------ fused tail: merge + verify + draft
-// One workgroup of 16 wavefronts per sequence.  Only the rows the two tree steps read are merged: the
-// arg-max of the T main rows (a wave per row), then, once the accepted path is known, the top-K of the
-// gamma stream rows of its last node (a wave per stream).  Rows of a sequence: main row of node i at i,
-// stream j of node i at T + i*gamma + (j-1).
+// One workgroup of 16 wavefronts per sequence, all latency.  Only the rows the two tree steps read are merged: the arg-max of
+// the T main rows (two rows per wave at a time, of every tile only its best candidate), then, once the accepted path is
+// known, the top-K of the gamma stream rows of its last node: up to four waves per stream, a lane per tile holding the
+// tile's sorted candidates, whose best heads are taken K times; the waves' lists are merged by counting.  Maxima go by
+// register moves.  Loads are never under a condition (their places are clamped and what is too much is set aside after the
+// wait): of a loaded value that is only wanted under a condition the compiler makes a load, a wait and a use, eight round
+// trips in the place of one.  The arguments are asked for all at once for the same reason.
+// 250 tiles of 4 candidates, 4 or 3 streams, kernel trace: one tree of 16 nodes 10.9 -> 6.8 us, two of 24 12.9 -> 7.7, two
+// of one node 8.7 -> 6.0.  Candidates by rank instead of by tile ([row][rank][tile]): no faster (8.2 against 7.8 at the time).
+// Rows of a sequence: main row of node i at i, stream j of node i at T + i*gamma + (j-1).
 struct TailArgs {
   const uint64_t* cand_key;  // [B*R][n_parts][K]
   int n_parts, K;
@@ -669,49 +675,104 @@ struct TailArgs {
 };
 
 __global__ __launch_bounds__(1024) void lm_tail_kernel(TailArgs t) {
-  __shared__ VerifyLds vs;
   __shared__ int am[64];
+  __shared__ uint64_t anc[64];
+  __shared__ uint64_t lists[SS_MAX_GAMMA][4 * SS_MAX_K];  // [stream][wave][rank]
   __shared__ int topk[SS_MAX_GAMMA * SS_MAX_K];
-  __shared__ int dpar[64];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, b = blockIdx.x;
-  const int R = t.T * (1 + t.gamma);
-  const int n = t.n_parts * t.K;
-  int p, my_tok;
-  verify_load(tid, b, t.tok, t.parent, t.T, p, my_tok);  // in flight during the arg-max pass
-  int tp, trank;
-  draft_load(tid, t.tmpl_parent, t.tmpl_rank, t.targ, t.T2, tp, trank);
-  for (int i = w; i < t.T; i += 16) {
-    const uint64_t* ck = t.cand_key + ((size_t)b * R + i) * n;
-    uint64_t best = 0;
-    for (int e0 = lane; e0 < n; e0 += 512) {  // eight independent loads, then the compares
-      uint64_t c[8];
+  asm volatile("" ::"s"(t.cand_key), "s"(t.tok), "s"(t.parent), "s"(t.n_parts), "s"(t.K), "s"(t.T), "s"(t.gamma), "s"(t.T2),
+               "s"(t.max_depth), "s"(t.tmpl_parent), "s"(t.main_argmax));
+  const int tid = threadIdx.x, lane = tid & 63, b = blockIdx.x;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int R = t.T * (1 + t.gamma), T = t.T, K = t.K, n_parts = t.n_parts;
+  const uint64_t* seq = t.cand_key + (size_t)b * R * n_parts * K;  // this sequence's candidates
+  const size_t row = (size_t)n_parts * K;
+  int p = t.parent[(size_t)b * T + min(lane, T - 1)];
+  const int my_tok = t.tok[(size_t)b * T + min(lane, T - 1)];
+  int tp = 0, trank = 0, level = 0;
+  if (w == 0) draft_load(min(lane, t.T2 - 1), t.tmpl_parent, t.tmpl_rank, t.targ, tp, trank);
+  for (int i0 = w; i0 < max(T, 16); i0 += 32) {
+    const uint64_t *row0 = seq + min(i0, T - 1) * row, *row1 = seq + min(i0 + 16, T - 1) * row;
+    uint64_t best[2] = {0, 0};
+    for (int e0 = 0; e0 < n_parts; e0 += 256) {
+      uint64_t c[2][4];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) c[j] = e0 + 64 * j < n ? ck[e0 + 64 * j] : 0;
+      for (int j = 0; j < 4; ++j) {
+        const int at = min(e0 + 64 * j + lane, n_parts - 1) * K;  // the last one again past the end
+        c[0][j] = row0[at];
+        c[1][j] = row1[at];
+      }
+      if (i0 == w && e0 == 0) {  // while the first candidates are on their way
+        p = lane < T ? clamp_parent(p, lane) : -1;
+        if (w == 0) {
+          anc[lane] = ancestors(lane, p, T, t.max_depth + 1);
+          tp = clamp_parent(tp, lane);
+          level = template_level(lane, tp, t.T2, t.gamma);
+        }
+      }
 #pragma unroll
-      for (int j = 0; j < 8; ++j) best = c[j] > best ? c[j] : best;
+      for (int j = 0; j < 4; ++j) {
+        best[0] = max_u64(best[0], c[0][j]);
+        best[1] = max_u64(best[1], c[1][j]);
+      }
     }
-    for (int off = 32; off > 0; off >>= 1) {
-      const uint32_t lo = __shfl_xor((uint32_t)best, off, 64), hi = __shfl_xor((uint32_t)(best >> 32), off, 64);
-      const uint64_t o = ((uint64_t)hi << 32) | lo;
-      best = o > best ? o : best;
-    }
-    if (lane == 0) {
-      am[i] = key_id(best);
-      if (t.main_argmax) t.main_argmax[(size_t)b * t.T + i] = key_id(best);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int id = key_id(wave_max_u64(best[q])), i = i0 + 16 * q;
+      if (lane == 0 && i < T) {
+        am[i] = id;
+        if (t.main_argmax) t.main_argmax[(size_t)b * T + i] = id;
+      }
     }
   }
   __syncthreads();
   int node, bonus_tok;
-  verify_sequence(tid, b, p, my_tok, am, 1, t.T, t.max_depth, t.n_accept, t.last, t.bonus, t.path, t.out_tokens, vs,
-                  node, bonus_tok);
-  if (w < t.gamma) {
-    const uint64_t* ck = t.cand_key + ((size_t)b * R + t.T + (size_t)node * t.gamma + w) * n;
-    row_topk(ck, n, t.K, lane, [&](int k, uint64_t best) {
-      if (lane == 0) topk[w * t.K + k] = key_id(best);
-    });
+  verify_sequence(lane, b, my_tok, anc[lane], lane < T ? am[lane] : 0, am[max(p, 0)], T, t.max_depth, w == 0, t.n_accept, t.last,
+                  t.bonus, t.path, t.out_tokens, node, bonus_tok);
+  const int per_stream = t.gamma > 0 ? min(4, 16 / t.gamma) : 0;  // waves
+  if (w < t.gamma * per_stream) {
+    const int j = w / per_stream, part = w % per_stream;
+    const uint64_t* ck = seq + (T + (size_t)node * t.gamma + j) * row;
+    TopList<SS_MAX_K> top;
+    top.clear();
+    for (int s0 = 0; s0 < n_parts; s0 += 64 * per_stream) {
+      const int e = s0 + part * 64 + lane;
+      uint64_t c[SS_MAX_K];
+#pragma unroll
+      for (int k = 0; k < SS_MAX_K; ++k) c[k] = ck[(size_t)min(e, n_parts - 1) * K + min(k, K - 1)];
+#pragma unroll
+      for (int k = 0; k < SS_MAX_K; ++k) c[k] = e < n_parts && k < K ? c[k] : 0;
+      if (s0 == 0) {
+#pragma unroll
+        for (int k = 0; k < SS_MAX_K; ++k) top.k[k] = c[k];  // sorted already
+      } else {
+        for (int k = 0; k < K; ++k) {
+          top.insert(c[0]);
+#pragma unroll
+          for (int q = 0; q + 1 < SS_MAX_K; ++q) c[q] = c[q + 1];
+        }
+      }
+    }
+    for (int k = 0; k < K; ++k) {
+      const uint64_t best = wave_max_u64(top.k[0]);
+      if (lane == 0) lists[j][part * K + k] = best;
+      if (best == top.k[0]) {  // keys are unique (token ids are): this lane won, pop its head
+#pragma unroll
+        for (int q = 0; q + 1 < SS_MAX_K; ++q) top.k[q] = top.k[q + 1];
+        top.k[SS_MAX_K - 1] = 0;
+      }
+    }
   }
   __syncthreads();
-  draft_sequence(tid, b, tp, trank, topk, t.K, bonus_tok, t.gamma, t.T2, t.next_tok, t.next_parent, dpar);
+  if (w < t.gamma) {  // a lane per candidate; its place is the number of better ones
+    const int n = per_stream * K;
+    const uint64_t mine = lane < n ? lists[w][lane] : 0;
+    int place = 0;
+#pragma unroll 8
+    for (int c = 0; c < n; ++c) place += lists[w][c] > mine ? 1 : 0;
+    if (mine != 0 && place < K) topk[w * K + place] = key_id(mine);
+  }
+  __syncthreads();
+  if (w == 0) draft_sequence(lane, b, tp, trank, level, topk, K, bonus_tok, t.gamma, t.T2, t.next_tok, t.next_parent);
 }
 
 // Tuning aids: a flavour (32-row tiles per workgroup, 8-wave kernel or not) that replaces the chosen one for

@@ -1,7 +1,6 @@
 // Greedy tree verification and top-k tree drafting of ONE sequence (Sec. 3.2.2, Appendix A.1) as device
-// functions: the bodies of the two stand-alone kernels and of the fused tail of the LM head.  Thread i of
-// the workgroup owns tree node i (T <= 64); threads beyond the first wavefront only take part in the
-// barriers, so every thread of the workgroup must make the call.
+// functions: the bodies of the two stand-alone kernels and of the fused tail of the LM head.  Lane i of a
+// wavefront owns tree node i (T <= 64).
 #pragma once
 #include "ss_common.h"
 
@@ -13,117 +12,106 @@ struct TemplateArg {
   int8_t rank[SS_MAX_T];
 };
 
-struct VerifyLds {
-  int par[64];
-  int edge_ok[64];
-  int tk[64];
-  int pth[64];
-  int res[3];
-};
+// Maxima over a wavefront (the result is uniform) by register moves: rotations within rows of 16 lanes, then the row swaps.
+// A lane shuffle is a trip through LDS, and a maximum of 64-bit keys is twelve of them one after the other.
+template <int ROR>
+SS_DEV uint32_t row_max_step(uint32_t v) {
+  return max(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x120 + ROR, 0xf, 0xf, false));
+}
+SS_DEV uint32_t wave_max_u32(uint32_t v) {
+  v = row_max_step<1>(row_max_step<2>(row_max_step<4>(row_max_step<8>(v))));
+  const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  v = max(a[0], a[1]);
+  const auto c = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return __builtin_amdgcn_readfirstlane(max(c[0], c[1]));
+}
+// The high words first; the low words only of the lanes that tie.
+SS_DEV uint64_t wave_max_u64(uint64_t v) {
+  const uint32_t hi = (uint32_t)(v >> 32), top = wave_max_u32(hi);
+  const uint64_t tied = __ballot(hi == top);
+  const uint32_t lo = (tied & (tied - 1)) == 0 ? (uint32_t)__builtin_amdgcn_readlane((int)v, (int)__builtin_ctzll(tied))
+                                               : wave_max_u32(hi == top ? (uint32_t)v : 0u);
+  return ((uint64_t)top << 32) | lo;
+}
+SS_DEV uint64_t max_u64(uint64_t a, uint64_t b) { return a > b ? a : b; }
 
-// Acceptance is a property of a node's whole root path: every edge on it must match.  Lane i walks its
-// path through LDS copies of parent / edge-match flags; the deepest accepted node is then picked with a
-// wave-wide max of (depth, 63 - index) so that ties go to the lowest index.  `a[n * node_stride]` is the
-// main stream's arg-max token at node n (global memory or LDS).  On return every thread holds the last
-// accepted node and the bonus token.
-// `p`, `my_tok`: node i's parent and token from verify_load (a caller with other memory work to do
-// first issues these loads early).
-SS_DEV void verify_load(int i, int b, const int32_t* __restrict__ tok, const int32_t* __restrict__ parent, int T,
-                        int& p, int& my_tok) {
-  p = -1;
-  my_tok = -1;
-  if (i < T) {
-    p = clamp_parent(parent[(size_t)b * T + i], i);
-    my_tok = tok[(size_t)b * T + i];
+// Ancestors-or-self of node i (bit set) in a tree of T nodes, lane i of a wavefront holding node i's clamped parent p: the
+// set doubles its reach with every step.  Complete for nodes of fewer than `reach` ancestors; the others' sets have more
+// than `reach` members too.
+SS_DEV uint64_t ancestors(int i, int p, int T, int reach) {
+  uint64_t bits = i < T ? 1ull << i : 1ull;
+  int up = i < T && i > 0 ? p : 0;
+  for (int r = 1; r <= reach; r <<= 1) {
+    const uint32_t lo = __shfl((uint32_t)bits, up, 64), hi = __shfl((uint32_t)(bits >> 32), up, 64);
+    bits |= ((uint64_t)hi << 32) | lo;
+    up = __shfl(up, up, 64);
   }
+  return bits;
 }
 
-SS_DEV void verify_sequence(int i, int b, int p, int my_tok, const int32_t* a, long node_stride, int T, int max_depth,
-                            int32_t* __restrict__ n_accept, int32_t* __restrict__ last, int32_t* __restrict__ bonus,
-                            int32_t* __restrict__ path, int32_t* __restrict__ out_tokens, VerifyLds& s,
-                            int& last_node, int& bonus_tok) {
-  if (i < T) {
-    s.par[i] = p;
-    s.tk[i] = my_tok;
-    s.edge_ok[i] = (i == 0) ? 1 : (my_tok == a[(size_t)p * node_stride]);
-  }
-  if (i <= max_depth) s.pth[i] = -1;
-  __syncthreads();
-  int depth = 0, ok = (i < T);
-  if (i < T) {
-    int n = i;
-    for (int step = 0; step < 64 && n > 0; ++step) {
-      ok &= s.edge_ok[n];
-      n = s.par[n];
-      ++depth;
-    }
-    ok &= (depth <= max_depth);
-  }
+// Acceptance is a property of a node's whole root path: every edge on it must match.  One wavefront, lane i = node i with
+// its parent p, token my_tok, ancestors `anc` (reach max_depth + 1), the main stream's arg-max a_own at the node and
+// a_parent at its parent: a node is accepted iff its ancestors-or-self hold no node whose edge fails.  The deepest accepted
+// node wins, ties go to the lowest index.  A parent has a lower index than its child, so node i's depth is its rank among
+// its ancestors and the lanes on the winner's path write their own slots.  Every wavefront of a workgroup may make the
+// call; those that `write` store the results.
+SS_DEV void verify_sequence(int i, int b, int my_tok, uint64_t anc, int a_own, int a_parent, int T, int max_depth,
+                            bool write, int32_t* __restrict__ n_accept, int32_t* __restrict__ last, int32_t* __restrict__ bonus,
+                            int32_t* __restrict__ path, int32_t* __restrict__ out_tokens, int& last_node, int& bonus_tok) {
+  const bool node = i < T;
+  const uint64_t fails = __ballot(node && i > 0 && my_tok != a_parent);
+  const int depth = __popcll(anc) - 1;
   // key: depth * 64 + (63 - i) for accepted nodes; the root (always accepted) gives key >= 63
-  int key = ok ? depth * 64 + (63 - i) : -1;
-  for (int off = 32; off > 0; off >>= 1) key = max(key, __shfl_xor(key, off, 64));
-  if (i == 0) {  // the first wavefront holds all nodes: its result is the sequence's
-    const int best = 63 - (key & 63);
-    const int best_depth = key >> 6;
-    const int bon = a[(size_t)best * node_stride];
+  const uint32_t mine = node && depth <= max_depth && (anc & fails) == 0 ? (uint32_t)(depth * 64 + (63 - i)) : 0u;
+  const uint32_t key = wave_max_u32(mine);
+  const int best = 63 - (int)(key & 63), best_depth = (int)(key >> 6);
+  last_node = best;
+  bonus_tok = __builtin_amdgcn_readlane(a_own, best);
+  if (!write) return;
+  if (i == 0) {
     n_accept[b] = best_depth;
     last[b] = best;
-    bonus[b] = bon;
-    s.res[0] = best;
-    s.res[1] = bon;
-    s.res[2] = best_depth;
-    int n = best;
-    for (int k = best_depth; k >= 0 && n >= 0; --k) {
-      s.pth[k] = n;
-      n = s.par[n];
-    }
+    bonus[b] = bonus_tok;
   }
-  __syncthreads();
-  last_node = s.res[0];
-  bonus_tok = s.res[1];
-  const int best_depth = s.res[2];
-  // path / emitted tokens: thread k < max_depth+1 writes slot k
-  if (i <= max_depth) {
-    const int node = s.pth[i];
-    path[(size_t)b * (max_depth + 1) + i] = node;
-    int t = -1;
-    if (i < best_depth) t = s.tk[s.pth[i + 1]];
-    else if (i == best_depth) t = bonus_tok;
-    out_tokens[(size_t)b * (max_depth + 1) + i] = t;
+  int32_t* pb = path + (size_t)b * (max_depth + 1);
+  int32_t* ob = out_tokens + (size_t)b * (max_depth + 1);
+  const uint64_t on_path = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(anc >> 32), best) << 32) |
+                           (uint32_t)__builtin_amdgcn_readlane((int)anc, best);
+  if (node && ((on_path >> i) & 1)) {
+    pb[depth] = i;
+    if (depth > 0) ob[depth - 1] = my_tok;
+  }
+  if (i <= max_depth && i >= best_depth) {
+    ob[i] = i == best_depth ? bonus_tok : -1;
+    if (i > best_depth) pb[i] = -1;
   }
 }
 
 // The next tree: node i of the template takes the token of rank `rank[i]` of stream `level(i)` of the
 // last accepted node; the root takes the bonus token.  `topk_of_node[(j-1) * K + r]` is the token of
-// rank r of stream j of that node (global memory or LDS).
-// `p`, `rank`: template entry i from draft_load (may be issued early).
+// rank r of stream j of that node (global memory or LDS).  One wavefront, lane i = template node i.
+// `p` (clamped), `rank`: template entry i; `level` from template_level.
 SS_DEV void draft_load(int i, const int32_t* __restrict__ tmpl_parent, const int32_t* __restrict__ tmpl_rank,
-                       const TemplateArg& targ, int T2, int& p, int& rank) {
-  p = 0;
-  rank = 0;
-  if (i < T2) {
-    p = tmpl_parent ? tmpl_parent[i] : (int)targ.parent[i];
-    rank = tmpl_rank ? tmpl_rank[i] : (int)targ.rank[i];
+                       const TemplateArg& targ, int& p, int& rank) {
+  if (tmpl_parent) {
+    p = tmpl_parent[i];
+    rank = tmpl_rank[i];
+  } else {
+    p = targ.parent[i];
+    rank = targ.rank[i];
   }
 }
+SS_DEV int template_level(int i, int p, int T2, int gamma) { return __popcll(ancestors(i, p, T2, gamma + 1)) - 1; }
 
-SS_DEV void draft_sequence(int i, int b, int p, int rank, const int32_t* topk_of_node, int K, int bonus_tok, int gamma,
-                           int T2, int32_t* __restrict__ next_tok, int32_t* __restrict__ next_parent,
-                           int* par /* LDS, 64 ints */) {
-  if (i < T2) par[i] = clamp_parent(p, i);
-  __syncthreads();
+SS_DEV void draft_sequence(int i, int b, int p, int rank, int level, const int32_t* topk_of_node, int K, int bonus_tok,
+                           int gamma, int T2, int32_t* __restrict__ next_tok, int32_t* __restrict__ next_parent) {
   if (i >= T2) return;
-  int level = 0;
-  for (int n = i, step = 0; step < 64 && n > 0; ++step) {
-    n = par[n];
-    ++level;
-  }
   int t;
   if (i == 0) t = bonus_tok;
   else if (level >= 1 && level <= gamma && rank >= 0 && rank < K) t = topk_of_node[(size_t)(level - 1) * K + rank];
   else t = -1;
   next_tok[(size_t)b * T2 + i] = t;
-  if (next_parent && b == 0) next_parent[i] = par[i];
+  if (next_parent && b == 0) next_parent[i] = p;
 }
 
 // Host: the template argument of a draft call from per-level branching (checks it against K and T2).

@@ -13,12 +13,14 @@ __global__ __launch_bounds__(64) void tree_verify_kernel(const int32_t* __restri
                                                          int32_t* __restrict__ n_accept, int32_t* __restrict__ last,
                                                          int32_t* __restrict__ bonus, int32_t* __restrict__ path,
                                                          int32_t* __restrict__ out_tokens) {
-  __shared__ VerifyLds s;
-  const int b = blockIdx.x;
-  int p, my_tok, last_node, bonus_tok;
-  verify_load(threadIdx.x, b, tok, parent, T, p, my_tok);
-  verify_sequence(threadIdx.x, b, p, my_tok, main_argmax + (size_t)b * batch_stride, node_stride, T, max_depth,
-                  n_accept, last, bonus, path, out_tokens, s, last_node, bonus_tok);
+  const int b = blockIdx.x, i = threadIdx.x;
+  const int at = min(i, T - 1);
+  const int p_raw = parent[(size_t)b * T + at], my_tok = tok[(size_t)b * T + at];
+  const int a_own = main_argmax[(size_t)b * batch_stride + (size_t)at * node_stride];
+  const int p = i < T ? clamp_parent(p_raw, i) : -1;
+  int last_node, bonus_tok;
+  verify_sequence(i, b, my_tok, ancestors(i, p, T, max_depth + 1), a_own, __shfl(a_own, max(p, 0), 64), T, max_depth, true,
+                  n_accept, last, bonus, path, out_tokens, last_node, bonus_tok);
 }
 
 __global__ __launch_bounds__(64) void tree_draft_kernel(const int32_t* __restrict__ stream_topk, long batch_stride,
@@ -28,13 +30,13 @@ __global__ __launch_bounds__(64) void tree_draft_kernel(const int32_t* __restric
                                                         const int32_t* __restrict__ tmpl_rank, TemplateArg targ,
                                                         int T, int gamma, int T2, int32_t* __restrict__ next_tok,
                                                         int32_t* __restrict__ next_parent) {
-  __shared__ int par[64];
   const int b = blockIdx.x;
   const int node = min(max(last[b], 0), T - 1);
   int p, rank;
-  draft_load(threadIdx.x, tmpl_parent, tmpl_rank, targ, T2, p, rank);
-  draft_sequence(threadIdx.x, b, p, rank, stream_topk + (size_t)b * batch_stride + (size_t)node * gamma * K, K, bonus[b],
-                 gamma, T2, next_tok, next_parent, par);
+  draft_load(min((int)threadIdx.x, T2 - 1), tmpl_parent, tmpl_rank, targ, p, rank);
+  p = clamp_parent(p, threadIdx.x);
+  draft_sequence(threadIdx.x, b, p, rank, template_level(threadIdx.x, p, T2, gamma), stream_topk + (size_t)b * batch_stride + (size_t)node * gamma * K, K, bonus[b],
+                 gamma, T2, next_tok, next_parent);
 }
 
 int draft_template_from_branching(const char* fn, const int32_t* branching, int gamma, int K, int T2,
