@@ -92,29 +92,44 @@ SS_DEV bool row_sees(const RowVis& v, int c, int T) {
   const bool as_stream = (c >= v.lo) & (c < v.hi);
   return (c < T) ? as_main : as_stream;
 }
-SS_DEV RowVis make_row_vis(int r, int T, int gamma, const uint64_t* anc_of_node, bool exclude_self) {
-  int node, strm;
-  row_split(r, T, gamma, node, strm);
+// anc: ancestors-or-self of the row's node.
+SS_DEV RowVis make_row_vis(int node, int strm, uint64_t anc, int T, int gamma, bool exclude_self) {
   RowVis v;
-  v.anc = anc_of_node[node];
+  v.anc = anc;
   v.lo = T + node * gamma;
   v.hi = v.lo + (strm == 0 ? 0 : (exclude_self ? strm - 1 : strm));
   return v;
 }
 
-// Ancestor-or-self bit sets of all T <= 64 nodes into anc_out[T] (LDS), computed
-// by the first T threads of the block, each walking up from its node.  par_lds[T]
-// must hold the clamped parents.  Callers synchronise before and after.
-SS_DEV void compute_anc(const int* par_lds, int T, uint64_t* anc_out, int tid) {
-  if (tid < T) {
-    uint64_t bits = 0;
-    int n = tid;
-    for (int step = 0; step < 64 && n >= 0; ++step) {
-      bits |= 1ull << n;
-      n = par_lds[n];
-    }
-    anc_out[tid] = bits;
+// Ancestors-or-self of node i (bit set) in a tree of T nodes, lane i of a wavefront holding node i's clamped parent p; all
+// lanes take part.  The set doubles its reach with every step: complete for nodes of at most `reach` ancestors, of the others
+// it holds more than `reach`.
+SS_DEV uint64_t ancestors(int i, int p, int T, int reach) {
+  uint64_t bits = i < T ? 1ull << i : 1ull;
+  int up = i < T && i > 0 ? p : 0;
+  for (int r = 1; r <= reach; r <<= 1) {
+    const uint32_t lo = __shfl((uint32_t)bits, up, 64), hi = __shfl((uint32_t)(bits >> 32), up, 64);
+    bits |= ((uint64_t)hi << 32) | lo;
+    up = __shfl(up, up, 64);
   }
+  return bits;
+}
+// The same for one node per lane, any of them: walks up from it, a lane shuffle per level.
+SS_DEV uint64_t ancestors_of(int node, int p) {
+  uint64_t bits = 0;
+  int n = node;
+  for (int step = 0; step < 64 && __any(n >= 0); ++step) {
+    const int up = __shfl(p, max(n, 0), 64);
+    bits |= n >= 0 ? 1ull << n : 0ull;
+    n = n >= 0 ? up : -1;
+  }
+  return bits;
+}
+// x / d for 0 <= x < 2^23, 0 < d: the rounded quotient is off by one at most.  Fewer than half the instructions of an
+// integer division, in kernels that last little longer than their start.
+SS_DEV int fast_div(int x, int d) {
+  const int q = (int)((float)x * __builtin_amdgcn_rcpf((float)d)), r = x - q * d;
+  return q + (r >= d ? 1 : 0) - (r < 0 ? 1 : 0);
 }
 
 }  // namespace ss

@@ -4,19 +4,19 @@
 
 namespace ss {
 
-// One workgroup per sequence.  parent -> LDS, ancestor sets by T threads, then
+// One workgroup per sequence.  Ancestor sets by the first wavefront, then
 // all threads fill the R x R byte matrix with coalesced stores.
 __global__ __launch_bounds__(256) void build_mask_kernel(const int32_t* __restrict__ parent, int T, int gamma,
                                                          uint32_t flags, uint8_t* __restrict__ mask,
                                                          uint64_t* __restrict__ anc_out,
                                                          int32_t* __restrict__ depth_out) {
-  __shared__ int par[SS_MAX_T];
   __shared__ uint64_t anc[SS_MAX_T];
   const int b = blockIdx.x, tid = threadIdx.x;
   const int R = T * (1 + gamma);
-  if (tid < T) par[tid] = clamp_parent(parent[(size_t)b * T + tid], tid);
-  __syncthreads();
-  compute_anc(par, T, anc, tid);
+  if (tid < 64) {
+    const int p = parent[(size_t)b * T + min(tid, T - 1)];
+    anc[tid] = ancestors(tid, clamp_parent(p, tid), T, T - 1);
+  }
   __syncthreads();
   if (tid < T) {
     if (anc_out) anc_out[(size_t)b * T + tid] = anc[tid];
@@ -27,7 +27,9 @@ __global__ __launch_bounds__(256) void build_mask_kernel(const int32_t* __restri
   uint8_t* m = mask + (size_t)b * R * R;
   for (int e = tid; e < R * R; e += blockDim.x) {
     const int r = e / R, c = e - r * R;
-    const RowVis v = make_row_vis(r, T, gamma, anc, excl);
+    int node, strm;
+    row_split(r, T, gamma, node, strm);
+    const RowVis v = make_row_vis(node, strm, anc[node], T, gamma, excl);
     m[e] = row_sees(v, c, T) ? 1 : 0;
   }
 }

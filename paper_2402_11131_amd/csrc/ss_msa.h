@@ -32,6 +32,7 @@ struct MsaArgs {
   float scale_log2;  // softmax scale times log2(e)
   uint32_t flags;
   int n_groups, n_stages;  // what the launch has of `groups` and `stages`
+  int n_extra;             // stages per wave group for more blocks of the step's own rows (MFMA path)
   // last, so that kernels that do not cut read no more of the arguments than they need
   int2* cut_table;  // [B] adaptive calls: splits and first slot of every sequence, which workgroup 0 of the attention
                     // kernel leaves in the workspace for the merge kernel; else NULL

@@ -32,8 +32,6 @@ __global__ __launch_bounds__(256) void msa_f32_kernel(MsaArgs a) {
   __shared__ __attribute__((aligned(16))) float Ks[KT][D + 4];
   __shared__ __attribute__((aligned(16))) float Vs[D][KT + 4];
   __shared__ __attribute__((aligned(16))) float Ps[4][RW][KT];
-  __shared__ int par[SS_MAX_T];
-  __shared__ uint64_t anc[SS_MAX_T];
 
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
   const int chunk = blockIdx.x, s = blockIdx.y;
@@ -56,20 +54,19 @@ __global__ __launch_bounds__(256) void msa_f32_kernel(MsaArgs a) {
   const float* k_cache = (const float*)a.k_cache;
   const float* v_cache = (const float*)a.v_cache;
 
-  if (tid < T) par[tid] = clamp_parent(a.parent[(size_t)b * T + tid], tid);
+  const int par = a.parent[(size_t)b * T + min(lane, T - 1)];
   for (int e = tid; e < RC * D; e += 256) {
     const int r = e / D, d = e % D;
     Qs[r][d] = (r0 + r < R) ? q[(((size_t)b * R + r0 + r) * a.H + h) * D + d] : 0.f;
   }
-  __syncthreads();
-  compute_anc(par, T, anc, tid);
-  __syncthreads();
 
   RowVis vis[RW];
   float m[RW], l[RW], o[RW][DL];
 #pragma unroll
   for (int i = 0; i < RW; ++i) {
-    vis[i] = make_row_vis(min(r0 + w * RW + i, R - 1), T, a.gamma, anc, (a.flags & SS_STREAM_EXCLUDE_SELF) != 0);
+    int node, strm;
+    row_split(min(r0 + w * RW + i, R - 1), T, a.gamma, node, strm);
+    vis[i] = make_row_vis(node, strm, ancestors_of(node, lane < T ? clamp_parent(par, lane) : -1), T, a.gamma, (a.flags & SS_STREAM_EXCLUDE_SELF) != 0);
     m[i] = -1e30f;
     l[i] = 0.f;
 #pragma unroll

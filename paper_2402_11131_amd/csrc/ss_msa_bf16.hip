@@ -107,14 +107,14 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
   constexpr int VHALF = D * 32;                // bytes of one 16-key half of the V tile: D feature rows of 32 bytes
 
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  // smem: [n_groups][n_stages][STAGE_BYTES] ring stages, overlaid by the buffer of the final merge of the groups
-  // ([n_groups - 1][NW][DT] KB); behind the larger of the two: par (first used for `cut`) | anc | ml
+  // smem: [n_groups][n_stages][STAGE_BYTES] ring stages, then [n_groups][n_extra][STAGE_BYTES] for more of the step's own
+  // rows, overlaid by the buffer of the final merge of the groups ([n_groups - 1][NW][DT] KB); behind the larger of the
+  // two: cut | ml
   unsigned char* stages = smem;
-  const int ring_bytes = n_groups * n_stages * STAGE_BYTES, merge_bytes = (n_groups - 1) * NW * DT * 1024;
-  int* par = reinterpret_cast<int*>(smem + max(ring_bytes, merge_bytes));
-  uint64_t* anc = reinterpret_cast<uint64_t*>(par + SS_MAX_T);
-  float* ml = reinterpret_cast<float*>(anc + SS_MAX_T);  // [n_groups][NW][2][16]: max, sum per query
-  int* cut = par;                                        // [8]: this workgroup's piece where the device cuts the sequences
+  const int n_extra = args.n_extra;
+  const int ring_bytes = n_groups * (n_stages + n_extra) * STAGE_BYTES, merge_bytes = (n_groups - 1) * NW * DT * 1024;
+  int* cut = reinterpret_cast<int*>(smem + max(ring_bytes, merge_bytes));  // [8]: this workgroup's piece where the device cuts
+  float* ml = reinterpret_cast<float*>(cut + 8);                           // [n_groups][NW][2][16]: max, sum per query
 
   // The wave index is made known to be wave-uniform, so that everything derived from it (unit, load
   // slots, base addresses) is computed on the scalar unit.
@@ -127,7 +127,11 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
   const int wl = wt & (LW - 1);
   unsigned char* my_stages = stages + (size_t)grp * n_stages * STAGE_BYTES;
   const uint32_t lds_stages = (uint32_t)(uintptr_t)my_stages;
-  const uint32_t new_stage = lds_stages + (uint32_t)(n_stages - 1) * STAGE_BYTES;
+  // LDS offset of the stage for this group's own block of round jn: the last ring stage, then the extra ones.
+  auto new_stage = [&](int jn) {
+    return jn == 0 || jn > n_extra ? (uint32_t)(grp * n_stages + n_stages - 1) * STAGE_BYTES
+                                   : (uint32_t)(n_groups * n_stages + grp * n_extra + jn - 1) * STAGE_BYTES;
+  };
 
   // This workgroup's piece: splits of the sequence (0: not known yet) and the first one's slot, lengths of split 0 and
   // of the others; this split's cached tokens are [k0, k1).
@@ -207,15 +211,15 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
     load_pages(a, 0);
     L_raw = a.seq_lens[b];
     n_kept = kept_nodes(b, a);
-    par_v = tid < a.T ? a.parent[(size_t)b * a.T + tid] : 0;
+    par_v = a.parent[(size_t)b * a.T + min(lane, a.T - 1)];
     R_kept = n_kept * (1 + a.gamma);
   };
   auto load_queries = [&](const MsaArgs& a) {
     const int f = qc * (16 * NW) + 16 * wt + lq;
     f_valid = f < a.g * R_kept;
-    const int f_row = f_valid ? f % R_kept : 0;
+    const int f_head = f_valid ? fast_div(f, R_kept) : 0, f_row = f_valid ? f - f_head * R_kept : 0;
     q_r = f_row < n_kept ? f_row : a.T + (f_row - n_kept);
-    q_h = hk * a.g + (f_valid ? f / R_kept : 0);
+    q_h = hk * a.g + f_head;
     const uint16_t* qp = (const uint16_t*)a.q + (((size_t)b * a.R + q_r) * a.H + q_h) * D + lg * 8;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) Qraw[ks] = ld16(qp + 32 * ks);
@@ -331,11 +335,17 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
     }
   };
 
-  // Split 0's first block of the step's own rows travels with the first round trip (its addresses need
-  // nothing from memory), into the last ring stage, which the main loop does not fill before its first barrier.
-  // Every sequence has a split 0, which scans them.
+  // Split 0's first blocks of the step's own rows travel with the first round trip (their addresses need
+  // nothing from memory), into the last ring stage, which the main loop does not fill before its first barrier, and the
+  // extra stages.  Every sequence has a split 0, which scans them.
   bool has_new = s == 0 && !spare && qc * (16 * NW) < a.g * R_kept;
-  if (has_new && loader && grp < n_new_units) dma_new(a, 32 * grp, new_stage);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
+  auto start_new = [&](const MsaArgs& a) {
+    if (has_new && loader)
+      for (int jn = 0; jn <= n_extra && jn * n_groups + grp < n_new_units; ++jn)
+        dma_new(a, 32 * (jn * n_groups + grp), lds0 + new_stage(jn));
+  };
+  start_new(a);
 
   // ---- where the device may cut the sequences: the lengths of all of them travel with the first trip, which goes out for
   // the host's cut: if that stands little is lost.  Otherwise one wave cuts anew and finds this workgroup's piece, and the
@@ -380,12 +390,11 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
       split0_keys = __builtin_amdgcn_readfirstlane(cut[5]);
       split_keys = __builtin_amdgcn_readfirstlane(cut[6]);
       slot0 = __builtin_amdgcn_readfirstlane(cut[7]);
-      __syncthreads();  // `cut` is free: the tree's parents go there
       const MsaArgs& a = reread_args<CUTS>(args);
       first_trip(a);
       load_queries(a);
       has_new = s == 0 && qc * (16 * NW) < a.g * R_kept;
-      if (has_new && loader && grp < n_new_units) dma_new(a, 32 * grp, new_stage);
+      start_new(a);
     }
   }
   k_head = (const uint16_t*)a.k_cache + (size_t)hk * a.page * D;
@@ -425,10 +434,6 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
     for (int i = 0; i < n_pre; ++i)
       dma_main(grp + i * n_groups, __builtin_amdgcn_readlane(tab_a, i), __builtin_amdgcn_readlane(tab_b, i),
                lds_stages + (uint32_t)i * STAGE_BYTES);
-  if (tid < T) par[tid] = clamp_parent(par_v, tid);
-  __syncthreads();
-  compute_anc(par, T, anc, tid);
-  __syncthreads();
 
   float pinf = INFINITY;  // see vmax2
   asm volatile("" : "+s"(pinf));
@@ -528,18 +533,23 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
   // ---- the step's own rows (split 0), one block per group and round, while the first prefix blocks
   // are on their way.
   if (has_new) {
-    const RowVis vis = make_row_vis(q_r, T, a.gamma, anc, (a.flags & SS_STREAM_EXCLUDE_SELF) != 0);
+    const int stream_row = q_r - T;
+    const int node = stream_row < 0 ? q_r : fast_div(stream_row, a.gamma), strm = stream_row < 0 ? 0 : stream_row - node * a.gamma + 1;
+    const uint64_t anc = ancestors_of(node, lane < T ? clamp_parent(par_v, lane) : -1);
+    const RowVis vis = make_row_vis(node, strm, anc, T, a.gamma, (a.flags & SS_STREAM_EXCLUDE_SELF) != 0);
+    __syncthreads();  // the blocks of rounds 0 .. n_extra have landed (the wait for the first trip was for them too)
     for (int jn = 0; jn * n_groups < n_new_units; ++jn) {
       const int un = jn * n_groups + grp;
       const bool mine = un < n_new_units;
-      if (jn > 0) {
-        __syncthreads();  // the previous round's block has been consumed
-        if (loader && mine) dma_new(a, 32 * un, new_stage);
+      if (jn > n_extra) {
+        __syncthreads();  // the stage has been consumed
+        if (loader && mine) {
+          dma_new(a, 32 * un, lds0 + new_stage(jn));
+          wait_vmcnt<0>();
+        }
+        __syncthreads();
       }
-      // round 0: only the prefix blocks issued after it may still be in flight; later rounds: nothing
-      if (loader && mine) wait_vm_units<LPB>(jn == 0 ? n_pre : 0);
-      __syncthreads();
-      if (mine) compute(std::false_type{}, true, 32 * un, my_stages + (size_t)(n_stages - 1) * STAGE_BYTES, vis);
+      if (mine) compute(std::false_type{}, true, 32 * un, smem + new_stage(jn), vis);
     }
   }
 
@@ -759,9 +769,14 @@ static int launch_dns(const MsaArgs& a, hipStream_t stream) {
   constexpr int lw = NW >= 4 ? 4 : NW >= 2 ? 2 : 1;
   const int n_stages = stages_for(n_groups, a.stages, stage_bytes, 2 * (32 * D * 2 / 1024) / lw);
   const size_t merge_bytes = (size_t)(n_groups - 1) * NW * (D / 16) * 64 * 16;
-  size_t lds = (size_t)n_groups * n_stages * stage_bytes;
+  // Stages for the step's own rows beyond one per group, where a compute unit holds one workgroup anyway: their later blocks
+  // need no trip of their own then.
+  int n_extra = 0;
+  if (n_groups > 1)
+    while (n_extra + 1 < ceil_div(ceil_div(a.R, 32), n_groups) && (size_t)n_groups * (n_stages + n_extra + 1) * stage_bytes <= 144 * 1024) ++n_extra;
+  size_t lds = (size_t)n_groups * (n_stages + n_extra) * stage_bytes;
   if (merge_bytes > lds) lds = merge_bytes;
-  lds += SS_MAX_T * 4 + SS_MAX_T * 8 + (size_t)n_groups * NW * 32 * 4;
+  lds += 8 * sizeof(int) + (size_t)n_groups * NW * 32 * 4;
   SS_REQUIRE(lds <= 160 * 1024, SS_ERR_UNSUPPORTED, "ss_msa_attention: %zu bytes of LDS needed", lds);
   auto kern = msa_bf16_kernel<D, NW, STREAM, CUTS>;
   static std::once_flag attr_once;
@@ -774,6 +789,7 @@ static int launch_dns(const MsaArgs& a, hipStream_t stream) {
   MsaArgs launch = a;
   launch.n_groups = n_groups;
   launch.n_stages = n_stages;
+  launch.n_extra = n_extra;
   hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(64 * NW * n_groups), lds, stream, launch);
   return check_launch("ss_msa_attention");
 }

@@ -42,10 +42,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
   constexpr int V_DBLK = K_SLOTS / 2, VHALF = D * 32;
   constexpr int ROWS = 32 * NW;
 
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // [NS][STAGE] | par (first used for `cut`) | anc
-  int* par = reinterpret_cast<int*>(smem + NS * STAGE);
-  uint64_t* anc = reinterpret_cast<uint64_t*>(par + SS_MAX_T);
-  int* cut = par;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // [NS][STAGE] | cut
+  int* cut = reinterpret_cast<int*>(smem + NS * STAGE);  // [8]: this workgroup's piece where the device cuts the sequences
 
   const int tid = threadIdx.x, lane = tid & 63, lq = lane & 31, lh = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -111,15 +109,15 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     load_pages(a, 0);
     L_raw = a.seq_lens[b];
     n_kept = kept_nodes(b, a);
-    par_v = tid < a.T ? a.parent[(size_t)b * a.T + tid] : 0;
+    par_v = a.parent[(size_t)b * a.T + min(lane, a.T - 1)];
     R_kept = n_kept * (1 + a.gamma);
   };
   auto load_queries = [&](const MsaArgs& a) {
     const int f = qc * ROWS + 32 * w + lq;
     f_valid = f < a.g * R_kept;
-    const int f_row = f_valid ? f % R_kept : 0;
+    const int f_head = f_valid ? fast_div(f, R_kept) : 0, f_row = f_valid ? f - f_head * R_kept : 0;
     q_r = f_row < n_kept ? f_row : a.T + (f_row - n_kept);
-    q_h = hk * a.g + (f_valid ? f / R_kept : 0);
+    q_h = hk * a.g + f_head;
     const uint16_t* qp = (const uint16_t*)a.q + (((size_t)b * a.R + q_r) * a.H + q_h) * D + lh * 8;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) Qraw[ks] = ld16(qp + 16 * ks);
@@ -243,7 +241,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
       split0_keys = __builtin_amdgcn_readfirstlane(cut[5]);
       split_keys = __builtin_amdgcn_readfirstlane(cut[6]);
       slot0 = __builtin_amdgcn_readfirstlane(cut[7]);
-      __syncthreads();  // `cut` is free: the tree's parents go there
       const MsaArgs& a = reread_args<CUTS>(args);
       first_trip(a);
       load_queries(a);
@@ -281,10 +278,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
   };
   if (loader)
     for (int i = n_own; i < min(n_blocks, NS - 1); ++i) fetch(i - n_own, lds0 + (uint32_t)(i - n_own) * STAGE);
-  if (tid < T) par[tid] = clamp_parent(par_v, tid);
-  __syncthreads();
-  compute_anc(par, T, anc, tid);
-  __syncthreads();
 
   floatx16 O[DT];
 #pragma unroll
@@ -398,7 +391,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
   // ---- the step's own rows (split 0): iteration u waits for its block, its barrier publishes it and frees the stage of
   // the one before, which block u + NS - 1 is sent to.
   if (has_new) {
-    const RowVis vis = make_row_vis(q_r, T, a.gamma, anc, (a.flags & SS_STREAM_EXCLUDE_SELF) != 0);
+    const int stream_row = q_r - T;
+    const int node = stream_row < 0 ? q_r : fast_div(stream_row, a.gamma), strm = stream_row < 0 ? 0 : stream_row - node * a.gamma + 1;
+    const uint64_t anc = ancestors_of(node, lane < T ? clamp_parent(par_v, lane) : -1);
+    const RowVis vis = make_row_vis(node, strm, anc, T, a.gamma, (a.flags & SS_STREAM_EXCLUDE_SELF) != 0);
     for (int u = 0; u < n_own; ++u) {
       if (loader) wait_vm_units<LPB>(min(n_blocks - 1 - u, NS - 2));
       __syncthreads();
@@ -522,7 +518,7 @@ static int launch_wide_dns(const MsaArgs& a, hipStream_t stream) {
   const int G = a.B * a.Hkv * a.n_splits;
   const long wgs = (long)ceil_div(G, 8) * 8 * a.n_qc;
   SS_REQUIRE(wgs <= 0x7fffffffL, SS_ERR_UNSUPPORTED, "ss_msa_attention: grid too large");
-  constexpr size_t lds = (size_t)NW * 4 * 32 * D + SS_MAX_T * 4 + SS_MAX_T * 8;
+  constexpr size_t lds = (size_t)NW * 4 * 32 * D + 8 * sizeof(int);
   auto kern = msa_bf16_wide_kernel<D, NW, STREAM, CUTS>;
   static std::once_flag attr_once;
   static hipError_t attr_err = hipSuccess;

@@ -85,25 +85,23 @@ struct PruneArgs {
 // below the threshold; a node stays iff every edge on its root path passes, i.e. iff its ancestor set
 // holds no failed node.  New numbers are ranks among the kept nodes (prefix count of the kept mask).
 __global__ __launch_bounds__(64) void tree_prune_kernel(PruneArgs a) {
-  __shared__ int par_lds[64];
-  __shared__ uint64_t anc[64];
   const int b = blockIdx.x, i = threadIdx.x, T = a.T;
   const bool live = i < T;
-  const int par = live ? clamp_parent(a.parent[(size_t)b * T + i], i) : -1;
-  par_lds[i] = par;
-  __syncthreads();
-  compute_anc(par_lds, T, anc, i);
-  __syncthreads();
-  const bool fails = live && i > 0 && (a.prob[(size_t)b * T + i] < a.threshold);
+  const size_t at = (size_t)b * T + min(i, T - 1);
+  const int par_raw = a.parent[at], tok = a.tok[at];
+  const float prob = a.prob[at];
+  const int par = live ? clamp_parent(par_raw, i) : -1;
+  const uint64_t anc = ancestors(i, par, T, T - 1);
+  const bool fails = live && i > 0 && prob < a.threshold;
   const uint64_t failed = __ballot(fails);
-  const bool kept = live && (anc[live ? i : 0] & failed) == 0;
+  const bool kept = live && (anc & failed) == 0;
   const uint64_t kept_mask = __ballot(kept);
   const int n = __popcll(kept_mask);
   if (live) {
     a.keep[(size_t)b * T + i] = kept ? 1 : 0;
     if (kept) {
       const int me = __popcll(kept_mask & ((1ull << i) - 1ull));
-      a.new_tok[(size_t)b * T + me] = a.tok[(size_t)b * T + i];
+      a.new_tok[(size_t)b * T + me] = tok;
       a.new_parent[(size_t)b * T + me] = i == 0 ? -1 : __popcll(kept_mask & ((1ull << par) - 1ull));
       a.old_index[(size_t)b * T + me] = i;
     }

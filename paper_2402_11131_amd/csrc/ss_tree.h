@@ -35,20 +35,6 @@ SS_DEV uint64_t wave_max_u64(uint64_t v) {
 }
 SS_DEV uint64_t max_u64(uint64_t a, uint64_t b) { return a > b ? a : b; }
 
-// Ancestors-or-self of node i (bit set) in a tree of T nodes, lane i of a wavefront holding node i's clamped parent p: the
-// set doubles its reach with every step.  Complete for nodes of fewer than `reach` ancestors; the others' sets have more
-// than `reach` members too.
-SS_DEV uint64_t ancestors(int i, int p, int T, int reach) {
-  uint64_t bits = i < T ? 1ull << i : 1ull;
-  int up = i < T && i > 0 ? p : 0;
-  for (int r = 1; r <= reach; r <<= 1) {
-    const uint32_t lo = __shfl((uint32_t)bits, up, 64), hi = __shfl((uint32_t)(bits >> 32), up, 64);
-    bits |= ((uint64_t)hi << 32) | lo;
-    up = __shfl(up, up, 64);
-  }
-  return bits;
-}
-
 // Acceptance is a property of a node's whole root path: every edge on it must match.  One wavefront, lane i = node i with
 // its parent p, token my_tok, ancestors `anc` (reach max_depth + 1), the main stream's arg-max a_own at the node and
 // a_parent at its parent: a node is accepted iff its ancestors-or-self hold no node whose edge fails.  The deepest accepted
