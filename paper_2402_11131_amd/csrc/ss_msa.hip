@@ -312,6 +312,13 @@ static bool wide_fits(int B, int R, int H, int Hkv, int D, int len) {
   return 10L * chunks * rows <= 11L * pad16 && (double)B * Hkv * chunks * ceil_div(len, 32) >= 75.0 * kWideSlots;
 }
 
+// Three or four splits are merged inside the attention kernel where the wave that finds itself last has little to read: few
+// rows of few features.  The merge kernel and its launch are saved, all of it for sequences of one split.  Us per layer with
+// the merge kernel and without (32 heads of 64, 5 rows, two sequences): in a table of four times their 411 and 777 tokens
+// 15.0 and 12.4, full tables of 2048 tokens 15.3 and 14.0, of 3100 18.0 and 17.5.  Beyond 512 values it loses or draws:
+// heads of 128, 5 rows 16.2 and 16.6, 38.7 and 40.0; 15 rows 22.3 and 23.9; eight splits 16.3 and 17.8, fourteen 17.5 and 33.5.
+static bool merges_few_rows(int F, int D, int n_splits) { return F * D <= 512 && n_splits <= 4; }
+
 static MsaPlan make_plan(int B, int R, int H, int Hkv, int D, int max_len, int dtype, bool allow_wide = true) {
   MsaPlan p;
   const int g = H / Hkv;
@@ -375,10 +382,13 @@ static MsaPlan make_plan(int B, int R, int H, int Hkv, int D, int max_len, int d
   if (dtype == SS_BF16 && p.n_splits > 1 && !overridden) {
     // Split 0 also scans the step's own rows: masked blocks with transposing reads, about `extra` blocks'
     // worth of time.  It gets that much less of the prefix; the others take whole iterations of all wave
-    // groups where that leaves split 0 something.
+    // groups where that leaves split 0 something.  Where it does not they take what they must (one sequence of 2048 tokens
+    // with 80 rows in 8 splits: one block and 7 x 9 instead of 8 x 8, 20.5 -> 20.0 us; 16 heads 19.9 -> 18.7, heads of 64
+    // 16.3 -> 15.5), with one block of `extra` less: with as many, 40 rows got splits of 9 blocks too, 18.0 -> 18.6 us.
     const int nu = ceil_div(len, 32), n = p.n_splits, extra = ceil_div(R, 32) + split0_extra_blocks();
     int rest = (nu + extra + n / 2) / n;
-    rest = (rest + p.groups / 2) / p.groups * p.groups;
+    const int whole = (rest + p.groups / 2) / p.groups * p.groups;
+    rest = nu - (n - 1) * whole >= 1 ? whole : (nu + extra - 1 + n / 2) / n;
     if (rest >= 2 && nu - (n - 1) * rest >= 1) {
       p.split_keys = 32 * rest;
       p.split0_keys = 32 * (nu - (n - 1) * rest);
@@ -402,7 +412,9 @@ static MsaPlan make_plan(int B, int R, int H, int Hkv, int D, int max_len, int d
   p.part_o_at = p.part_lse_at = p.table_at = 0;
   p.total_bytes = p.scratch_bytes = 256;  // to align the start
   if (p.n_splits > 1) {
-    const size_t counters = dtype == SS_BF16 && !p.wide && p.n_splits == 2
+    // Merged in the attention kernel: two splits, or a few of few rows (merges_few_rows)
+    const bool merged = dtype == SS_BF16 && !p.wide && (p.n_splits == 2 || merges_few_rows(g * R, D, p.n_splits));
+    const size_t counters = merged
                                 ? align_up((size_t)B * Hkv * p.n_qc * kArriveTiles * sizeof(unsigned int), 256) : 0;
     if (counters <= kArriveRegionBytes) p.arrive_bytes = counters;
     const size_t rows = (size_t)B * H * p.n_splits * R;
@@ -410,7 +422,7 @@ static MsaPlan make_plan(int B, int R, int H, int Hkv, int D, int max_len, int d
     p.part_lse_at = p.part_o_at + align_up(rows * D * sizeof(float), 256);
     p.table_at = p.part_lse_at + align_up(rows * sizeof(float), 256);
     p.total_bytes += p.table_at + (p.adaptive ? kAdaptiveMaxB * sizeof(int2) : 0);
-    p.scratch_bytes += p.table_at - kArriveRegionBytes + counters;
+    p.scratch_bytes += p.table_at - kArriveRegionBytes + (p.n_splits == 2 ? counters : 0);
   }
   return p;
 }

@@ -592,12 +592,12 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
   // (max, sum, O) in LDS; group 0 brings everything to a common maximum, adds and stores.
   const bool split_launch = a.n_splits > 1;
   const bool merge_here = split_launch && a.arrive != nullptr && !(a.flags & SS_MSA_PARTIALS_ONLY);
-  // In-kernel merge of two splits.  Every query tile of a split has an arrival counter.  A tile that finds
-  // the other split's tile already arrived (or the sequence too short to have another split) takes that
-  // split's partial rows from memory, folds them with what it holds in registers and writes the final rows.
-  // Otherwise it stores its own partial rows, announces itself, and does the same only if the other tile
+  // In-kernel merge of two splits (of a few, where there are few rows).  Every query tile has an arrival counter.  A tile
+  // that finds the other splits' tiles already arrived (or the sequence too short to have another split) takes their
+  // partial rows from memory, folds them with what it holds in registers and writes the final rows.
+  // Otherwise it stores its own partial rows, announces itself, and does the same only if the others have
   // arrived in between.  Nothing waits for anything.  The counter is read early, before the wave groups are
-  // merged, so that the other split's rows travel while that happens.
+  // merged, so that the one other split's rows travel while that happens.
   unsigned int* ctr = nullptr;
   unsigned int early = 0;
   if (merge_here && grp == 0) {
@@ -624,14 +624,14 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
   if (grp > 0) return;
 
   // rows of the other split, on their way during the merge of the groups
-  const int s_other = 1 - s;
+  const int s_other = 1 - s;  // where there are two
   early = __builtin_amdgcn_readfirstlane(early);
-  const bool others_ready = merge_here && early + 1 == (unsigned)n_active;  // n_active is 1 or 2 here
+  const bool others_ready = merge_here && early + 1 == (unsigned)n_active;
   const bool prefetched = others_ready && n_active == 2 && f_valid;
   float l_other = -INFINITY;
   floatx4 o_other[DT];
   auto part_row = [&](int sp) { return part_row_of<CUTS>(a, b, slot0, sp, q_h, q_r); };
-  const size_t pr_other = part_row(s_other);
+  const size_t pr_other = part_row(n_active == 2 ? s_other : s);
   if (prefetched) ld_row_device<DT>(a.part_lse + pr_other, a.part_o + pr_other * D + 4 * lg, l_other, o_other);
 
   float mm = m_run;
@@ -685,7 +685,7 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
     if (lane == 0) seen = atomicAdd(ctr, 1u);  // lane 0 holds the tile's first row: valid whenever any is
     seen = __builtin_amdgcn_readfirstlane(seen);
     fold_now = seen + 1 == (unsigned)n_active;
-    if (fold_now) ld_row_device<DT>(a.part_lse + pr_other, a.part_o + pr_other * D + 4 * lg, l_other, o_other);
+    if (fold_now && n_active == 2) ld_row_device<DT>(a.part_lse + pr_other, a.part_o + pr_other * D + 4 * lg, l_other, o_other);
   }
   if (!fold_now) return;
   // the splits in index order with the arithmetic of the merge kernel, so that the result does not depend
@@ -704,9 +704,32 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
       M = m_new;
     }
   };
-  if (n_active == 2 && s_other == 0) fold(l_other, o_other);
-  fold(my_lse, O);
-  if (n_active == 2 && s_other == 1) fold(l_other, o_other);
+  bool folded = false;
+  if constexpr (NW == 1) {
+    if (n_active > 2) {  // four splits at a time; past the end the last one again, this split's own from registers
+      folded = true;
+      for (int s0 = 0; s0 < n_active; s0 += 4) {
+        float l4[4];
+        floatx4 o4[4][DT];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const size_t at = part_row(min(s0 + i, n_active - 1));
+          ld_row_device<DT>(a.part_lse + at, a.part_o + at * D + 4 * lg, l4[i], o4[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (s0 + i < n_active) {
+            if (s0 + i == s) fold(my_lse, O);
+            else fold(l4[i], o4[i]);
+          }
+      }
+    }
+  }
+  if (!folded) {
+    if (n_active == 2 && s_other == 0) fold(l_other, o_other);
+    fold(my_lse, O);
+    if (n_active == 2 && s_other == 1) fold(l_other, o_other);
+  }
   const float inv2 = wsum > 0.f ? 1.f / wsum : 0.f;
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) {
