@@ -17,22 +17,25 @@ struct ProbArgs {
   int B, T, d, V;
 };
 
-// One wavefront per (sequence, node): the early-exit logit of the PARENT's row at the node's token is
-// a dot product of length d; prob = exp(logit - lse[parent]).
+// One workgroup per (sequence, node): the early-exit logit of the PARENT's row at the node's token is
+// a dot product of length d; prob = exp(logit - lse[parent]).  All latency: two round trips (tree, then the two rows and the
+// normaliser).  Four waves, two pieces per thread and trip: 4.0 us for 64 nodes of 4096 features; one wave in eight trips 6.1 us.
 template <bool BF16>
-__global__ __launch_bounds__(64) void transition_prob_kernel(ProbArgs a) {
-  const int b = blockIdx.x / a.T, i = blockIdx.x % a.T, lane = threadIdx.x;
+__global__ __launch_bounds__(256) void transition_prob_kernel(ProbArgs a) {
+  __shared__ float part[4];
+  const int b = blockIdx.x / a.T, i = blockIdx.x % a.T, tid = threadIdx.x;
   float* out = a.prob + (size_t)b * a.T + i;
   if (i == 0) {
-    if (lane == 0) *out = 1.f;
+    if (tid == 0) *out = 1.f;
     return;
   }
-  const int p = clamp_parent(a.parent[(size_t)b * a.T + i], i);
-  const int c = a.tok[(size_t)b * a.T + i];
+  const int p_raw = a.parent[(size_t)b * a.T + i], c = a.tok[(size_t)b * a.T + i];
+  const int p = clamp_parent(p_raw, i);
   if (c < 0 || c >= a.V) {
-    if (lane == 0) *out = 0.f;
+    if (tid == 0) *out = 0.f;
     return;
   }
+  const float lse = a.lse[(size_t)b * a.T + p];
   const size_t hr = ((size_t)b * a.T + p) * a.d, wr = (size_t)c * a.d;
   float acc = 0.f;
   constexpr int PER = BF16 ? 8 : 4;  // elements per 16-byte piece
@@ -40,20 +43,34 @@ __global__ __launch_bounds__(64) void transition_prob_kernel(ProbArgs a) {
   if (vec) {
     const uintx4* hv = reinterpret_cast<const uintx4*>((const unsigned char*)a.h + hr * (BF16 ? 2 : 4));
     const uintx4* wv = reinterpret_cast<const uintx4*>((const unsigned char*)a.W + wr * (BF16 ? 2 : 4));
-    for (int c0 = lane; c0 < a.d / PER; c0 += 64) {
-      const uintx4 x = hv[c0], y = wv[c0];
+    const int n = a.d / PER;
+    for (int c0 = 0; c0 < n; c0 += 512) {
+      uintx4 x[2], y[2];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if constexpr (BF16) {
-          acc = fmaf(bf16_bits_to_f32(x[q] & 0xffffu), bf16_bits_to_f32(y[q] & 0xffffu), acc);
-          acc = fmaf(bf16_bits_to_f32(x[q] >> 16), bf16_bits_to_f32(y[q] >> 16), acc);
-        } else {
-          acc = fmaf(__uint_as_float(x[q]), __uint_as_float(y[q]), acc);
+      for (int j = 0; j < 2; ++j) {
+        const int at = min(c0 + 256 * j + tid, n - 1);
+        x[j] = hv[at];
+        y[j] = wv[at];
+      }
+#pragma unroll
+      for (int j = 0; j < 2; ++j) asm volatile("" : "+v"(x[j]), "+v"(y[j]));
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        float piece = 0.f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          if constexpr (BF16) {
+            piece = fmaf(bf16_bits_to_f32(x[j][q] & 0xffffu), bf16_bits_to_f32(y[j][q] & 0xffffu), piece);
+            piece = fmaf(bf16_bits_to_f32(x[j][q] >> 16), bf16_bits_to_f32(y[j][q] >> 16), piece);
+          } else {
+            piece = fmaf(__uint_as_float(x[j][q]), __uint_as_float(y[j][q]), piece);
+          }
         }
+        acc += c0 + 256 * j + tid < n ? piece : 0.f;
       }
     }
   } else
-  for (int e = lane; e < a.d; e += 64) {
+  for (int e = tid; e < a.d; e += 256) {
     float x, y;
     if constexpr (BF16) {
       x = bf16_bits_to_f32(((const uint16_t*)a.h)[hr + e]);
@@ -65,7 +82,9 @@ __global__ __launch_bounds__(64) void transition_prob_kernel(ProbArgs a) {
     acc = fmaf(x, y, acc);
   }
   for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-  if (lane == 0) *out = expf(acc - a.lse[(size_t)b * a.T + p]);
+  if ((tid & 63) == 0) part[tid >> 6] = acc;
+  __syncthreads();
+  if (tid == 0) *out = expf(part[0] + part[1] + part[2] + part[3] - lse);
 }
 
 struct PruneArgs {
@@ -155,8 +174,8 @@ int ss_transition_probs(const void* h, const void* W, const int32_t* tok, const 
   a.h = h; a.W = W; a.tok = tok; a.parent = parent; a.lse = lse; a.prob = prob;
   a.B = B; a.T = T; a.d = d; a.V = V;
   const dim3 grid((unsigned)(B * T));
-  if (dtype == SS_F32) hipLaunchKernelGGL(transition_prob_kernel<false>, grid, dim3(64), 0, (hipStream_t)stream, a);
-  else hipLaunchKernelGGL(transition_prob_kernel<true>, grid, dim3(64), 0, (hipStream_t)stream, a);
+  if (dtype == SS_F32) hipLaunchKernelGGL(transition_prob_kernel<false>, grid, dim3(256), 0, (hipStream_t)stream, a);
+  else hipLaunchKernelGGL(transition_prob_kernel<true>, grid, dim3(256), 0, (hipStream_t)stream, a);
   return check_launch(fn);
 }
 
