@@ -116,7 +116,8 @@ def _check(rc: int):
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    # the handle itself: a Stream object made for each call and asked for its handle costs 1.5 us
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _dev(t: torch.Tensor, dtype, name: str) -> int:
@@ -224,11 +225,11 @@ def _msa_shapes(q, k_new, v_new, k_cache, v_cache, block_table, seq_lens, parent
     Hkv = k_new.shape[2]
     T = parent.shape[1]
     P, _, page, _ = k_cache.shape
-    if R != T * (1 + gamma) or tuple(k_new.shape) != (B, R, Hkv, D) or tuple(v_new.shape) != (B, R, Hkv, D):
+    if R != T * (1 + gamma) or k_new.shape != (B, R, Hkv, D) or v_new.shape != (B, R, Hkv, D):
         raise ValueError("q / k_new / v_new shapes do not match B,R,H,Hkv,D")
-    if tuple(k_cache.shape) != (P, Hkv, page, D) or tuple(v_cache.shape) != (P, Hkv, D, page):
+    if k_cache.shape != (P, Hkv, page, D) or v_cache.shape != (P, Hkv, D, page):
         raise ValueError("k_cache must be [P,Hkv,page,D] and v_cache [P,Hkv,D,page]")
-    if block_table.shape[0] != B or tuple(seq_lens.shape) != (B,) or parent.shape[0] != B:
+    if block_table.shape[0] != B or seq_lens.shape != (B,) or parent.shape[0] != B:
         raise ValueError("block_table / seq_lens / parent batch size mismatch")
     return B, R, H, D, Hkv, T, P, page, block_table.shape[1]
 
@@ -250,7 +251,7 @@ def ss_msa_attention(q, k_new, v_new, k_cache, v_cache, block_table, seq_lens, p
     if workspace is None:
         workspace = ss_msa_workspace(B, T, gamma, H, Hkv, D, max_pages * page, code, q.device)
     if n_nodes is not None:
-        if tuple(n_nodes.shape) != (B,):
+        if n_nodes.shape != (B,):
             raise ValueError("n_nodes must be [B]")
         _check(lib.ss_msa_attention_pruned(
             _dev(q, dt, "q"), _dev(k_new, dt, "k_new"), _dev(v_new, dt, "v_new"), _dev(k_cache, dt, "k_cache"),
@@ -519,9 +520,9 @@ def ss_kv_commit(k_new, v_new, k_cache, v_cache, block_table, seq_lens, path, n_
     if R % (1 + gamma):
         raise ValueError("k_new has %d rows, not a multiple of 1+gamma" % R)
     T = R // (1 + gamma)
-    if tuple(v_new.shape) != (B, R, Hkv, D) or tuple(k_cache.shape) != (P, Hkv, page, D) or tuple(v_cache.shape) != (P, Hkv, D, page):
+    if v_new.shape != (B, R, Hkv, D) or k_cache.shape != (P, Hkv, page, D) or v_cache.shape != (P, Hkv, D, page):
         raise ValueError("k_new/v_new must be [B,R,Hkv,D], k_cache [P,Hkv,page,D], v_cache [P,Hkv,D,page]")
-    if block_table.shape[0] != B or tuple(seq_lens.shape) != (B,) or path.shape[0] != B or tuple(n_accept.shape) != (B,):
+    if block_table.shape[0] != B or seq_lens.shape != (B,) or path.shape[0] != B or n_accept.shape != (B,):
         raise ValueError("block_table / seq_lens / path / n_accept batch size mismatch")
     i32 = torch.int32
     if new_seq_lens is None and want_lens:
@@ -543,7 +544,7 @@ def ss_kv_alloc_pages(block_table, seq_lens, n_accept, page: int, max_depth: int
     lib = load_library()
     i32 = torch.int32
     B, max_pages = block_table.shape
-    if tuple(seq_lens.shape) != (B,) or tuple(n_accept.shape) != (B,) or free_count.numel() != 1:
+    if seq_lens.shape != (B,) or n_accept.shape != (B,) or free_count.numel() != 1:
         raise ValueError("seq_lens / n_accept must be [B], free_count one element")
     if n_commit is None:
         n_commit = torch.empty(B, dtype=i32, device=block_table.device)
@@ -562,11 +563,11 @@ def ss_linear_rows(x: torch.Tensor, W: torch.Tensor, y: Optional[torch.Tensor] =
     dt = x.dtype
     N, d = x.shape
     V = W.shape[0]
-    if tuple(W.shape) != (V, d):
+    if W.shape != (V, d):
         raise ValueError("W must be [V,%d]" % d)
     if y is None:
         y = torch.empty(N, V, dtype=dt, device=x.device)
-    elif tuple(y.shape) != (N, V):
+    elif y.shape != (N, V):
         raise ValueError("y must be [%d,%d]" % (N, V))
     if live is not None:
         _check(lib.ss_linear_rows_live(_dev(x, dt, "x"), _dev(W, dt, "W"), N, d, V, code, _dev(y, dt, "y"),
@@ -595,11 +596,11 @@ def ss_linear_rows_ws(x: torch.Tensor, W: torch.Tensor, y: Optional[torch.Tensor
     dt = x.dtype
     N, d = x.shape
     V = W.shape[0]
-    if tuple(W.shape) != (V, d):
+    if W.shape != (V, d):
         raise ValueError("W must be [V,%d]" % d)
     if y is None:
         y = torch.empty(N, V, dtype=dt, device=x.device)
-    elif tuple(y.shape) != (N, V):
+    elif y.shape != (N, V):
         raise ValueError("y must be [%d,%d]" % (N, V))
     if workspace is None:
         workspace = torch.empty(max(ss_linear_rows_workspace_bytes(N, d, V, code), 1), dtype=torch.uint8, device=x.device)
@@ -616,14 +617,14 @@ def ss_stream_insert(M: torch.Tensor, P: torch.Tensor, fM: Optional[torch.Tensor
     dt = M.dtype
     B, T, d = M.shape
     gamma = P.shape[0]
-    if tuple(P.shape) != (gamma, d):
+    if P.shape != (gamma, d):
         raise ValueError("P must be [gamma,%d]" % d)
-    if fM is not None and tuple(fM.shape) != (B, T, d):
+    if fM is not None and fM.shape != (B, T, d):
         raise ValueError("fM must have M's shape")
     R = T * (1 + gamma)
     if X is None:
         X = torch.empty(B, R, d, dtype=dt, device=M.device)
-    elif tuple(X.shape) != (B, R, d):
+    elif X.shape != (B, R, d):
         raise ValueError("X must be [%d,%d,%d]" % (B, R, d))
     _check(lib.ss_stream_insert(_dev(M, dt, "M"), None if fM is None else _dev(fM, dt, "fM"), _dev(P, dt, "P"),
                                 B, T, gamma, d, code, _dev(X, dt, "X"), _stream()))
@@ -638,14 +639,14 @@ def ss_stream_insert_linear(M: torch.Tensor, P: torch.Tensor, W: torch.Tensor, f
     dt = M.dtype
     B, T, d = M.shape
     gamma, V = P.shape[0], W.shape[0]
-    if tuple(P.shape) != (gamma, d) or tuple(W.shape) != (V, d):
+    if P.shape != (gamma, d) or W.shape != (V, d):
         raise ValueError("P must be [gamma,%d] and W [V,%d]" % (d, d))
-    if fM is not None and tuple(fM.shape) != (B, T, d):
+    if fM is not None and fM.shape != (B, T, d):
         raise ValueError("fM must have M's shape")
     R = T * (1 + gamma)
     if Y is None:
         Y = torch.empty(B, R, V, dtype=dt, device=M.device)
-    elif tuple(Y.shape) != (B, R, V):
+    elif Y.shape != (B, R, V):
         raise ValueError("Y must be [%d,%d,%d]" % (B, R, V))
     need = lib.ss_stream_insert_linear_workspace_bytes(B, T, gamma, d, V, code, 0 if fM is None else 1)
     if workspace is None:
@@ -676,7 +677,7 @@ def ss_lm_head_logsumexp(hidden: torch.Tensor, W: torch.Tensor, lse: Optional[to
     dt = hidden.dtype
     N, d = hidden.shape
     V = W.shape[0]
-    if tuple(W.shape) != (V, d):
+    if W.shape != (V, d):
         raise ValueError("W must be [V,%d]" % d)
     if lse is None:
         lse = torch.empty(N, dtype=torch.float32, device=hidden.device)
@@ -696,7 +697,7 @@ def ss_transition_probs(h: torch.Tensor, W: torch.Tensor, tok: torch.Tensor, par
     dt = h.dtype
     B, T, d = h.shape
     V = W.shape[0]
-    if tuple(W.shape) != (V, d) or tuple(tok.shape) != (B, T) or tuple(parent.shape) != (B, T) or lse.numel() != B * T:
+    if W.shape != (V, d) or tok.shape != (B, T) or parent.shape != (B, T) or lse.numel() != B * T:
         raise ValueError("W must be [V,d], tok/parent [B,T], lse [B*T]")
     if prob is None:
         prob = torch.empty(B, T, dtype=torch.float32, device=h.device)
@@ -712,7 +713,7 @@ def ss_tree_prune(tok: torch.Tensor, parent: torch.Tensor, prob: torch.Tensor, t
     padded trees."""
     lib = load_library()
     B, T = tok.shape
-    if tuple(parent.shape) != (B, T) or tuple(prob.shape) != (B, T):
+    if parent.shape != (B, T) or prob.shape != (B, T):
         raise ValueError("parent and prob must be [B,T]")
     i32 = torch.int32
     out = {k: torch.empty(B, T, dtype=i32, device=tok.device) for k in ("keep", "tok", "parent", "old_index")}
