@@ -42,8 +42,6 @@ SS_DEV int lm_row_id(const LmArgs& a, int r, int n_rows) {
   return a.live_rows ? min(max(a.live_rows[rc], 0), a.N - 1) : rc;
 }
 
-SS_DEV bool cand_better(float v, int i, float bv, int bi) { return v > bv || (v == bv && i < bi); }
-SS_DEV bool cand_after(float v, int i, float pv, int pi) { return v < pv || (v == pv && i > pi); }
 
 // (max, sum of exp(x - max)) of two sets of logits -> of their union.  An empty set is (-inf, 0).
 SS_DEV float2 lse_merge(float2 p, float2 q) {
@@ -74,17 +72,22 @@ SS_DEV int key_id(uint64_t k) { return k == 0 ? INT_MAX : (int)(0xffffffffu - (u
 // Workgroup tile BM (32 or 8) rows x 64 vocabulary columns, feature chunks of 64 through LDS (rows padded by 16
 // bytes: 16-byte reads of 16 lanes meet 64 different banks), the next chunk on its way to registers meanwhile;
 // thread (wave w, lane c) accumulates rows w, w+4, ... of column c.  8 rows where tiles of 32 would be few (see
-// launch_lm_f32): 32 rows x 256 features x 1000 ids took 40.4 us in 16 workgroups with nothing in flight (the step it
-// is half of: 91 -> 28 us).
+// launch_lm_f32): 32 rows x 256 features x 1000 ids took 40.4 us in 16 workgroups with nothing in flight.
+//
+// A wave's sums never leave it: its K maxima per row are of 64-bit keys by register moves (K rounds of lane shuffles over a
+// copy of the tile in LDS before; with the tail, 40 rows x 256 x 1000: 14.5 -> 11.5 us, 6 x 2048 x 32000: 71.8 -> 66.9).
+// 32 rows: four waves per SIMD are asked for.  With that LDS gone the compiler plans for six and puts the loads behind the
+// barrier (320 rows x 1024 x 8000: 296 us; at four 146, before 187; 1000 x 4096 x 4000: 712, before 785); a second chunk of
+// features in flight lost at four waves (188) and at three (150, 805), and gained nothing with 8 rows (11.5 -> 12.4).
 //
 // MODE 0: top-K search.  MODE 1: the plain projection, the tile is written to y.  MODE 2: (max, sum of
 // exp) of the tile's logits per row, for the log-sum-exp over the vocabulary.
 template <int MODE, int BM>
-__global__ __launch_bounds__(256) void lm_head_f32_kernel(LmArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BM == 32 ? 4 : 1, BM == 32 ? 4 : 8)))
+void lm_head_f32_kernel(LmArgs a) {
   constexpr int BN = 64, BK = 64;
   __shared__ __attribute__((aligned(16))) float As[BM][BK + 4];
   __shared__ __attribute__((aligned(16))) float Ws[BN][BK + 4];
-  __shared__ float Z[BM][BN + 1];
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
   const int v0 = blockIdx.x * BN, r0 = blockIdx.y * BM;
   const int n_rows = lm_rows(a);
@@ -141,50 +144,29 @@ __global__ __launch_bounds__(256) void lm_head_f32_kernel(LmArgs a) {
     }
     return;
   }
-#pragma unroll
-  for (int i = 0; i < BM / 4; ++i) Z[w + 4 * i][lane] = acc[i];
-  __syncthreads();
   if constexpr (MODE == 2) {
-    for (int rr = w; rr < BM; rr += 4) {
-      if (r0 + rr >= n_rows) break;
-      const int row = lm_row_id(a, r0 + rr, n_rows);
-      float2 p = v0 + lane < a.V ? make_float2(Z[rr][lane], 1.f) : make_float2(-INFINITY, 0.f);
+#pragma unroll
+    for (int i = 0; i < BM / 4; ++i) {
+      if (r0 + w + 4 * i >= n_rows) break;
+      const int row = lm_row_id(a, r0 + w + 4 * i, n_rows);
+      float2 p = v0 + lane < a.V ? make_float2(acc[i], 1.f) : make_float2(-INFINITY, 0.f);
       for (int off = 32; off > 0; off >>= 1)
         p = lse_merge(p, make_float2(__shfl_xor(p.x, off, 64), __shfl_xor(p.y, off, 64)));
       if (lane == 0) reinterpret_cast<float2*>(a.cand_key)[(size_t)row * a.n_tiles + blockIdx.x] = p;
     }
     return;
   }
-  // wave w selects for rows w, w+4, ...: K rounds of a wave-wide arg-max over the 64 columns
-  for (int rr = w; rr < BM; rr += 4) {
-    if (r0 + rr >= n_rows) break;
-    const int row = lm_row_id(a, r0 + rr, n_rows);
-    const int col = v0 + lane;
-    const float v = col < a.V ? Z[rr][lane] : -INFINITY;
-    const int ci = col < a.V ? col : INT_MAX;
-    float pv = INFINITY;
-    int pi = -1;
+  // wave w selects for rows w, w+4, ...: K maxima over the 64 columns' keys by register moves (a NaN is never selected)
+#pragma unroll
+  for (int i = 0; i < BM / 4; ++i) {
+    if (r0 + w + 4 * i >= n_rows) break;
+    uint64_t* out = a.cand_key + ((size_t)lm_row_id(a, r0 + w + 4 * i, n_rows) * a.n_tiles + blockIdx.x) * a.K;
+    uint64_t mine = v0 + lane < a.V && acc[i] == acc[i] ? cand_key(acc[i], v0 + lane) : 0;
+#pragma unroll 1
     for (int k = 0; k < a.K; ++k) {
-      float bv = -INFINITY;
-      int bi = INT_MAX;
-      if (cand_after(v, ci, pv, pi)) {
-        bv = v;
-        bi = ci;
-      }
-      for (int off = 32; off > 0; off >>= 1) {
-        const float ov = __shfl_xor(bv, off, 64);
-        const int oi = __shfl_xor(bi, off, 64);
-        if (cand_better(ov, oi, bv, bi)) {
-          bv = ov;
-          bi = oi;
-        }
-      }
-      if (lane == 0) {
-        const size_t o = ((size_t)row * a.n_tiles + blockIdx.x) * a.K + k;
-        a.cand_key[o] = bi == INT_MAX ? 0 : cand_key(bv, bi);
-      }
-      pv = bv;
-      pi = bi;
+      const uint64_t best = wave_max_u64(mine);
+      if (lane == 0) out[k] = best;
+      if (mine == best) mine = 0;
     }
   }
 }
@@ -917,7 +899,7 @@ static int launch_lm_bf16(LmFlavour f, int KT, hipStream_t st, const LmArgs& arg
 }
 
 // Which MFMA kernel, how many rows per workgroup and how many row chunks.  A compute unit holds one workgroup
-// (LDS) and sustains a fixed number of outstanding reads, so a launch takes about (rounds of 256 workgroups) x
+// (LDS) and its reads, hits behind misses, come at a nearly fixed rate, so a launch takes about (rounds of 256 workgroups) x
 // (bytes a workgroup loads) x (latency): the shape with the smallest rounds x (ids + rows) per tile wins; among
 // equals the one with fewer workgroups, i.e. less traffic through the L2 in all (12288 outputs: 192 workgroups of
 // 128 ids x 160 rows take 50 us, 256 workgroups of 192 ids x 96 rows 53 us).  Measured with weights that no cache holds, 320 rows: 32000 outputs ->
@@ -955,7 +937,7 @@ template <int MODE>
 static int launch_lm_f32(const char* fn, hipStream_t st, const LmArgs& a, int plan_rows) {
   const int chunks = ceil_div(a.N, 32);
   SS_REQUIRE(chunks <= 65535, SS_ERR_UNSUPPORTED, "%s: N too large", fn);
-  // Eight rows per workgroup while they are at most 3200 (us with 8 and with 32 rows per workgroup, the latter's number; 625:
+  // Eight rows per workgroup while they are at most 3200 (us with 8 and with 32 rows as first measured, the latter's number; 625:
   // 54 and 70, 640: 178 and 287, 790: 34 and 38; then 960: 256 and 297, 1000: 82 and 75, 1020: 37 and 33: they hide more
   // latency but read W four times as often), and for eight rows or fewer, where 32 are mostly padding (4000: 100 and 356).
   const int eights = ceil_div(a.N, 8);

@@ -19,11 +19,28 @@ namespace ss {
 // Softmax is the usual running max / running sum in the log2 domain.
 //
 // Small problems are all latency: a tile's values are fetched into registers while the tile before is computed, with
-// one page lookup per lane (the wave's other lanes' rows come by lane reads), and operands leave LDS four at a time.
-// RW = 8, or 2 (see the launch).  One layer of 4 heads of 64, 128 cached tokens, 32 rows: 45.6 us before, with eight rows
-// per wave, a lookup and an uncovered load per value; with the fp32 LM head (1000 ids) the whole step 91 -> 28 us, and
-// where RW is 8 either way (4 sequences of 500..1000 tokens, 192 rows, 8 heads) the attention 174 -> 106 us.  Heads of
-// 128: 16 of them over 8192 tokens 397 -> 184 us, 256 over 1000 tokens with 192 rows 5185 -> 1876 us.
+// one page lookup per lane (the wave's other lanes' rows come by lane reads); the queries are asked for before the first
+// lookup is waited for.  A tile's maximum is taken by register moves and a row's sum once, at the end (by lane shuffles, and
+// each tile: 10 us of 40 rows' 15).  Operands leave LDS four steps at a time, two with heads of 128: the code of more of them
+// is fetched cold by every launch (eight: 11.9 -> 14.4 us).  RW = 8, 2 or 1 (see the launch).  Before and after, one layer:
+// 4 heads of 64, 128 cached tokens, 40 rows 15.0 -> 9.8 us; 8 heads of 64, 4 sequences of 500..1000 tokens, 192 rows (RW = 8)
+// 109 -> 92; 16 heads of 128, 8000 tokens, 40 rows 202 -> 150; 32 of 128 on 8, 4 sequences of 500..1000, 80 rows 331 -> 254.
+// Maximum over a wavefront by register moves (a lane shuffle is a trip through LDS).
+template <int ROR>
+SS_DEV float row_ror(float v) {
+  return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp((int)__float_as_uint(v), (int)__float_as_uint(v), 0x120 + ROR, 0xf, 0xf, false));
+}
+SS_DEV float wave_max_f32(float v) {
+  v = fmaxf(v, row_ror<8>(v));
+  v = fmaxf(v, row_ror<4>(v));
+  v = fmaxf(v, row_ror<2>(v));
+  v = fmaxf(v, row_ror<1>(v));
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto c = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(c[0]), __uint_as_float(c[1]));
+}
+
 template <int D, int RW>
 __global__ __launch_bounds__(256) void msa_f32_kernel(MsaArgs a) {
   constexpr int RC = 4 * RW, KT = 64, DL = D / 64;
@@ -55,22 +72,11 @@ __global__ __launch_bounds__(256) void msa_f32_kernel(MsaArgs a) {
   const float* v_cache = (const float*)a.v_cache;
 
   const int par = a.parent[(size_t)b * T + min(lane, T - 1)];
-  for (int e = tid; e < RC * D; e += 256) {
-    const int r = e / D, d = e % D;
-    Qs[r][d] = (r0 + r < R) ? q[(((size_t)b * R + r0 + r) * a.H + h) * D + d] : 0.f;
-  }
-
-  RowVis vis[RW];
-  float m[RW], l[RW], o[RW][DL];
+  float qv[RC * D / 256];  // asked for before, and put down after, the first tile's page lookup is waited for
 #pragma unroll
-  for (int i = 0; i < RW; ++i) {
-    int node, strm;
-    row_split(min(r0 + w * RW + i, R - 1), T, a.gamma, node, strm);
-    vis[i] = make_row_vis(node, strm, ancestors_of(node, lane < T ? clamp_parent(par, lane) : -1), T, a.gamma, (a.flags & SS_STREAM_EXCLUDE_SELF) != 0);
-    m[i] = -1e30f;
-    l[i] = 0.f;
-#pragma unroll
-    for (int dd = 0; dd < DL; ++dd) o[i][dd] = 0.f;
+  for (int i = 0; i < RC * D / 256; ++i) {
+    const int r = (tid + 256 * i) / D, d = (tid + 256 * i) % D;
+    qv[i] = q[(((size_t)b * R + min(r0 + r, R - 1)) * a.H + h) * D + d];
   }
 
   // Tile t0's values on their way to registers.  Of K a wave takes whole rows (or halves), of V whole features of the
@@ -107,6 +113,22 @@ __global__ __launch_bounds__(256) void msa_f32_kernel(MsaArgs a) {
     for (int i = 0; i < NL; ++i) vv[i] = vp[(size_t)(w_u + 4 * i) * vstride];
   };
   if (total > 0) fetch(0);
+#pragma unroll
+  for (int i = 0; i < RC * D / 256; ++i) Qs[(tid + 256 * i) / D][(tid + 256 * i) % D] = qv[i];
+
+  RowVis vis[RW];
+  float m[RW], l[RW], o[RW][DL];
+#pragma unroll
+  for (int i = 0; i < RW; ++i) {
+    int node, strm;
+    row_split(min(r0 + w * RW + i, R - 1), T, a.gamma, node, strm);
+    vis[i] = make_row_vis(node, strm, ancestors_of(node, lane < T ? clamp_parent(par, lane) : -1), T, a.gamma, (a.flags & SS_STREAM_EXCLUDE_SELF) != 0);
+    m[i] = -1e30f;
+    l[i] = 0.f;
+#pragma unroll
+    for (int dd = 0; dd < DL; ++dd) o[i][dd] = 0.f;
+  }
+
   for (int t0 = 0; t0 < total; t0 += KT) {
     __syncthreads();  // the previous tile has been consumed
 #pragma unroll
@@ -120,7 +142,7 @@ __global__ __launch_bounds__(256) void msa_f32_kernel(MsaArgs a) {
     float sc[RW];
 #pragma unroll
     for (int i = 0; i < RW; ++i) sc[i] = 0.f;
-#pragma unroll 4
+#pragma unroll (D == 128 ? 2 : 4)
     for (int d = 0; d < D; d += 4) {
       const floatx4 kd = *reinterpret_cast<const floatx4*>(&Ks[lane][d]);
 #pragma unroll
@@ -136,14 +158,10 @@ __global__ __launch_bounds__(256) void msa_f32_kernel(MsaArgs a) {
       bool vis_ok = u < total;
       if (u >= n_prefix) vis_ok = vis_ok && row_sees(vis[i], u - n_prefix, T);
       const float sv = vis_ok ? sc[i] * a.scale_log2 : -INFINITY;
-      float mx = sv;
-      for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-      const float m_new = fmaxf(m[i], mx);
+      const float m_new = fmaxf(m[i], wave_max_f32(sv));
       const float alpha = exp2f(m[i] - m_new);
       const float p = exp2f(sv - m_new);
-      float ps = p;
-      for (int off = 32; off > 0; off >>= 1) ps += __shfl_xor(ps, off, 64);
-      l[i] = l[i] * alpha + ps;
+      l[i] = l[i] * alpha + p;  // this lane's keys; the lanes are summed at the end
       m[i] = m_new;
 #pragma unroll
       for (int dd = 0; dd < DL; ++dd) o[i][dd] *= alpha;
@@ -154,7 +172,7 @@ __global__ __launch_bounds__(256) void msa_f32_kernel(MsaArgs a) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll 4
+#pragma unroll (D == 128 ? 2 : 4)
     for (int kk = 0; kk < KT; kk += 4) {
       floatx4 vk[DL];
 #pragma unroll
@@ -175,6 +193,7 @@ __global__ __launch_bounds__(256) void msa_f32_kernel(MsaArgs a) {
     const int row = r0 + w * RW + i;
     if (row >= R) continue;
     if ((row < T ? row : (row - T) / max(a.gamma, 1)) >= n_kept) continue;  // rows of removed nodes are not written
+    for (int off = 32; off > 0; off >>= 1) l[i] += __shfl_xor(l[i], off, 64);
     const float inv = l[i] > 0.f ? 1.f / l[i] : 0.f;
     if (a.n_splits == 1) {
       float* out = (float*)a.out + (((size_t)b * R + row) * a.H + h) * D;
@@ -572,15 +591,17 @@ static int msa_run(const char* fn, const void* q, const void* k_new, const void*
   if (flags & SS_MSA_MERGE_ONLY) {
     // the attention kernel ran in an earlier call with SS_MSA_PARTIALS_ONLY
   } else if (dtype == SS_F32) {
-    // Rows per workgroup of the fp32 kernel, by the workgroups that chunks of 32 rows and the splits really make.  D = 64:
-    // 8 while those are fewer than 512 (us with 8 and with 32 rows; 128: 32 and 64, 256: 46 and 66, 384: 67 and 81, 512: 75
-    // and 71 or 124 and 113, 768: 174 and 129): smaller workgroups hide more latency but read K and V four times as often.
-    // D = 128: always 8, two workgroups per compute unit (75 KB of LDS) where of 32 rows (93 KB) only one fits (256: 99 and
-    // 119, 512: 184 and 236, 1536 over 1000 tokens: 1876 and 2431, 4608 with 576 rows: 5586 and 6738).
+    // Rows per workgroup of the fp32 kernel, by the workgroups that are really made.  D = 64: 32 from 512 workgroups of 32
+    // rows and splits on, where reading K and V four times as often costs more than the latency that smaller workgroups
+    // hide (us with 8 and with 32 rows, first measured as 384: 67 and 81, 512: 75 and 71 or 124 and 113, 768: 174 and 129);
+    // 4 while workgroups of 8 are at most 256 (us with 4 and with 8 rows; 20: 9.8 and 11.9, 120: 12.4 and 15.1, 160: 15.0
+    // and 15.5, 240: 15.3 and 15.7, 320: 19.0 and 18.8, 480: 32.2 and 29.5); else 8.  D = 128: always 8, two workgroups per
+    // compute unit (75 KB of LDS) where of 32 rows (93 KB) only one fits (256: 99 and 119, 512: 184 and 236).
     const bool few = D == 128 || (long)B * H * plan.n_qc * plan.n_splits < 512;
-    dim3 grid(few ? ceil_div(R, 8) : plan.n_qc, plan.n_splits, B * H);
+    const bool fewest = D == 64 && few && (long)B * H * ceil_div(R, 8) * plan.n_splits <= 256;
+    dim3 grid(fewest ? ceil_div(R, 4) : few ? ceil_div(R, 8) : plan.n_qc, plan.n_splits, B * H);
     SS_REQUIRE((long)B * H <= 65535 && plan.n_splits <= 65535, SS_ERR_UNSUPPORTED, "%s: grid too large", fn);
-    auto kern = D == 128 ? msa_f32_kernel<128, 2> : few ? msa_f32_kernel<64, 2> : msa_f32_kernel<64, 8>;
+    auto kern = D == 128 ? msa_f32_kernel<128, 2> : fewest ? msa_f32_kernel<64, 1> : few ? msa_f32_kernel<64, 2> : msa_f32_kernel<64, 8>;
     hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, a);
     if (int rc = check_launch(fn)) return rc;
   } else {
