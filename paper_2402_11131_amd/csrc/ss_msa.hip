@@ -24,7 +24,7 @@ namespace ss {
 // each tile: 10 us of 40 rows' 15).  Operands leave LDS four steps at a time, two with heads of 128: the code of more of them
 // is fetched cold by every launch (eight: 11.9 -> 14.4 us).  RW = 8, 2 or 1 (see the launch).  Before and after, one layer:
 // 4 heads of 64, 128 cached tokens, 40 rows 15.0 -> 9.8 us; 8 heads of 64, 4 sequences of 500..1000 tokens, 192 rows (RW = 8)
-// 109 -> 92; 16 heads of 128, 8000 tokens, 40 rows 202 -> 150; 32 of 128 on 8, 4 sequences of 500..1000, 80 rows 331 -> 254.
+// 109 -> 92; 16 heads of 128, 8000 tokens, 40 rows 202 -> 150; 32 of 128 on 8, 4 sequences of 500..1000, 80 rows 331 -> 245.
 // Maximum over a wavefront by register moves (a lane shuffle is a trip through LDS).
 template <int ROR>
 SS_DEV float row_ror(float v) {
