@@ -744,6 +744,7 @@ __global__ __launch_bounds__(1024) void lm_tail_kernel(TailArgs t) {
       }
     }
   }
+  if (w < t.gamma && lane < K) topk[w * K + lane] = key_id(0);  // of a row with fewer candidates the ranks that are left
   __syncthreads();
   if (w < t.gamma) {  // a lane per candidate; its place is the number of better ones
     const int n = per_stream * K;

@@ -69,3 +69,31 @@ def test_tail(name):
     alone = api.ss_tree_verify(torch.from_numpy(tok).to(DEV), torch.from_numpy(parent).to(DEV), idx, md, batch_stride=R * K, node_stride=K)
     for k in ("n_accept", "last", "bonus", "path", "out_tokens"):
         assert torch.equal(alone[k], out[k]), k
+
+
+@pytest.mark.parametrize("name", ["nan_rows", "few_numbers"])
+def test_ranks_without_a_candidate(name):
+    # A row with fewer than K logits that are numbers (its hidden state is NaN, or most of W is): the ranks that are left get
+    # what the stand-alone top-K gives them, whatever a call before left behind.
+    B, T, gamma, K, d, V, dbr = 3, 16, 4, 4, 64, 300, (4, 2, 1, 1)
+    R = T * (1 + gamma)
+    g = torch.Generator().manual_seed(11)
+    hidden, W = torch.randn(B * R, d, generator=g), torch.randn(V, d, generator=g)
+    parent = synth.make_trees(5, B, T, (4, 2, 2), 3)
+    tok = synth.make_draft_tokens(6, parent, V)
+    t_dev, p_dev = torch.from_numpy(tok).to(DEV), torch.from_numpy(parent).to(DEV)
+    call = lambda h, w: api.ss_lm_head_verify_draft(h.to(DEV), w.to(DEV), K, t_dev, p_dev, gamma, 3, branching=dbr)
+    call(hidden, W)                          # leaves tokens of its own where the next call's lists go
+    if name == "nan_rows":
+        hidden.view(B, R, d)[:, T + 1::2] = float("nan")      # every other stream row
+        hidden.view(B, R, d)[2] = float("nan")                # all rows of a sequence, main rows too
+    else:
+        W[torch.arange(V) % 128 != 5] = float("nan")          # ids 5, 133 and 261: three numbers per row
+    idx, _ = api.ss_lm_head_argmax_topk(hidden.to(DEV), W.to(DEV), K)
+    ver = api.ss_tree_verify(t_dev, p_dev, idx, 3, batch_stride=R * K, node_stride=K)
+    nxt, _ = api.ss_tree_draft(idx, K, ver["last"], ver["bonus"], T, gamma, branching=dbr, batch_stride=R * K, offset=T * K)
+    assert int(nxt.max()) == np.iinfo(np.int32).max
+    out = call(hidden, W)
+    for k in ("n_accept", "last", "bonus", "path", "out_tokens"):
+        assert torch.equal(out[k], ver[k]), k
+    assert torch.equal(out["next_tok"], nxt)
