@@ -255,6 +255,18 @@ int ss_msa_plan_splits(int B, int T, int gamma, int H, int Hkv, int D, int max_s
                        const int32_t* seq_lens, const int32_t* n_nodes, int* where, int32_t* n_splits);
 
 /*
+ * The attention kernel's launch for a call of a2 with this shape (SS_BF16) and a
+ * workspace of workspace_bytes, as currently tuned:
+ *  launch [6] (HOST): query rows per wave (16 or 32: which of the two kernels) and
+ *          per workgroup, splits, workgroups, waves per workgroup, bytes of LDS per
+ *          workgroup
+ * Host-only, no GPU work.  Returns SS_OK or the error ss_msa_attention would
+ * return.
+ */
+int ss_msa_plan_launch(int B, int T, int gamma, int H, int Hkv, int D, int max_seq_len,
+                       size_t workspace_bytes, int32_t* launch);
+
+/*
  * Tuning knob for a2: number of cached tokens one workgroup scans (the KV
  * split length).  0 = choose from the problem shape (default).  Values below
  * 64 count as 64, and values are rounded up to a multiple of 32 (SS_BF16) or

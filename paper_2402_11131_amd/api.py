@@ -27,7 +27,7 @@ SS_MAX_T, SS_MAX_GAMMA, SS_MAX_K = 64, 8, 8
 
 EXPORTS = (
     "ss_version", "ss_last_error", "ss_probe_hbm_read", "ss_probe_mfma_bf16", "ss_check_tree_host", "ss_build_mask", "ss_msa_workspace_bytes",
-    "ss_msa_attention", "ss_msa_workspace_init", "ss_msa_attention_static", "ss_msa_static_scratch_bytes", "ss_msa_plan", "ss_msa_plan_splits", "ss_msa_set_split_keys", "ss_msa_set_merge_in_kernel", "ss_lm_head_workspace_bytes", "ss_lm_set_flavour", "ss_lm_set_stagger", "ss_lm_set_candidates_only", "ss_lm_head_argmax_topk", "ss_lm_head_verify_draft",
+    "ss_msa_attention", "ss_msa_workspace_init", "ss_msa_attention_static", "ss_msa_static_scratch_bytes", "ss_msa_plan", "ss_msa_plan_splits", "ss_msa_plan_launch", "ss_msa_set_split_keys", "ss_msa_set_merge_in_kernel", "ss_lm_head_workspace_bytes", "ss_lm_set_flavour", "ss_lm_set_stagger", "ss_lm_set_candidates_only", "ss_lm_head_argmax_topk", "ss_lm_head_verify_draft",
     "ss_tree_verify", "ss_tree_draft", "ss_full_tree_template_host", "ss_kv_commit", "ss_kv_alloc_pages", "ss_linear_rows", "ss_linear_rows_ws", "ss_linear_rows_workspace_bytes", "ss_linear_rows_splits", "ss_stream_insert", "ss_stream_insert_linear", "ss_stream_insert_linear_workspace_bytes", "ss_value_rotate",
     "ss_lm_head_logsumexp", "ss_transition_probs", "ss_tree_prune", "ss_live_rows", "ss_msa_attention_pruned",
     "ss_linear_rows_live", "ss_lm_head_argmax_topk_live", "ss_lm_head_verify_draft_live",
@@ -65,6 +65,7 @@ def load_library() -> ctypes.CDLL:
     lib.ss_msa_plan.argtypes = [i32] * 8 + [ctypes.POINTER(ctypes.c_int)] * 2
     lib.ss_msa_plan.restype = i32
     lib.ss_msa_plan_splits.argtypes = [i32] * 8 + [vp, vp, c.POINTER(c.c_int), vp]
+    lib.ss_msa_plan_launch.argtypes = [i32] * 7 + [sz, vp]
     lib.ss_msa_attention.argtypes = [vp, vp, vp, vp, vp, vp, i32, i32, vp, vp, i32, i32, i32, i32, i32, i32, i32,
                                      c.c_float, i32, u32, vp, vp, sz, vp]
     lib.ss_msa_workspace_init.argtypes = [vp, sz, vp]
@@ -195,6 +196,16 @@ def ss_msa_plan_splits(B, T, gamma, H, Hkv, D, max_seq_len, dtype_code, seq_lens
     _check(load_library().ss_msa_plan_splits(B, T, gamma, H, Hkv, D, max_seq_len, dtype_code, arr(*seq_lens),
                                              None if n_nodes is None else arr(*n_nodes), ctypes.byref(where), n))
     return where.value, list(n)[:B]
+
+
+def ss_msa_plan_launch(B, T, gamma, H, Hkv, D, max_seq_len, workspace_bytes: Optional[int] = None) -> dict:
+    """The bf16 attention kernel's launch for a call of this shape with a workspace of that size (default: what
+    ss_msa_workspace_bytes asks for): rows_per_wave (16 or 32: which kernel), rows, n_splits, workgroups, waves, lds."""
+    if workspace_bytes is None:
+        workspace_bytes = ss_msa_workspace_bytes(B, T, gamma, H, Hkv, D, max_seq_len, SS_BF16)
+    launch = (ctypes.c_int32 * 6)()
+    _check(load_library().ss_msa_plan_launch(B, T, gamma, H, Hkv, D, max_seq_len, workspace_bytes, launch))
+    return dict(zip(("rows_per_wave", "rows", "n_splits", "workgroups", "waves", "lds"), launch))
 
 
 def ss_msa_set_split_keys(split_keys: int) -> int:

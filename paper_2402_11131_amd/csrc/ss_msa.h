@@ -199,9 +199,18 @@ constexpr size_t kArriveRegionBytes = (size_t)8192 * kArriveTiles * sizeof(unsig
 int launch_msa_bf16(const MsaArgs& a, hipStream_t stream);
 // Query rows per workgroup chunk the MFMA path uses for F = g*R folded rows.
 int msa_bf16_rows_per_chunk(int F);
+// The launch of that kernel: workgroups, wave groups of each, ring stages per group, stages per group for more of the step's
+// own rows, waves and bytes of LDS per workgroup.
+struct MsaLaunch {
+  long wgs;
+  int groups, stages, extra, waves;
+  size_t lds;
+};
+MsaLaunch msa_bf16_launch(const MsaArgs& a);
 
 // The same with 32 query rows per wave (D = 128, more than 80 folded rows).
 constexpr int kWideSlots = 512;  // workgroups the chip holds at a time: two per compute unit
+MsaLaunch msa_bf16_wide_launch(const MsaArgs& a);
 int launch_msa_bf16_wide(const MsaArgs& a, hipStream_t stream);
 int msa_bf16_wide_rows(int F);
 

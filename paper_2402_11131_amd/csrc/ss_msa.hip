@@ -638,6 +638,31 @@ int ss_msa_plan(int B, int T, int gamma, int H, int Hkv, int D, int max_seq_len,
   return SS_OK;
 }
 
+int ss_msa_plan_launch(int B, int T, int gamma, int H, int Hkv, int D, int max_seq_len, size_t workspace_bytes, int32_t* launch) {
+  using namespace ss;
+  clear_error();
+  const char* fn = "ss_msa_plan_launch";
+  if (int rc = check_shape(fn, B, T, gamma, H, Hkv, D, SS_BF16)) return rc;
+  SS_REQUIRE(launch != nullptr, SS_ERR_INVALID_ARG, "%s: NULL launch", fn);
+  if (max_seq_len < 0) max_seq_len = 0;
+  MsaPlan plan = make_plan(B, T * (1 + gamma), H, Hkv, D, max_seq_len, SS_BF16);
+  if (plan.wide && plan.n_splits > 1 && workspace_bytes < plan.total_bytes)
+    plan = make_plan(B, T * (1 + gamma), H, Hkv, D, max_seq_len, SS_BF16, false);
+  SS_REQUIRE(plan.n_splits == 1 || workspace_bytes >= plan.total_bytes, SS_ERR_WORKSPACE, "%s: workspace of %zu bytes needed, %zu given", fn,
+             plan.total_bytes, workspace_bytes);
+  MsaArgs a = {};
+  set_plan(a, plan, B, T, gamma, H, Hkv, D, max_seq_len, SS_BF16);
+  const MsaLaunch l = plan.wide ? msa_bf16_wide_launch(a) : msa_bf16_launch(a);
+  SS_REQUIRE(l.wgs <= 0x7fffffffL, SS_ERR_UNSUPPORTED, "%s: grid too large", fn);
+  launch[0] = plan.wide ? 32 : 16;
+  launch[1] = plan.chunk_rows;
+  launch[2] = plan.n_splits;
+  launch[3] = (int32_t)l.wgs;
+  launch[4] = l.waves;
+  launch[5] = (int32_t)l.lds;
+  return SS_OK;
+}
+
 int ss_msa_plan_splits(int B, int T, int gamma, int H, int Hkv, int D, int max_seq_len, int dtype,
                        const int32_t* seq_lens, const int32_t* n_nodes, int* where, int32_t* n_splits) {
   using namespace ss;

@@ -782,25 +782,41 @@ static int stages_for(int n_groups, int wanted, size_t stage_bytes, int lpb) {
   return n < 2 ? 2 : n;
 }
 
+// Stages for the step's own rows beyond one per group (their later blocks need no trip of their own then), where they cost no
+// residency: the launch has a workgroup per compute unit at most, or as many fit one as without them.  What fits is bounded by
+// 160 KB of LDS and, for heads of 64, by six waves per SIMD (73 registers or more; heads of 128 fill the LDS alone).
+// Us per layer with a stage more wherever 144 KB of ring allow it and by this rule, heads of 64: 576 rows in nine chunks of 64
+// (12 waves, 74 KB or 98), 8 x 4096 tokens 185 and 133; 192 rows in three, 16 x 4096 75 and 62, 32 x 512 35 and 27; 525 rows in
+// eleven of 48, 16 x 4096 226 and 218.  Without any: 640 rows in five of 128 (16 waves) 110 and 106, 80 rows (10 waves) of 7 x 32
+// heads x 2048 40 and 37; one sequence of 2048 tokens, heads of 128, 22.7 and 22.1.
+MsaLaunch msa_bf16_launch(const MsaArgs& a) {
+  const int nw = a.chunk_rows / 16, lw = nw >= 4 ? 4 : nw >= 2 ? 2 : 1;
+  const size_t stage_bytes = 2 * 32 * (size_t)a.D * 2;
+  MsaLaunch l;
+  l.wgs = (long)ceil_div(a.B * a.Hkv * a.n_splits, 8) * 8 * a.n_qc;
+  l.groups = groups_for(nw, a.groups);
+  l.stages = stages_for(l.groups, a.stages, stage_bytes, 2 * (32 * a.D * 2 / 1024) / lw);
+  l.waves = nw * l.groups;
+  const size_t merge_bytes = (size_t)(l.groups - 1) * nw * (a.D / 16) * 64 * 16;
+  auto lds = [&](int extra) {
+    const size_t ring = (size_t)l.groups * (l.stages + extra) * stage_bytes;
+    return (ring > merge_bytes ? ring : merge_bytes) + 8 * sizeof(int) + (size_t)l.waves * 32 * 4;
+  };
+  auto resident = [&](int extra) { const int by_lds = (int)(160 * 1024 / lds(extra)), by_waves = 24 / l.waves; return by_lds < by_waves ? by_lds : by_waves; };
+  l.extra = 0;
+  if (l.groups > 1)
+    while (l.extra + 1 < ceil_div(ceil_div(a.R, 32), l.groups) && (size_t)l.groups * (l.stages + l.extra + 1) * stage_bytes <= 144 * 1024 &&
+           (l.wgs <= 256 || resident(l.extra + 1) >= resident(0)))
+      ++l.extra;
+  l.lds = lds(l.extra);
+  return l;
+}
+
 template <int D, int NW, bool STREAM, bool CUTS>
 static int launch_dns(const MsaArgs& a, hipStream_t stream) {
-  const int n_groups = groups_for(NW, a.groups);
-  const int G = a.B * a.Hkv * a.n_splits;
-  const long wgs = (long)ceil_div(G, 8) * 8 * a.n_qc;
-  SS_REQUIRE(wgs <= 0x7fffffffL, SS_ERR_UNSUPPORTED, "ss_msa_attention: grid too large");
-  const size_t stage_bytes = 2 * 32 * D * 2;
-  constexpr int lw = NW >= 4 ? 4 : NW >= 2 ? 2 : 1;
-  const int n_stages = stages_for(n_groups, a.stages, stage_bytes, 2 * (32 * D * 2 / 1024) / lw);
-  const size_t merge_bytes = (size_t)(n_groups - 1) * NW * (D / 16) * 64 * 16;
-  // Stages for the step's own rows beyond one per group, where a compute unit holds one workgroup anyway: their later blocks
-  // need no trip of their own then.
-  int n_extra = 0;
-  if (n_groups > 1)
-    while (n_extra + 1 < ceil_div(ceil_div(a.R, 32), n_groups) && (size_t)n_groups * (n_stages + n_extra + 1) * stage_bytes <= 144 * 1024) ++n_extra;
-  size_t lds = (size_t)n_groups * (n_stages + n_extra) * stage_bytes;
-  if (merge_bytes > lds) lds = merge_bytes;
-  lds += 8 * sizeof(int) + (size_t)n_groups * NW * 32 * 4;
-  SS_REQUIRE(lds <= 160 * 1024, SS_ERR_UNSUPPORTED, "ss_msa_attention: %zu bytes of LDS needed", lds);
+  const MsaLaunch l = msa_bf16_launch(a);
+  SS_REQUIRE(l.wgs <= 0x7fffffffL, SS_ERR_UNSUPPORTED, "ss_msa_attention: grid too large");
+  SS_REQUIRE(l.lds <= 160 * 1024, SS_ERR_UNSUPPORTED, "ss_msa_attention: %zu bytes of LDS needed", l.lds);
   auto kern = msa_bf16_kernel<D, NW, STREAM, CUTS>;
   static std::once_flag attr_once;
   static hipError_t attr_err = hipSuccess;
@@ -810,10 +826,10 @@ static int launch_dns(const MsaArgs& a, hipStream_t stream) {
   if (attr_err != hipSuccess)
     SS_FAIL(SS_ERR_HIP, "ss_msa_attention: hipFuncSetAttribute: %s", hipGetErrorString(attr_err));
   MsaArgs launch = a;
-  launch.n_groups = n_groups;
-  launch.n_stages = n_stages;
-  launch.n_extra = n_extra;
-  hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(64 * NW * n_groups), lds, stream, launch);
+  launch.n_groups = l.groups;
+  launch.n_stages = l.stages;
+  launch.n_extra = l.extra;
+  hipLaunchKernelGGL(kern, dim3((unsigned)l.wgs), dim3(64 * l.waves), l.lds, stream, launch);
   return check_launch("ss_msa_attention");
 }
 

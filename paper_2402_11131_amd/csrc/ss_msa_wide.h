@@ -513,21 +513,30 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 // Folded query rows one workgroup takes where a KV head has more than 80: 128 or 96, whichever pads less.
 int msa_bf16_wide_rows(int F) { return ceil_div(F, 96) * 96 < ceil_div(F, 128) * 128 ? 96 : 128; }
 
+// One ring of as many stages as there are waves, whose output tiles take its place at the end.
+MsaLaunch msa_bf16_wide_launch(const MsaArgs& a) {
+  MsaLaunch l;
+  l.wgs = (long)ceil_div(a.B * a.Hkv * a.n_splits, 8) * 8 * a.n_qc;
+  l.groups = 1;
+  l.waves = l.stages = a.chunk_rows / 32;
+  l.extra = 0;
+  l.lds = (size_t)l.stages * 128 * a.D + 8 * sizeof(int);
+  return l;
+}
+
 template <int D, int NW, bool STREAM, bool CUTS>
 static int launch_wide_dns(const MsaArgs& a, hipStream_t stream) {
-  const int G = a.B * a.Hkv * a.n_splits;
-  const long wgs = (long)ceil_div(G, 8) * 8 * a.n_qc;
-  SS_REQUIRE(wgs <= 0x7fffffffL, SS_ERR_UNSUPPORTED, "ss_msa_attention: grid too large");
-  constexpr size_t lds = (size_t)NW * 4 * 32 * D + 8 * sizeof(int);
+  const MsaLaunch l = msa_bf16_wide_launch(a);
+  SS_REQUIRE(l.wgs <= 0x7fffffffL, SS_ERR_UNSUPPORTED, "ss_msa_attention: grid too large");
   auto kern = msa_bf16_wide_kernel<D, NW, STREAM, CUTS>;
   static std::once_flag attr_once;
   static hipError_t attr_err = hipSuccess;
   std::call_once(attr_once, [&]() {
-    attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)l.lds);
   });
   if (attr_err != hipSuccess)
     SS_FAIL(SS_ERR_HIP, "ss_msa_attention: hipFuncSetAttribute: %s", hipGetErrorString(attr_err));
-  hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(64 * NW), lds, stream, a);
+  hipLaunchKernelGGL(kern, dim3((unsigned)l.wgs), dim3(64 * NW), l.lds, stream, a);
   return check_launch("ss_msa_attention");
 }
 

@@ -175,3 +175,18 @@ def test_shapes_of_the_uneven_batches_are_of_the_kind_they_stand_for():
         assert where == (2 if name in t.CUT else 0), name
     plans = [api.ss_msa_plan(*t._shape(name)) for name in t.CUT]
     assert (2, 1) in plans and any(n > 2 for n, _ in plans)      # merged in the attention kernel, and by the merge kernel
+
+
+def test_stages_for_the_own_rows_cost_no_resident_workgroup():
+    # heads of 64 in several row chunks of nine to twelve waves: two workgroups fit a compute unit's 160 KB, whatever the tree
+    # (more of the step's own rows get stages only where no workgroup goes for them)
+    for T, gamma, H, rows, waves in ((21, 4, 40, 48, 9), (64, 2, 8, 64, 12), (64, 8, 8, 64, 12)):
+        p = api.ss_msa_plan_launch(16, T, gamma, H, 8, 64, 4096)
+        assert (p["rows_per_wave"], p["rows"], p["waves"]) == (16, rows, waves) and p["workgroups"] > 256
+        assert 2 * p["lds"] <= 160 * 1024, p
+    # where one workgroup fits anyway (sixteen waves: 3 rounds of own blocks; heads of 128) or the launch has one per compute
+    # unit at most, the later rounds have their stages: (groups, stages and more stages per group) of 8 or 16 KB
+    for shape, most_wgs, stages in (((16, 32, 4, 32, 8, 64, 4096), 1280, 2 * (3 + 2) * 8192), ((1, 21, 4, 40, 8, 64, 512), 256, 3 * (3 + 1) * 8192),
+                                    ((1, 16, 4, 32, 32, 128, 2048), 256, 2 * (3 + 1) * 16384)):
+        p = api.ss_msa_plan_launch(*shape)
+        assert p["workgroups"] <= most_wgs and stages <= p["lds"] < stages + 4096, (shape, p)
