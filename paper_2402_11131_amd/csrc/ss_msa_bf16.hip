@@ -91,7 +91,10 @@ constexpr int kMaxStages = 10;  // ring stages per wave group: at most kMaxStage
 // STREAM: the cache is loaded with the streaming hint.  Right when a (sequence, KV head, split) has one row
 // chunk, so that every byte of the cache is wanted by exactly one workgroup; with several row chunks (long GQA
 // trees) the chunks share K/V through the L2 and the hint undoes that (measured: +25 % time).
-template <int D, int NW, bool STREAM, bool CUTS>
+// FEW: three or four splits of few rows are merged here (merges_few_rows).  An instance of its own: it holds the partial rows
+// of four splits at once (D = 128: 284 registers, one wave per SIMD, and 212, two, without; D = 64: 156 and 152), which no other
+// call of up to 16 rows should pay for.
+template <int D, int NW, bool STREAM, bool CUTS, bool FEW = false>
 __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves / NW : kMaxGroups)) void msa_bf16_kernel(MsaArgs args) {
   const int n_groups = args.n_groups, n_stages = args.n_stages;
   constexpr int KS = D / 32, DT = D / 16;
@@ -704,28 +707,21 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
       M = m_new;
     }
   };
-  bool folded = false;
-  if constexpr (NW == 1) {
-    if (n_active > 2) {  // four splits at a time; past the end the last one again, this split's own from registers
-      folded = true;
-      for (int s0 = 0; s0 < n_active; s0 += 4) {
-        float l4[4];
-        floatx4 o4[4][DT];
+  if (FEW && n_active > 2) {  // all (four at most) at once; past the end the last one again, this split's own from registers
+    float l4[4];
+    floatx4 o4[4][DT];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const size_t at = part_row(min(s0 + i, n_active - 1));
-          ld_row_device<DT>(a.part_lse + at, a.part_o + at * D + 4 * lg, l4[i], o4[i]);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (s0 + i < n_active) {
-            if (s0 + i == s) fold(my_lse, O);
-            else fold(l4[i], o4[i]);
-          }
-      }
+    for (int i = 0; i < 4; ++i) {
+      const size_t at = part_row(min(i, n_active - 1));
+      ld_row_device<DT>(a.part_lse + at, a.part_o + at * D + 4 * lg, l4[i], o4[i]);
     }
-  }
-  if (!folded) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (i < n_active) {
+        if (i == s) fold(my_lse, O);
+        else fold(l4[i], o4[i]);
+      }
+  } else {
     if (n_active == 2 && s_other == 0) fold(l_other, o_other);
     fold(my_lse, O);
     if (n_active == 2 && s_other == 1) fold(l_other, o_other);
@@ -812,12 +808,12 @@ MsaLaunch msa_bf16_launch(const MsaArgs& a) {
   return l;
 }
 
-template <int D, int NW, bool STREAM, bool CUTS>
+template <int D, int NW, bool STREAM, bool CUTS, bool FEW = false>
 static int launch_dns(const MsaArgs& a, hipStream_t stream) {
   const MsaLaunch l = msa_bf16_launch(a);
   SS_REQUIRE(l.wgs <= 0x7fffffffL, SS_ERR_UNSUPPORTED, "ss_msa_attention: grid too large");
   SS_REQUIRE(l.lds <= 160 * 1024, SS_ERR_UNSUPPORTED, "ss_msa_attention: %zu bytes of LDS needed", l.lds);
-  auto kern = msa_bf16_kernel<D, NW, STREAM, CUTS>;
+  auto kern = msa_bf16_kernel<D, NW, STREAM, CUTS, FEW>;
   static std::once_flag attr_once;
   static hipError_t attr_err = hipSuccess;
   std::call_once(attr_once, [&]() {
@@ -838,6 +834,9 @@ template <int D, int NW>
 static int launch_dn(const MsaArgs& a, hipStream_t stream) {
   if constexpr (NW > 2) {
     if (a.n_qc > 1) return a.adaptive ? launch_dns<D, NW, false, true>(a, stream) : launch_dns<D, NW, false, false>(a, stream);
+  }
+  if constexpr (NW == 1) {
+    if (a.arrive != nullptr && a.n_splits > 2) return launch_dns<D, NW, true, false, true>(a, stream);
   }
   return launch_dns<D, NW, true, false>(a, stream);
 }
