@@ -338,6 +338,23 @@ static bool wide_fits(int B, int R, int H, int Hkv, int D, int len) {
 // heads of 128, 5 rows 16.2 and 16.6, 38.7 and 40.0; 15 rows 22.3 and 23.9; eight splits 16.3 and 17.8, fourteen 17.5 and 33.5.
 static bool merges_few_rows(int F, int D, int n_splits) { return F * D <= 512 && n_splits <= 4; }
 
+// What a launch of 256 and more items with several row chunks costs in n splits, in blocks: rounds of the 32 compute units of
+// an XCD, which gets whole (sequence, KV head, split) groups, times the blocks of a split and 8 for its start, and what the
+// partial results cost (a fiftieth per workgroup, as in cut_cost, and the merge kernel).  With 32 rows per wave it says where
+// whole rounds of 256 workgroups want too many splits: they are kept if that costs at most 3 % more (of batches that are cut
+// on the device more splits are finer pieces).  Measured on 90 shapes (2 to 16 sequences of 2300 to 32000 tokens, 450 to 2700
+// rows per KV head), against the best of 1 to 8 splits: 3 % lost on average, 9 to 12 % by whole rounds alone, with which
+// shorter sequences were slower than with 16 rows per wave (us: 13 x 4416 tokens, 1296 rows, 4 splits 548, unsplit 375;
+// 10 x 5248, 480 rows, 5 splits 187, unsplit 146, with 16 rows 151; 16 x 2368, 1410 rows, 2 splits 419, unsplit 314, 377).
+// Where that kernel's chunks are 80 rows (15 waves) the two costs compare as the times do, and it keeps what it does as well in
+// one split (a cost at most 7 % higher): 9 x 4288 tokens, 780 rows, 3 rounds either way, 188 and with 32 rows 207; 12 x 5312,
+// 2072 rows, 5 rounds, 389 and 408; 8 x 4288 of which a twelfth to a quarter is used, 960 rows, 72 and 92.  (Its chunks of 48
+// or 64 rows take 1.2 to 2.3 times as long, those of 128 1.1 to 1.5.)
+static double launch_cost(int groups, int chunks, int len, int n) {
+  const long per_xcd = ((long)groups * n + 7) / 8 * chunks;
+  return (double)((per_xcd + 31) / 32) * (ceil_div(ceil_div(len, 32), n) + 8) + (n > 1 ? 0.16 * (double)per_xcd + 16.0 : 0.0);
+}
+
 static MsaPlan make_plan(int B, int R, int H, int Hkv, int D, int max_len, int dtype, bool allow_wide = true) {
   MsaPlan p;
   const int g = H / Hkv;
@@ -383,8 +400,6 @@ static MsaPlan make_plan(int B, int R, int H, int Hkv, int D, int max_len, int d
       int best_n = 1;
       double best_waste = 0.0;
       for (int cand = 1; cand <= 8 && (cand == 1 || len / cand >= 1024); ++cand) {
-        // (32 rows per wave, two workgroups per compute unit, the same: 1, 2, 3, 4, 5, 8 splits 882, 896, 773, 782, 813,
-        // 793 us)
         const double wgs = (double)base * cand, waste = ceil(wgs / 256.0) * 256.0 / wgs;
         if (cand == 1 || waste < best_waste - 1e-9) {
           best_n = cand;
@@ -392,6 +407,15 @@ static MsaPlan make_plan(int B, int R, int H, int Hkv, int D, int max_len, int d
         }
       }
       n = best_n;
+      if (p.wide) {
+        for (int cand = best_n - 1; cand >= 1; --cand)
+          if (launch_cost(B * Hkv, p.n_qc, len, cand) <= launch_cost(B * Hkv, p.n_qc, len, n)) n = cand;
+        if (launch_cost(B * Hkv, p.n_qc, len, best_n) <= 1.03 * launch_cost(B * Hkv, p.n_qc, len, n)) n = best_n;
+        if (msa_bf16_rows_per_chunk(g * R) == 80) {
+          const MsaPlan q = make_plan(B, R, H, Hkv, D, max_len, dtype, false);
+          if (q.n_splits == 1 && launch_cost(B * Hkv, q.n_qc, len, 1) <= 1.07 * launch_cost(B * Hkv, p.n_qc, len, n)) return q;
+        }
+      }
     }
     split_keys = ceil_div(ceil_div(len, unit), n) * unit;
   }

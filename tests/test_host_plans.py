@@ -190,3 +190,19 @@ def test_stages_for_the_own_rows_cost_no_resident_workgroup():
                                     ((1, 16, 4, 32, 32, 128, 2048), 256, 2 * (3 + 1) * 16384)):
         p = api.ss_msa_plan_launch(*shape)
         assert p["workgroups"] <= most_wgs and stages <= p["lds"] < stages + 4096, (shape, p)
+
+
+def test_splits_of_long_trees_by_their_cost():
+    # (B, T, gamma, H, Hkv) -> query rows per wave and splits of launches of 256 and more items with 32 query rows per wave
+    plan = lambda B, T, gamma, H, Hkv, cap: tuple(api.ss_msa_plan_launch(B, T, gamma, H, Hkv, 128, cap)[k] for k in ("rows_per_wave", "n_splits"))
+    assert plan(8, 32, 4, 32, 8, 32768) == (32, 4)      # 5 whole rounds
+    assert plan(8, 32, 4, 32, 8, 8192) == (32, 4)
+    assert plan(13, 27, 5, 64, 8, 4416) == (32, 1)      # short sequences: partial results cost more than a round's end
+    assert plan(16, 47, 5, 40, 8, 2368) == (32, 1)
+    assert plan(6, 32, 4, 40, 8, 8192) == (32, 1)
+    assert plan(9, 29, 4, 32, 4, 21056)[1] > 1          # 468 items, but 5 groups of 13 on an XCD are one more than it holds
+    assert plan(7, 57, 5, 28, 4, 2240) == (32, 1)       # never more than whole rounds want
+    for shape in ((9, 26, 4, 48, 8, 4288), (12, 37, 6, 32, 4, 5312), (10, 24, 4, 32, 8, 5248), (8, 20, 5, 64, 8, 4096), (8, 48, 4, 32, 8, 4288),
+                  (2, 59, 6, 48, 8, 9600)):
+        assert plan(*shape) == (16, 1), shape           # as many rounds of 80 rows as of 96
+    assert plan(12, 37, 6, 32, 4, 12288)[0] == 32       # the same rows, longer: that kernel would cut them in eight
