@@ -179,6 +179,12 @@ int ss_build_mask(const int32_t* parent, int B, int T, int gamma, uint32_t flags
  * that may run at the same time (different streams, graphs replayed on
  * different streams) need a workspace each; calls that follow each
  * other on one stream can share one.  The library keeps nothing between calls.
+ * Long trees (more than 80 query rows per KV head, D = 128, SS_BF16) have two
+ * kernels, of which one may split further and need more workspace: a workspace
+ * that is too small for the chosen one but large enough for the other is taken,
+ * the other kernel then runs, and the result differs from that with the full
+ * workspace as far as rounding goes (ss_msa_plan_launch tells which runs; the
+ * other queries suppose a workspace of ss_msa_workspace_bytes).
  * A sequence's result may depend on the other sequences' lengths and kept nodes
  * as far as the order of floating-point sums goes: they share in the choice of
  * where its cached prefix is split (see ss_msa_plan_splits).
@@ -199,20 +205,22 @@ int ss_msa_attention(const void* q, const void* k_new, const void* v_new, const 
  * a2 for callers that cannot allocate device memory (code under HIP graph
  * capture that owns no buffers, tight serving loops, harnesses that forbid
  * hipMalloc): ss_msa_attention without the workspace arguments.  The partial
- * results and arrival counters live in an array of
- * ss_msa_static_scratch_bytes() = 32 MiB that is part of the library's device
- * code; every GPU the library is used on holds its own copy until the process
- * ends.  The call allocates and frees nothing.  The first call on a device
+ * results and arrival counters live in an array (64 MiB) that is part of the
+ * library's device code; every GPU the library is used on holds its own copy
+ * until the process ends.  The call allocates and frees nothing.  The first call on a device
  * looks the array's address up (the device that is current in the calling
  * thread must be the one `stream` belongs to).  The counters are cleared by a
  * small kernel at the start of every call; the rest of the array keeps what the
  * last call left there.  All calls on one GPU share the array: calls that
  * overlap in time (different streams, graph replays on different streams) RACE
  * and give wrong results; enqueue them on one stream or use ss_msa_attention.
- * Results are those of ss_msa_attention, bit for bit.
+ * Results are those of ss_msa_attention with a workspace of
+ * ss_msa_workspace_bytes(...), bit for bit.
  * Errors: those of ss_msa_attention; SS_ERR_UNSUPPORTED if the shape's partial
- * results and counters need more than the array holds (the message tells how
- * much; a workspace is some 256 KB larger), nothing is enqueued then.
+ * results and counters need more than ss_msa_static_scratch_bytes() = 32 MiB
+ * (the message tells how much; a workspace is some 256 KB larger; where a2 has
+ * two kernels for a shape, what the one with fewer splits needs counts), nothing
+ * is enqueued then.
  */
 size_t ss_msa_static_scratch_bytes(void);
 int ss_msa_attention_static(const void* q, const void* k_new, const void* v_new,

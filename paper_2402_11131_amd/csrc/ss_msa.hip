@@ -283,6 +283,10 @@ __global__ __launch_bounds__(256) void msa_combine_kernel(MsaArgs a) {
 static std::atomic<int> g_split_keys_override{0};
 static std::atomic<int> g_merge_in_kernel{1};
 
+// Scratch memory of ss_msa_attention_static: it takes a shape whose partial results need at most the first with one of the
+// shape's two plans (MsaPlan.scratch_bytes); with its own plan they find room in the second.
+constexpr size_t kStaticScratchBytes = (size_t)32 << 20, kStaticArrayBytes = (size_t)64 << 20;
+
 struct MsaPlan {
   int split_keys, split0_keys, n_splits, n_qc, groups, stages;
   int adaptive, new_units, min_units, chunk_rows;
@@ -467,6 +471,23 @@ static MsaPlan make_plan(int B, int R, int H, int Hkv, int D, int max_len, int d
     p.total_bytes += p.table_at + (p.adaptive ? kAdaptiveMaxB * sizeof(int2) : 0);
     p.scratch_bytes += p.table_at - kArriveRegionBytes + (p.n_splits == 2 ? counters : 0);
   }
+  // ss_msa_attention_static and ss_msa_attention have one plan.  This kernel's splits may be twice the other's, so a shape
+  // counts there as what the smaller needs, and the other kernel takes it, in both calls, if this one's do not fit the array.
+  // (It taking all shapes whose 32 MiB only it keeps to cost 5 to 12 %: 4 x 9600 tokens, 512 rows 110 and 124 us.)
+  if (p.wide && p.scratch_bytes > kStaticScratchBytes) {
+    const MsaPlan q = make_plan(B, R, H, Hkv, D, max_len, dtype, false);
+    if (q.scratch_bytes <= kStaticScratchBytes) {
+      if (p.scratch_bytes > kStaticArrayBytes) return q;
+      p.scratch_bytes = q.scratch_bytes;
+    }
+  }
+  return p;
+}
+
+// The plan of a call with a workspace of that size: one that only the other kernel's splits fit stays good.
+static MsaPlan plan_for(int B, int R, int H, int Hkv, int D, int max_len, int dtype, size_t workspace_bytes) {
+  const MsaPlan p = make_plan(B, R, H, Hkv, D, max_len, dtype);
+  if (p.wide && p.n_splits > 1 && workspace_bytes < p.total_bytes) return make_plan(B, R, H, Hkv, D, max_len, dtype, false);
   return p;
 }
 
@@ -521,12 +542,11 @@ static int zero_bytes(unsigned char* p, size_t bytes, hipStream_t st, const char
 }
 
 // Scratch memory of ss_msa_attention_static: the per-split partial results and the arrival counters of a
-// call, for callers that cannot provide a workspace.  Every GPU the library runs on holds its own copy of
+// call, for callers that cannot provide a workspace: the counters' region, kStaticArrayBytes of partial rows and
+// the table of cuts.  Every GPU the library runs on holds its own copy of
 // the array; host code reaches it only through the address hipGetSymbolAddress reports for the device that
 // is current, looked up once per device.
-constexpr size_t kStaticScratchBytes = (size_t)32 << 20;
-// ... of partial rows, the counters' region in front of them and the table of cuts behind
-static __device__ __align__(256) unsigned char g_msa_scratch[kArriveRegionBytes + kStaticScratchBytes + kAdaptiveMaxB * sizeof(int2)];
+static __device__ __align__(256) unsigned char g_msa_scratch[kArriveRegionBytes + kStaticArrayBytes + kAdaptiveMaxB * sizeof(int2)];
 constexpr int kMaxDevices = 64;
 static std::mutex g_scratch_mutex;
 static void* g_scratch_ptr[kMaxDevices];  // guarded by g_scratch_mutex
@@ -577,10 +597,8 @@ static int msa_run(const char* fn, const void* q, const void* k_new, const void*
 
   const int R = T * (1 + gamma);
   const int max_len = max_pages_per_seq * page_size;
-  MsaPlan plan = make_plan(B, R, H, Hkv, D, max_len, dtype);
-  // A workspace that only the other kernel's splits fit stays good.
-  if (plan.wide && plan.n_splits > 1 && (workspace == nullptr || workspace_bytes < (library_scratch ? plan.scratch_bytes : plan.total_bytes)))
-    plan = make_plan(B, R, H, Hkv, D, max_len, dtype, false);
+  const MsaPlan plan = library_scratch ? make_plan(B, R, H, Hkv, D, max_len, dtype)
+                                       : plan_for(B, R, H, Hkv, D, max_len, dtype, workspace == nullptr ? 0 : workspace_bytes);
   if (library_scratch) {
     SS_REQUIRE(plan.scratch_bytes <= workspace_bytes, SS_ERR_UNSUPPORTED,
                "%s: this shape needs %zu bytes of scratch memory, the library's array holds %zu; use "
@@ -669,9 +687,7 @@ int ss_msa_plan_launch(int B, int T, int gamma, int H, int Hkv, int D, int max_s
   if (int rc = check_shape(fn, B, T, gamma, H, Hkv, D, SS_BF16)) return rc;
   SS_REQUIRE(launch != nullptr, SS_ERR_INVALID_ARG, "%s: NULL launch", fn);
   if (max_seq_len < 0) max_seq_len = 0;
-  MsaPlan plan = make_plan(B, T * (1 + gamma), H, Hkv, D, max_seq_len, SS_BF16);
-  if (plan.wide && plan.n_splits > 1 && workspace_bytes < plan.total_bytes)
-    plan = make_plan(B, T * (1 + gamma), H, Hkv, D, max_seq_len, SS_BF16, false);
+  const MsaPlan plan = plan_for(B, T * (1 + gamma), H, Hkv, D, max_seq_len, SS_BF16, workspace_bytes);
   SS_REQUIRE(plan.n_splits == 1 || workspace_bytes >= plan.total_bytes, SS_ERR_WORKSPACE, "%s: workspace of %zu bytes needed, %zu given", fn,
              plan.total_bytes, workspace_bytes);
   MsaArgs a = {};

@@ -147,3 +147,26 @@ def test_which_calls_take_it():
     assert plan(4, 32, 4, 8, 128, 4096) == (2, 1)      # 40: 16 rows per wave, two splits merged in the kernel
     assert plan(4, 32, 4, 8, 64, 8192) == (2, 1)       # heads of 64
     assert plan(4, 16, 4, 8, 128, 16384) == (2, 1)     # 320 rows pad to 384
+
+
+def test_the_call_without_a_workspace_has_the_same_plan():
+    # four splits of 9600 tokens: 32.25 MiB of partial results, and 16.1 MiB with 16 rows per wave
+    B, T, gamma, H, Hkv, cap = 4, 32, 3, 32, 8, 9600
+    p = api.ss_msa_plan_launch(B, T, gamma, H, Hkv, 128, cap)
+    need = api.ss_msa_workspace_bytes(B, T, gamma, H, Hkv, 128, cap, api.SS_BF16)
+    limit = api.ss_msa_static_scratch_bytes()
+    assert (p["rows_per_wave"], p["n_splits"]) == (32, 4) and need > limit + 262144
+    less = api.ss_msa_plan_launch(B, T, gamma, H, Hkv, 128, cap, limit)
+    assert (less["rows_per_wave"], less["n_splits"]) == (16, 2)
+    cfg = synth.scaled(synth.CONFIGS["c2"], B=B, H=H, Hkv=Hkv, D=128, page=64, T=T, gamma=gamma, branching=(8, 8, 4), max_depth=3,
+                       L_min=300, L_max=700)
+    inp = synth.make_msa_inputs(cfg, 5)
+    table = torch.zeros(B, cap // 64, dtype=torch.int32)
+    table[:, :inp["block_table"].shape[1]] = inp["block_table"]
+    inp["block_table"] = table
+    want = _run(inp, cfg)
+    d = {k: (v.to(DEV) if isinstance(v, torch.Tensor) else v) for k, v in inp.items()}
+    got = api.ss_msa_attention_static(d["q"], d["k_new"], d["v_new"], d["k_cache"], d["v_cache"], d["block_table"], d["seq_lens"],
+                                      d["parent"], gamma, d["scale"], out=torch.full_like(d["q"], 3.0))
+    assert torch.equal(got, want)
+    _check(got, inp, cfg)
