@@ -116,9 +116,15 @@ def _check(rc: int):
         raise SSError(rc, load_library().ss_last_error().decode())
 
 
+# The current stream's handle: a Stream object made for each call and asked for its handle costs 1.5 us.  The two functions
+# that give the handle itself are torch's own, without a promise: where one is missing the Stream object it is.
+_raw_stream, _device = (getattr(torch._C, n, None) for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+
+
 def _stream() -> int:
-    # the handle itself: a Stream object made for each call and asked for its handle costs 1.5 us
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _raw_stream is None or _device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device())
 
 
 def _dev(t: torch.Tensor, dtype, name: str) -> int:

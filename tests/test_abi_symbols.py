@@ -154,3 +154,12 @@ def test_missing_library_fails_loudly(monkeypatch):
     monkeypatch.setattr(api, "LIB_PATH", "/nonexistent/libss.so")
     with pytest.raises(RuntimeError, match="not built"):
         api.load_library()
+
+
+def test_stream_handle_without_the_private_functions(monkeypatch):
+    stream = type("Stream", (), {"cuda_stream": 4711})
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: stream)
+    for name in ("_raw_stream", "_device"):
+        with monkeypatch.context() as m:
+            m.setattr(api, name, None)
+            assert api._stream() == 4711
