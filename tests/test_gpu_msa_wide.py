@@ -36,10 +36,17 @@ def _inputs(name):
     return cfg, inp
 
 
-def _run(inp, cfg, split=0, **kw):
+def _rows_per_wave(cfg, cap, workspace_bytes=None):
+    return api.ss_msa_plan_launch(cfg.B, cfg.T, cfg.gamma, cfg.H, cfg.Hkv, cfg.D, cap, workspace_bytes)["rows_per_wave"]
+
+
+def _run(inp, cfg, split=0, rows_per_wave=32, **kw):
+    """The call, which has to take the kernel with that many query rows per wave."""
     d = {k: (v.to(DEV) if isinstance(v, torch.Tensor) else v) for k, v in inp.items()}
+    ws = kw.get("workspace")
     prev = api.ss_msa_set_split_keys(split)
     try:
+        assert _rows_per_wave(cfg, d["block_table"].shape[1] * cfg.page, None if ws is None else ws.numel()) == rows_per_wave
         got = api.ss_msa_attention(d["q"], d["k_new"], d["v_new"], d["k_cache"], d["v_cache"], d["block_table"], d["seq_lens"],
                                    d["parent"], cfg.gamma, d["scale"], out=torch.full_like(d["q"], 3.0), **kw)
     finally:
@@ -65,12 +72,6 @@ def _check(got, inp, cfg, flags=0, nodes=None):
         g, w = to_np_f32(got[b])[keep[b]], want[b][keep[b]]
         assert np.isfinite(g).all()
         assert rel_err(g, w) <= 2e-2 or (int(inp["seq_lens"][b]) < 64 and np.abs(g - w).max() <= few), (b, rel_err(g, w))
-
-
-def _needs(cfg, cap):
-    """Workspace of the call, and what it needs with 16 rows per wave (a table just below the line has that kernel's plan)."""
-    need = lambda n: api.ss_msa_workspace_bytes(cfg.B, cfg.T, cfg.gamma, cfg.H, cfg.Hkv, cfg.D, n, api.SS_BF16)
-    return need(cap), max(need(cap // 4), 1)
 
 
 @pytest.mark.parametrize("pruned", [False, True])
@@ -122,26 +123,34 @@ def test_memory_past_the_end_may_hold_nan():
 def test_a_workspace_for_the_other_kernel_is_taken_as_before(name):
     # the call falls back to 16 rows per wave where only that kernel's splits fit; both round bf16 probabilities and outputs
     cfg, inp = _inputs(name)
-    lib, cap = api.load_library(), CASES[name][6]
-    d = {k: (v.to(DEV) if isinstance(v, torch.Tensor) else v) for k, v in inp.items()}
-    shape = (cfg.B, cfg.T, cfg.gamma, cfg.H, cfg.Hkv, cfg.D)
-    full, few = _needs(cfg, cap)
-    want = _run(inp, cfg).float()
-    refused = 0
-    for ws_bytes in (full, full - 1, few):
-        ws = torch.zeros(ws_bytes, dtype=torch.uint8, device=DEV)
+    full = api.ss_msa_workspace_bytes(cfg.B, cfg.T, cfg.gamma, cfg.H, cfg.Hkv, cfg.D, CASES[name][6], api.SS_BF16)
+    want = _run(inp, cfg)
+    zeros = lambda n: torch.zeros(n, dtype=torch.uint8, device=DEV)
+    assert torch.equal(_run(inp, cfg, workspace=zeros(full)), want)
+    got = _run(inp, cfg, workspace=zeros(full - 1), rows_per_wave=16)
+    assert not torch.equal(got, want)
+    assert (got.float() - want.float()).norm() <= 2.0 ** -7 * want.float().norm()
+    _check(got, inp, cfg)
+    few = full - 1                      # the least that the other kernel's splits fit, and a byte less
+    lo = 0
+    while few - lo > 1:
+        mid = (few + lo) // 2
         try:
-            got = _run(inp, cfg, workspace=ws).float()
-        except api.SSError as e:
-            assert e.code == 4
-            refused += 1
-            continue
-        assert (got - want).norm() <= 2.0 ** -7 * want.norm()
-    assert refused <= 1
+            _rows_per_wave(cfg, CASES[name][6], mid)
+            few = mid
+        except api.SSError:
+            lo = mid
+    assert torch.equal(_run(inp, cfg, workspace=zeros(few), rows_per_wave=16), got)
+    with pytest.raises(api.SSError) as e:
+        api.ss_msa_plan_launch(cfg.B, cfg.T, cfg.gamma, cfg.H, cfg.Hkv, cfg.D, CASES[name][6], few - 1)
+    assert e.value.code == 4
 
 
 def test_which_calls_take_it():
-    # seen from the plan: two workgroups per compute unit make more splits of a batch that does not fill them
+    # two workgroups per compute unit make more splits of a batch that does not fill them
+    rows = lambda B, T, g, Hkv, D, cap: api.ss_msa_plan_launch(B, T, 4, Hkv * g, Hkv, D, cap)["rows_per_wave"]
+    assert rows(4, 32, 4, 8, 128, 8192) == 32 and rows(4, 32, 4, 8, 128, 4096) == 16
+    assert rows(4, 32, 4, 8, 64, 8192) == 16 and rows(4, 16, 4, 8, 128, 16384) == 16
     plan = lambda B, T, g, Hkv, D, cap: api.ss_msa_plan(B, T, 4, Hkv * g, Hkv, D, cap, api.SS_BF16)
     assert plan(4, 32, 4, 8, 128, 8192) == (3, 2)      # 640 rows, 80 blocks per workgroup in flight
     assert plan(4, 32, 4, 8, 128, 4096) == (2, 1)      # 40: 16 rows per wave, two splits merged in the kernel
