@@ -143,14 +143,18 @@ class MsaWorkload:
         b_msa, f_msa = msa_bytes(cfg, self.seq_lens), msa_flops(cfg, self.seq_lens)
         gbps = b_msa / (us_kernel * 1e-6) / 1e9
         tflops = f_msa / (us_kernel * 1e-6) / 1e12
+        name = "msa_f32_kernel"
+        if cfg.dtype == "bf16":
+            launch = api.ss_msa_plan_launch(cfg.B, cfg.T, cfg.gamma, cfg.H, cfg.Hkv, cfg.D, self.max_len)
+            name = "msa_bf16_wide_kernel" if launch["rows_per_wave"] == 32 else "msa_bf16_kernel"
         # Which roofline binds the kernel on this workload: the matrix cores if its FLOP per byte exceed the
         # machine's ridge (long GQA trees: c5), HBM otherwise.  Both figures are reported either way.
         if f_msa / b_msa > MFMA_BF16_PEAK_TFLOPS * 1e12 / (HBM_PEAK_GBPS * 1e9):
-            roof = {"kernel": "msa_bf16_kernel", "bound": "mfma", "achieved": round(tflops, 1), "peak": MFMA_BF16_PEAK_TFLOPS,
+            roof = {"kernel": name, "bound": "mfma", "achieved": round(tflops, 1), "peak": MFMA_BF16_PEAK_TFLOPS,
                     "unit": "TFLOP/s", "frac": round(tflops / MFMA_BF16_PEAK_TFLOPS, 4),
                     "traffic": msa_traffic_bytes(workload_name), "algorithmic_flops": f_msa, "hbm_gbps": round(gbps, 1)}
         else:
-            roof = {"kernel": "msa_bf16_kernel", "bound": "hbm", "achieved": round(gbps, 1), "peak": HBM_PEAK_GBPS,
+            roof = {"kernel": name, "bound": "hbm", "achieved": round(gbps, 1), "peak": HBM_PEAK_GBPS,
                     "unit": "GB/s", "frac": round(gbps / HBM_PEAK_GBPS, 4), "traffic": msa_traffic_bytes(workload_name),
                     "algorithmic_bytes": b_msa, "mfma_tflops": round(tflops, 1)}
         roof["kernel_us"] = round(us_kernel, 2)

@@ -169,8 +169,8 @@ int ss_build_mask(const int32_t* parent, int B, int T, int gamma, uint32_t flags
  * the dot products (1/sqrt(D) in the paper's MHA).
  * workspace: device scratch of at least ss_msa_workspace_bytes(...) bytes with
  * max_seq_len = max_pages_per_seq*page_size.  It holds the per-split partial
- * results and, when two splits are merged inside the attention kernel (see
- * ss_msa_set_merge_in_kernel), their arrival counters, which have a region of
+ * results and, when the splits are merged inside the attention kernel (two, or a
+ * few of few rows: see ss_msa_set_merge_in_kernel), their arrival counters, which have a region of
  * their own in front, the same for all shapes.  The counters must be ZERO when a
  * call is enqueued and every call leaves them zero: fill a new workspace with
  * zeros once (ss_msa_workspace_init, or any memset) and it can be used for any
@@ -207,9 +207,9 @@ int ss_msa_attention(const void* q, const void* k_new, const void* v_new, const 
  * hipMalloc): ss_msa_attention without the workspace arguments.  The partial
  * results and arrival counters live in an array (64 MiB) that is part of the
  * library's device code; every GPU the library is used on holds its own copy
- * until the process ends.  The call allocates and frees nothing.  The first call on a device
- * looks the array's address up (the device that is current in the calling
- * thread must be the one `stream` belongs to).  The counters are cleared by a
+ * until the process ends.  The call allocates and frees nothing.  The first call
+ * on a device looks the array's address up (the device that is current in the
+ * calling thread must be the one `stream` belongs to).  The counters are cleared by a
  * small kernel at the start of every call; the rest of the array keeps what the
  * last call left there.  All calls on one GPU share the array: calls that
  * overlap in time (different streams, graph replays on different streams) RACE
@@ -235,8 +235,8 @@ int ss_msa_attention_static(const void* q, const void* k_new, const void* v_new,
  * *n_splits = number of splits of the cached prefix that a sequence of
  * max_seq_len tokens has (1 = unsplit, no workspace needed; see
  * ss_msa_plan_splits for shorter ones), *n_kernels = 1 if the call is a single
- * kernel (unsplit, or two splits merged inside the attention kernel), 2 if a
- * merge kernel follows.
+ * kernel (unsplit, or splits that are merged inside the attention kernel: see
+ * ss_msa_set_merge_in_kernel), 2 if a merge kernel follows.
  * Either pointer may be NULL.  Host-only, no GPU work.  Returns SS_OK or the
  * error ss_msa_attention would return for the shape.
  */
@@ -284,11 +284,13 @@ int ss_msa_plan_launch(int B, int T, int gamma, int H, int Hkv, int D, int max_s
 int ss_msa_set_split_keys(int split_keys);
 
 /*
- * Tuning knob for a2 (MFMA path, problems split in two): merge the two splits
- * inside the attention kernel instead of in a second kernel (default: on).  The
- * split that finishes second adds the other's partial rows to its own and writes
- * `out`; the arithmetic is that of the merge kernel, so the result is the same
- * bit for bit and does not depend on which split finishes first.  The splits
+ * Tuning knob for a2 (MFMA path): merge the splits inside the attention kernel
+ * instead of in a second kernel (default: on) where that has 16 query rows per
+ * wave and the problem two splits, or three or four splits and at most 512 values
+ * per KV head and sequence (query rows x D).  The split that finishes last adds
+ * the others' partial rows to its own and writes `out`; the arithmetic is that of
+ * the merge kernel, so the result is the same bit for bit and does not depend on
+ * the order in which the splits finish.  The splits
  * find each other through arrival counters in front of the call's workspace
  * (see a2 for the zero-fill rule).  Calls of more than 8192 (sequence, KV head,
  * row chunk) items take the second kernel.  Returns the previous setting.

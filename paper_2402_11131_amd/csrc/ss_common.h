@@ -125,6 +125,29 @@ SS_DEV uint64_t ancestors_of(int node, int p) {
   }
   return bits;
 }
+// Maxima over a wavefront by register moves: rotations within rows of 16 lanes, then the row swaps.  A lane shuffle is a trip
+// through LDS, and a maximum of 64-bit keys is twelve of them one after the other.
+template <int ROR>
+SS_DEV uint32_t row_ror(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x120 + ROR, 0xf, 0xf, false);
+}
+template <typename Max>
+SS_DEV uint32_t wave_max(uint32_t v, Max max_of) {
+  v = max_of(v, row_ror<8>(v));
+  v = max_of(v, row_ror<4>(v));
+  v = max_of(v, row_ror<2>(v));
+  v = max_of(v, row_ror<1>(v));
+  const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  v = max_of(a[0], a[1]);
+  const auto c = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return max_of(c[0], c[1]);
+}
+SS_DEV uint32_t wave_max_u32(uint32_t v) {  // known to be uniform
+  return __builtin_amdgcn_readfirstlane(wave_max(v, [](uint32_t a, uint32_t b) { return a > b ? a : b; }));
+}
+SS_DEV float wave_max_f32(float v) {
+  return __uint_as_float(wave_max(__float_as_uint(v), [](uint32_t a, uint32_t b) { return __float_as_uint(fmaxf(__uint_as_float(a), __uint_as_float(b))); }));
+}
 // x / d for 0 <= x < 2^23, 0 < d: the rounded quotient is off by one at most.  Fewer than half the instructions of an
 // integer division, in kernels that last little longer than their start.
 SS_DEV int fast_div(int x, int d) {

@@ -27,8 +27,8 @@ struct MsaArgs {
   int n_qc;        // query-row chunks per (sequence, KV head) (MFMA path)
   int groups;      // wave groups per workgroup the plan asks for (MFMA path)
   int stages;      // ring stages per wave group the plan asks for (MFMA path)
-  unsigned int* arrive;  // MFMA path, two splits merged inside the kernel: arrival counters [B,Hkv,n_qc,kArriveTiles] in the
-                         // workspace (zero before the call, zero again after it), else NULL
+  unsigned int* arrive;  // MFMA path, splits merged inside the kernel (two, or a few of few rows): arrival counters
+                         // [B,Hkv,n_qc,kArriveTiles] in the workspace (zero before the call, zero again after it), else NULL
   float scale_log2;  // softmax scale times log2(e)
   uint32_t flags;
   int n_groups, n_stages;  // what the launch has of `groups` and `stages`
@@ -100,8 +100,8 @@ SS_DEV int wave_scan(int v, int lane) {  // inclusive
 SS_HD int cut_load(const MsaArgs& a, int U) { return max(U + a.new_units, 1); }
 SS_HD int cut_chunks(const MsaArgs& a, int kept) { return (a.g * kept * (1 + a.gamma) + a.chunk_rows - 1) / a.chunk_rows; }
 // Shortest and longest split that is considered, from the sum and the largest of the loads.  Rounding the sum down keeps
-// every candidate worth a look; what does not fit the slots is dropped by its cost (the merge inside the attention
-// kernel takes two splits of a sequence at most).
+// every candidate worth a look; what does not fit the slots is dropped by its cost (of launches that are cut the attention
+// kernel merges two splits of a sequence at most).
 struct CutRange {
   int lo, hi;
 };

@@ -25,22 +25,6 @@ namespace ss {
 // is fetched cold by every launch (eight: 11.9 -> 14.4 us).  RW = 8, 2 or 1 (see the launch).  Before and after, one layer:
 // 4 heads of 64, 128 cached tokens, 40 rows 15.0 -> 9.8 us; 8 heads of 64, 4 sequences of 500..1000 tokens, 192 rows (RW = 8)
 // 109 -> 92; 16 heads of 128, 8000 tokens, 40 rows 202 -> 150; 32 of 128 on 8, 4 sequences of 500..1000, 80 rows 331 -> 245.
-// Maximum over a wavefront by register moves (a lane shuffle is a trip through LDS).
-template <int ROR>
-SS_DEV float row_ror(float v) {
-  return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp((int)__float_as_uint(v), (int)__float_as_uint(v), 0x120 + ROR, 0xf, 0xf, false));
-}
-SS_DEV float wave_max_f32(float v) {
-  v = fmaxf(v, row_ror<8>(v));
-  v = fmaxf(v, row_ror<4>(v));
-  v = fmaxf(v, row_ror<2>(v));
-  v = fmaxf(v, row_ror<1>(v));
-  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-  const auto c = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return fmaxf(__uint_as_float(c[0]), __uint_as_float(c[1]));
-}
-
 template <int D, int RW>
 __global__ __launch_bounds__(256) void msa_f32_kernel(MsaArgs a) {
   constexpr int RC = 4 * RW, KT = 64, DL = D / 64;
@@ -503,7 +487,7 @@ static void set_plan(MsaArgs& a, const MsaPlan& plan, int B, int T, int gamma, i
   a.xcd_slots = plan.wide ? kWideSlots / 8 : 32; a.cut_fixed = plan.wide ? 8.f : 4.f; a.cut_piece = plan.wide ? 0.02f : 0.f;
 }
 
-// Whether a full call folds its two splits inside the attention kernel (see ss_msa_attention).
+// Whether a full call folds its splits inside the attention kernel (see msa_run).
 static bool merges_in_kernel(const MsaPlan& plan) {
   return g_merge_in_kernel.load() && plan.arrive_bytes > 0;
 }
@@ -618,9 +602,9 @@ static int msa_run(const char* fn, const void* q, const void* k_new, const void*
   a.page = page_size; a.page_shift = page_size == 16 ? 4 : (page_size == 32 ? 5 : 6);
   a.max_pages = max_pages_per_seq; a.num_pages = num_pages;
   a.scale_log2 = scale * 1.4426950408889634f;
-  // In-kernel merge (MFMA path, two splits): the second split of a (sequence, head) to finish adds the other's
-  // partial rows to its own and writes the output, which saves the merge kernel and its kernel boundary.  With
-  // more splits the partial rows would be fetched one split after the other and the merge kernel is faster.
+  // In-kernel merge (MFMA path, 16 rows per wave; two splits, or three and four of few rows: merges_few_rows): the last split
+  // of a (sequence, head) to finish adds the others' partial rows to its own and writes the output, which saves the merge kernel
+  // and its kernel boundary.  With more to fetch for one wave the merge kernel is faster.
   a.arrive = nullptr;
   if (merges_in_kernel(plan) && !(flags & SS_MSA_MERGE_ONLY))
     a.arrive = (unsigned int*)ws;

@@ -60,7 +60,6 @@
 #include <type_traits>
 
 #include "ss_msa_mfma.h"
-#include "ss_msa_wide.h"
 
 namespace ss {
 

@@ -13,7 +13,7 @@
 //
 // Scores are computed transposed, S^T = K Q^T, so that a lane holds 16 tokens of one query row; which token a row of the
 // score tile holds is chosen so that they are the k-slots the lane must supply to O^T += V^T P^T (wide_key).
-#pragma once
+#include <mutex>
 
 #include "ss_msa_mfma.h"
 

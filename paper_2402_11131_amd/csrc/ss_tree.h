@@ -12,19 +12,6 @@ struct TemplateArg {
   int8_t rank[SS_MAX_T];
 };
 
-// Maxima over a wavefront (the result is uniform) by register moves: rotations within rows of 16 lanes, then the row swaps.
-// A lane shuffle is a trip through LDS, and a maximum of 64-bit keys is twelve of them one after the other.
-template <int ROR>
-SS_DEV uint32_t row_max_step(uint32_t v) {
-  return max(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x120 + ROR, 0xf, 0xf, false));
-}
-SS_DEV uint32_t wave_max_u32(uint32_t v) {
-  v = row_max_step<1>(row_max_step<2>(row_max_step<4>(row_max_step<8>(v))));
-  const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-  v = max(a[0], a[1]);
-  const auto c = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-  return __builtin_amdgcn_readfirstlane(max(c[0], c[1]));
-}
 // The high words first; the low words only of the lanes that tie.
 SS_DEV uint64_t wave_max_u64(uint64_t v) {
   const uint32_t hi = (uint32_t)(v >> 32), top = wave_max_u32(hi);
