@@ -97,16 +97,10 @@ template <int D, int NW, bool STREAM, bool CUTS, bool FEW = false>
 __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves / NW : kMaxGroups)) void msa_bf16_kernel(MsaArgs args) {
   const int n_groups = args.n_groups, n_stages = args.n_stages;
   constexpr int KS = D / 32, DT = D / 16;
-  constexpr int K_BYTES = 32 * D * 2;          // K rows of a unit (V takes the same)
-  constexpr int STAGE_BYTES = 2 * K_BYTES;
-  constexpr int K_SLOTS = K_BYTES / 1024;      // 1 KB load slots of a unit's K rows (V: as many)
-  constexpr int LW = NW >= 4 ? 4 : NW >= 2 ? 2 : 1;  // waves of a group that move data: divides K_SLOTS
-  constexpr int KJ = K_SLOTS / LW;             // K slots per loading wave, and V slots per loading wave
-  constexpr int LPB = 2 * KJ;                  // loads per block and loading wave
-  constexpr int CPR = D / 8;                   // 16-byte chunks per K row
-  constexpr int ROWS_PER_SLOT = 64 / CPR;
-  constexpr int V_DBLK = K_SLOTS / 2;          // 32-feature blocks per 16-key half of the V tile
-  constexpr int VHALF = D * 32;                // bytes of one 16-key half of the V tile: D feature rows of 32 bytes
+  constexpr int LW = NW >= 4 ? 4 : NW >= 2 ? 2 : 1;  // waves of a group that move data: divides the slots of a block
+  using Slots = BlockSlots<D, LW>;
+  constexpr int K_BYTES = Slots::kKBytes, STAGE_BYTES = Slots::kStage, K_SLOTS = Slots::kSlots, KJ = Slots::KJ, LPB = Slots::kLoads;
+  constexpr int CPR = Slots::kPieces, ROWS_PER_SLOT = Slots::kRowsPerSlot, V_DBLK = Slots::kVBlocks, VHALF = Slots::kVHalf;
 
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   // smem: [n_groups][n_stages][STAGE_BYTES] ring stages, then [n_groups][n_extra][STAGE_BYTES] for more of the step's own
@@ -169,26 +163,9 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
   bool f_valid;
   uintx4 Qraw[KS];
 
-  // Rows c0 .. c0+31 of the step's own block -> LDS stage at st_addr: K rows as above, V rows token-major
-  // (row r at 2*D*r, chunk position p holding chunk p ^ 2*(r&3)) for the transposing operand read.  Rows past
-  // R repeat the last one (they are masked).  The lane id is laundered so that none of this arithmetic is
-  // kept in registers across the main loop.
-  auto dma_new = [&](const MsaArgs& a, int c0, uint32_t st_addr) {
-    int lane2 = lane;
-    asm volatile("" : "+v"(lane2));
-    const int ril2 = lane2 / CPR, pch2 = lane2 % CPR;
-    const size_t head0 = ((size_t)b * a.R * a.Hkv + hk) * D;  // elements to row 0 of this sequence and head
-    const uint16_t* kn = (const uint16_t*)a.k_new + head0;
-    const uint16_t* vn = (const uint16_t*)a.v_new + head0;
-#pragma unroll
-    for (int j = 0; j < KJ; ++j) {
-      const int sl = wl + LW * j;
-      const int rr = ROWS_PER_SLOT * sl + ril2;
-      const uint32_t row_off = (uint32_t)min(c0 + rr, a.R - 1) * (uint32_t)(a.Hkv * D * 2);
-      dma16<false>(kn, row_off + (uint32_t)((pch2 ^ k_swz<D>(rr)) * 16), st_addr + sl * 1024);
-      dma16<false>(vn, row_off + (uint32_t)((pch2 ^ (2 * (rr & 3))) * 16), st_addr + K_BYTES + sl * 1024);
-    }
-  };
+  // Rows c0 .. c0+31 of the step's own block -> LDS stage at st_addr.
+  auto swz = [](int row) { return k_swz<D>(row); };
+  auto dma_new = [&](const MsaArgs& a, int c0, uint32_t st_addr) { move_own<D, LW>(a, b, hk, c0, wl, lane, st_addr, swz); };
 
   // ---- which piece of work: XCD-aware order.  Workgroup ids go round-robin over
   // the 8 XCDs, so ids that are equal mod 8 share an L2: the query chunks of one
@@ -238,7 +215,6 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
   const MsaArgs& a = reread_args<CUTS>(args);
   const int R = a.R, T = a.T, F = a.g * R;
   const float c = a.scale_log2;
-  const size_t page_stride = (size_t)a.Hkv * a.page * D;  // elements per physical page (K and V alike)
   const uint16_t *k_head, *v_head;  // this head inside page 0
   const int pmask = a.page - 1;
   const int n_new_units = (R + 31) >> 5;
@@ -261,13 +237,7 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
   // Kept in four registers from here on: as a known constant the compiler would build it anew in every block.
   asm volatile("" : "+v"(ones));
 
-  // ---- how a block reaches LDS.  A unit is moved in 1 KB slots, one direct-to-LDS load each: K slot sl
-  // holds rows ROWS_PER_SLOT*sl + lane/CPR, the lane at chunk position p = lane%CPR fetching chunk
-  // p ^ k_swz(row).  The V tile consists of two halves of 16 keys, each D feature rows of 32 bytes; V slot
-  // s2 holds features dblk*32 + lane/2 of half s2 / V_DBLK (dblk = s2 % V_DBLK), the lane at position
-  // lane&1 fetching the 8-key chunk (lane&1) ^ ((feature >> 3) & 1), which makes the 16-lane operand reads
-  // (16 features x 16 bytes) hit 64 different banks.  In a feature-major page a slot is one contiguous KB.
-  // The first LW waves of a group move the data: wave wt takes K slots and V slots wt + LW*j.
+  // ---- how a full block of the prefix reaches LDS (see BlockSlots): the first LW waves of a group move the data
   const int ril = lane / CPR, pch = lane % CPR;
   // Slot sl lies in the second 16-key half of the unit when sl >= K_SLOTS / 2 (K and V alike); its offset inside
   // the half is part of the lane's byte offset, so that a half has one scalar base.
@@ -303,39 +273,9 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
 #pragma unroll
     for (int j = 0; j < KJ; ++j) dma16<STREAM>(second[j] ? vb : va, v_voff[j], slot_addr + K_BYTES + LW * j * 1024);
   };
-  // ---- the ragged last block of the prefix goes through registers (per-lane page lookups, clamped to
-  // existing keys; what is read in excess is masked).  base = its first cached token, last = the last one.
-  uintx4 stg[2 * KJ];
-  auto load_ragged = [&](int base, int last) {
-    int lane2 = lane;
-    asm volatile("" : "+v"(lane2));
-    const int ril2 = lane2 / CPR, pch2 = lane2 % CPR;
-#pragma unroll
-    for (int j = 0; j < KJ; ++j) {
-      const int sl = wl + LW * j;
-      const int rr = ROWS_PER_SLOT * sl + ril2;
-      const int key = min(base + rr, last);
-      const int pg = min(max(my_table[key >> a.page_shift], 0), a.num_pages - 1);
-      const uint16_t* ksrc = k_head + (size_t)pg * page_stride + (size_t)(key & pmask) * D;
-      const int half = sl / V_DBLK, dblk = sl % V_DBLK;
-      const int vkey = min(base + 16 * half + (lane2 & 1) * 8, last & ~7);
-      const int vpg = min(max(my_table[vkey >> a.page_shift], 0), a.num_pages - 1);
-      const uint16_t* vsrc = v_head + (size_t)vpg * page_stride + (size_t)(dblk * 32 + (lane2 >> 1)) * a.page + (vkey & pmask);
-      stg[j] = ld16(ksrc + ((pch2 ^ k_swz<D>(rr)) * 8));
-      stg[KJ + j] = ld16(vsrc);
-    }
-  };
-  auto store_ragged = [&](unsigned char* st) {
-    int lane2 = lane;
-    asm volatile("" : "+v"(lane2));
-#pragma unroll
-    for (int j = 0; j < KJ; ++j) {
-      const int sl = wl + LW * j;
-      *reinterpret_cast<uintx4*>(st + sl * 1024 + lane2 * 16) = stg[j];
-      const int half = sl / V_DBLK, fr = (sl % V_DBLK) * 32 + (lane2 >> 1);
-      *reinterpret_cast<uintx4*>(st + K_BYTES + half * VHALF + fr * 32 + (((lane2 & 1) ^ ((fr >> 3) & 1)) * 16)) = stg[KJ + j];
-    }
-  };
+  uintx4 stg[LPB];
+  auto load_ragged = [&](int base, int last) { load_ragged_block<D, LW>(a, my_table, k_head, v_head, base, last, wl, lane, stg, swz); };
+  auto store_ragged = [&](unsigned char* st) { store_ragged_block<D, LW>(st, wl, lane, stg); };
 
   // Split 0's first blocks of the step's own rows travel with the first round trip (their addresses need
   // nothing from memory), into the last ring stage, which the main loop does not fill before its first barrier, and the
@@ -351,8 +291,7 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
 
   // ---- where the device may cut the sequences: the lengths of all of them travel with the first trip, which goes out for
   // the host's cut: if that stands little is lost.  Otherwise one wave cuts anew and finds this workgroup's piece, and the
-  // trip is made again.  Pieces keep the order above: those of one sequence together, the splits of a head next to each
-  // other, the live row chunks of a (sequence, KV head, split) on one XCD.
+  // trip is made again.
   if constexpr (CUTS) {
     if (plan_is_even<16 * NW>(a, lane, lane_len, lane_kept)) {
       if (blockIdx.x == 0 && w == 0 && lane < a.B)
@@ -360,28 +299,7 @@ __global__ __launch_bounds__(64 * NW * (kMaxWaves / NW < kMaxGroups ? kMaxWaves 
       if (spare) return;
     } else {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing of the abandoned trip is under way to LDS
-      if (w == 0) {
-        const MsaArgs& a = reread_args<CUTS>(args);
-        const SeqCut r = plan_uneven(a, lane, len_units(lane_len, a), lane_kept);
-        const int slots = wave_scan(r.n, lane), groups0 = (slots - r.n) * a.Hkv;  // pieces of earlier sequences
-        const int skip = (groups0 + 7 - xcd) >> 3;    // this XCD takes the pieces that are xcd mod 8
-        const int here = (((slots * a.Hkv + 7 - xcd) >> 3) - skip) * r.chunks;
-        const int upto = wave_scan(here, lane);
-        const int bb = __popcll(__ballot(upto <= slot));
-        if (blockIdx.x == 0 && lane < a.B) a.cut_table[lane] = make_int2(r.n, slots - r.n);
-        if (lane == 0) cut[0] = bb;  // 64: none
-        if (lane == bb) {
-          const int at = slot - (upto - here);
-          const int piece = 8 * (skip + at / r.chunks) + xcd - groups0;
-          cut[1] = piece % r.n;
-          cut[2] = piece / r.n;
-          cut[3] = at % r.chunks;
-          cut[4] = r.n;
-          cut[5] = 32 * r.split0;
-          cut[6] = 32 * r.split;
-          cut[7] = slots - r.n;
-        }
-      }
+      if (w == 0) find_piece(reread_args<CUTS>(args), xcd, slot, lane, lane_len, lane_kept, cut);
       __syncthreads();
       b = __builtin_amdgcn_readfirstlane(cut[0]);
       if (b >= 64) return;

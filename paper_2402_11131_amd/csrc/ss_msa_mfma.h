@@ -117,4 +117,111 @@ SS_DEV const MsaArgs& reread_args(const MsaArgs& args) {
   return *(const MsaArgs*)p;
 }
 
+
+// ---- how blocks of 32 tokens reach an LDS stage.  A block is moved in 1 KB slots, one direct-to-LDS load each: K slot sl
+// holds rows kRowsPerSlot*sl + lane/kPieces, the lane at piece position p = lane%kPieces fetching piece p ^ swz(row).  The V
+// tile consists of two halves of 16 keys, each D feature rows of 32 bytes; V slot s2 holds features dblk*32 + lane/2 of half
+// s2 / kVBlocks (dblk = s2 % kVBlocks), the lane at position lane&1 fetching the 8-key piece (lane&1) ^ ((feature >> 3) & 1),
+// which makes the 16-lane operand reads (16 features x 16 bytes) hit 64 different banks.  In a feature-major page a slot is
+// one contiguous KB.  LW waves move the data: wave wl of them takes K slots and V slots wl + LW*j.  The full blocks of the
+// prefix are moved by the kernels' own code: through a function that both call, the compiler's schedule of the 16-row kernel's
+// main loop came out slower (two sequences of 8000 and 3001 tokens, 384 rows 38.9 -> 39.8 us).
+template <int D, int LW>
+struct BlockSlots {
+  static constexpr int kKBytes = 32 * D * 2;        // K rows of a block (V takes the same)
+  static constexpr int kStage = 2 * kKBytes;
+  static constexpr int kSlots = kKBytes / 1024;     // of K (V: as many)
+  static constexpr int KJ = kSlots / LW;            // K slots per loading wave, and V slots per loading wave
+  static constexpr int kLoads = 2 * KJ;             // loads per block and loading wave
+  static constexpr int kPieces = D / 8;             // 16-byte pieces per K row
+  static constexpr int kRowsPerSlot = 64 / kPieces;
+  static constexpr int kVBlocks = kSlots / 2;       // 32-feature blocks per 16-key half of the V tile
+  static constexpr int kVHalf = D * 32;             // bytes of one 16-key half of the V tile
+};
+
+// Rows c0 .. c0+31 of the step's own block -> the stage at st_addr: K rows as above, V rows token-major (row r at 2*D*r, piece
+// position p holding piece p ^ 2*(r&3)) for the transposing operand read.  Rows past R repeat the last one (they are masked).
+// The lane id is laundered, here and below, so that none of this arithmetic is kept in registers across the main loop.
+template <int D, int LW, typename Swz>
+SS_DEV void move_own(const MsaArgs& a, int b, int hk, int c0, int wl, int lane, uint32_t st_addr, Swz swz) {
+  using S = BlockSlots<D, LW>;
+  asm volatile("" : "+v"(lane));
+  const int ril = lane / S::kPieces, pch = lane % S::kPieces;
+  const size_t head0 = ((size_t)b * a.R * a.Hkv + hk) * D;  // elements to row 0 of this sequence and head
+  const uint16_t* kn = (const uint16_t*)a.k_new + head0;
+  const uint16_t* vn = (const uint16_t*)a.v_new + head0;
+#pragma unroll
+  for (int j = 0; j < S::KJ; ++j) {
+    const int sl = wl + LW * j;
+    const int rr = S::kRowsPerSlot * sl + ril;
+    const uint32_t row_off = (uint32_t)min(c0 + rr, a.R - 1) * (uint32_t)(a.Hkv * D * 2);
+    dma16<false>(kn, row_off + (uint32_t)((pch ^ swz(rr)) * 16), st_addr + sl * 1024);
+    dma16<false>(vn, row_off + (uint32_t)((pch ^ (2 * (rr & 3))) * 16), st_addr + S::kKBytes + sl * 1024);
+  }
+}
+// The ragged last block of the prefix goes through registers (per-lane page lookups, clamped to existing keys; what is read in
+// excess is masked).  base = its first cached token, last = the last one.
+template <int D, int LW, typename Swz>
+SS_DEV void load_ragged_block(const MsaArgs& a, const int32_t* my_table, const uint16_t* k_head, const uint16_t* v_head, int base,
+                              int last, int wl, int lane, uintx4 (&stg)[BlockSlots<D, LW>::kLoads], Swz swz) {
+  using S = BlockSlots<D, LW>;
+  const size_t page_stride = (size_t)a.Hkv * a.page * D;  // elements per physical page (K and V alike)
+  const int pmask = a.page - 1;
+  asm volatile("" : "+v"(lane));
+  const int ril = lane / S::kPieces, pch = lane % S::kPieces;
+#pragma unroll
+  for (int j = 0; j < S::KJ; ++j) {
+    const int sl = wl + LW * j;
+    const int rr = S::kRowsPerSlot * sl + ril;
+    const int key = min(base + rr, last);
+    const int pg = min(max(my_table[key >> a.page_shift], 0), a.num_pages - 1);
+    const uint16_t* ksrc = k_head + (size_t)pg * page_stride + (size_t)(key & pmask) * D;
+    const int half = sl / S::kVBlocks, dblk = sl % S::kVBlocks;
+    const int vkey = min(base + 16 * half + (lane & 1) * 8, last & ~7);
+    const int vpg = min(max(my_table[vkey >> a.page_shift], 0), a.num_pages - 1);
+    const uint16_t* vsrc = v_head + (size_t)vpg * page_stride + (size_t)(dblk * 32 + (lane >> 1)) * a.page + (vkey & pmask);
+    stg[j] = ld16(ksrc + ((pch ^ swz(rr)) * 8));
+    stg[S::KJ + j] = ld16(vsrc);
+  }
+}
+template <int D, int LW>
+SS_DEV void store_ragged_block(unsigned char* st, int wl, int lane, const uintx4 (&stg)[BlockSlots<D, LW>::kLoads]) {
+  using S = BlockSlots<D, LW>;
+  asm volatile("" : "+v"(lane));
+#pragma unroll
+  for (int j = 0; j < S::KJ; ++j) {
+    const int sl = wl + LW * j;
+    *reinterpret_cast<uintx4*>(st + sl * 1024 + lane * 16) = stg[j];
+    const int half = sl / S::kVBlocks, fr = (sl % S::kVBlocks) * 32 + (lane >> 1);
+    *reinterpret_cast<uintx4*>(st + S::kKBytes + half * S::kVHalf + fr * 32 + (((lane & 1) ^ ((fr >> 3) & 1)) * 16)) = stg[S::KJ + j];
+  }
+}
+
+// One wavefront cuts a batch anew and finds the piece of the workgroup in `slot` of XCD `xcd`; lane b holds sequence b's length
+// and kept nodes.  Pieces keep the order of the host's cut: those of one sequence together, the splits of a head next to each
+// other, the live row chunks of a (sequence, KV head, split) on one XCD.  Workgroup 0 leaves the table of cuts.
+// cut [8]: sequence (64: no piece), split, KV head, row chunk, splits of the sequence, tokens of split 0 and of the others,
+// the sequence's first slot.
+SS_DEV void find_piece(const MsaArgs& a, int xcd, int slot, int lane, int lane_len, int lane_kept, int* cut) {
+  const SeqCut r = plan_uneven(a, lane, len_units(lane_len, a), lane_kept);
+  const int slots = wave_scan(r.n, lane), groups0 = (slots - r.n) * a.Hkv;  // pieces of earlier sequences
+  const int skip = (groups0 + 7 - xcd) >> 3;    // this XCD takes the pieces that are xcd mod 8
+  const int here = (((slots * a.Hkv + 7 - xcd) >> 3) - skip) * r.chunks;
+  const int upto = wave_scan(here, lane);
+  const int bb = __popcll(__ballot(upto <= slot));
+  if (blockIdx.x == 0 && lane < a.B) a.cut_table[lane] = make_int2(r.n, slots - r.n);
+  if (lane == 0) cut[0] = bb;  // 64: none
+  if (lane == bb) {
+    const int at = slot - (upto - here);
+    const int piece = 8 * (skip + at / r.chunks) + xcd - groups0;
+    cut[1] = piece % r.n;
+    cut[2] = piece / r.n;
+    cut[3] = at % r.chunks;
+    cut[4] = r.n;
+    cut[5] = 32 * r.split0;
+    cut[6] = 32 * r.split;
+    cut[7] = slots - r.n;
+  }
+}
+
 }  // namespace ss

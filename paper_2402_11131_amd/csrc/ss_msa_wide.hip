@@ -33,13 +33,11 @@ SS_DEV int wide_swz(int row) { return row & 15; }
 template <int D, int NW, bool STREAM, bool CUTS>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2))) void msa_bf16_wide_kernel(MsaArgs args) {
   constexpr int KS = D / 16, DT = D / 32;
-  constexpr int K_BYTES = 32 * D * 2, STAGE = 2 * K_BYTES;
   constexpr int NS = NW;                       // ring stages: the waves' output tiles take their place at the end
-  constexpr int K_SLOTS = K_BYTES / 1024;      // 1 KB load slots of a block's K rows (V: as many)
   constexpr int LW = NW == 4 ? 4 : 2;          // waves that move data
-  constexpr int KJ = K_SLOTS / LW, LPB = 2 * KJ;
-  constexpr int CPR = D / 8, ROWS_PER_SLOT = 64 / CPR;
-  constexpr int V_DBLK = K_SLOTS / 2, VHALF = D * 32;
+  using Slots = BlockSlots<D, LW>;
+  constexpr int K_BYTES = Slots::kKBytes, STAGE = Slots::kStage, K_SLOTS = Slots::kSlots, KJ = Slots::KJ, LPB = Slots::kLoads;
+  constexpr int CPR = Slots::kPieces, ROWS_PER_SLOT = Slots::kRowsPerSlot, V_DBLK = Slots::kVBlocks, VHALF = Slots::kVHalf;
   constexpr int ROWS = 32 * NW;
 
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // [NS][STAGE] | cut
@@ -72,22 +70,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
   bool f_valid;
   uintx4 Qraw[KS];
 
-  auto dma_new = [&](const MsaArgs& a, int c0, uint32_t st_addr) {
-    int lane2 = lane;
-    asm volatile("" : "+v"(lane2));
-    const int ril2 = lane2 / CPR, pch2 = lane2 % CPR;
-    const size_t head0 = ((size_t)b * a.R * a.Hkv + hk) * D;
-    const uint16_t* kn = (const uint16_t*)a.k_new + head0;
-    const uint16_t* vn = (const uint16_t*)a.v_new + head0;
-#pragma unroll
-    for (int j = 0; j < KJ; ++j) {
-      const int sl = wl + LW * j;
-      const int rr = ROWS_PER_SLOT * sl + ril2;
-      const uint32_t row_off = (uint32_t)min(c0 + rr, a.R - 1) * (uint32_t)(a.Hkv * D * 2);
-      dma16<false>(kn, row_off + (uint32_t)((pch2 ^ wide_swz(rr)) * 16), st_addr + sl * 1024);
-      dma16<false>(vn, row_off + (uint32_t)((pch2 ^ (2 * (rr & 3))) * 16), st_addr + K_BYTES + sl * 1024);
-    }
-  };
+  auto swz = [](int row) { return wide_swz(row); };
+  auto dma_new = [&](const MsaArgs& a, int c0, uint32_t st_addr) { move_own<D, LW>(a, b, hk, c0, wl, lane, st_addr, swz); };
 
   const int G = args.B * args.Hkv * args.n_splits;
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
@@ -134,7 +118,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const MsaArgs& a = reread_args<CUTS>(args);
   const int R = a.R, T = a.T;
   const float c = a.scale_log2;
-  const size_t page_stride = (size_t)a.Hkv * a.page * D;
   const uint16_t *k_head, *v_head;
   const int pmask = a.page - 1;
 
@@ -162,37 +145,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 #pragma unroll
     for (int j = 0; j < KJ; ++j) dma16<STREAM>(second[j] ? vb : va, v_voff[j], slot_addr + K_BYTES + LW * j * 1024);
   };
-  uintx4 stg[2 * KJ];
-  auto load_ragged = [&](int base, int last) {
-    int lane2 = lane;
-    asm volatile("" : "+v"(lane2));
-    const int ril2 = lane2 / CPR, pch2 = lane2 % CPR;
-#pragma unroll
-    for (int j = 0; j < KJ; ++j) {
-      const int sl = wl + LW * j;
-      const int rr = ROWS_PER_SLOT * sl + ril2;
-      const int key = min(base + rr, last);
-      const int pg = min(max(my_table[key >> a.page_shift], 0), a.num_pages - 1);
-      const uint16_t* ksrc = k_head + (size_t)pg * page_stride + (size_t)(key & pmask) * D;
-      const int half = sl / V_DBLK, dblk = sl % V_DBLK;
-      const int vkey = min(base + 16 * half + (lane2 & 1) * 8, last & ~7);
-      const int vpg = min(max(my_table[vkey >> a.page_shift], 0), a.num_pages - 1);
-      const uint16_t* vsrc = v_head + (size_t)vpg * page_stride + (size_t)(dblk * 32 + (lane2 >> 1)) * a.page + (vkey & pmask);
-      stg[j] = ld16(ksrc + ((pch2 ^ wide_swz(rr)) * 8));
-      stg[KJ + j] = ld16(vsrc);
-    }
-  };
-  auto store_ragged = [&](unsigned char* st) {
-    int lane2 = lane;
-    asm volatile("" : "+v"(lane2));
-#pragma unroll
-    for (int j = 0; j < KJ; ++j) {
-      const int sl = wl + LW * j;
-      *reinterpret_cast<uintx4*>(st + sl * 1024 + lane2 * 16) = stg[j];
-      const int half = sl / V_DBLK, fr = (sl % V_DBLK) * 32 + (lane2 >> 1);
-      *reinterpret_cast<uintx4*>(st + K_BYTES + half * VHALF + fr * 32 + (((lane2 & 1) ^ ((fr >> 3) & 1)) * 16)) = stg[KJ + j];
-    }
-  };
+  uintx4 stg[LPB];
+  auto load_ragged = [&](int base, int last) { load_ragged_block<D, LW>(a, my_table, k_head, v_head, base, last, wl, lane, stg, swz); };
+  auto store_ragged = [&](unsigned char* st) { store_ragged_block<D, LW>(st, wl, lane, stg); };
 
   bool has_new = s == 0 && !spare && qc * ROWS < a.g * R_kept;
   const int n_new_pre = min(n_new_units, NS - 1);
@@ -209,28 +164,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
       if (spare) return;
     } else {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing of the abandoned trip is under way to LDS
-      if (w == 0) {
-        const MsaArgs& a = reread_args<CUTS>(args);
-        const SeqCut r = plan_uneven(a, lane, len_units(lane_len, a), lane_kept);
-        const int slots = wave_scan(r.n, lane), groups0 = (slots - r.n) * a.Hkv;  // pieces of earlier sequences
-        const int skip = (groups0 + 7 - xcd) >> 3;    // this XCD takes the pieces that are xcd mod 8
-        const int here = (((slots * a.Hkv + 7 - xcd) >> 3) - skip) * r.chunks;
-        const int upto = wave_scan(here, lane);
-        const int bb = __popcll(__ballot(upto <= slot));
-        if (blockIdx.x == 0 && lane < a.B) a.cut_table[lane] = make_int2(r.n, slots - r.n);
-        if (lane == 0) cut[0] = bb;  // 64: none
-        if (lane == bb) {
-          const int at = slot - (upto - here);
-          const int piece = 8 * (skip + at / r.chunks) + xcd - groups0;
-          cut[1] = piece % r.n;
-          cut[2] = piece / r.n;
-          cut[3] = at % r.chunks;
-          cut[4] = r.n;
-          cut[5] = 32 * r.split0;
-          cut[6] = 32 * r.split;
-          cut[7] = slots - r.n;
-        }
-      }
+      if (w == 0) find_piece(reread_args<CUTS>(args), xcd, slot, lane, lane_len, lane_kept, cut);
       __syncthreads();
       b = __builtin_amdgcn_readfirstlane(cut[0]);
       if (b >= 64) return;
