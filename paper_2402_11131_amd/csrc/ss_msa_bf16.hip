@@ -60,6 +60,7 @@
 #include <type_traits>
 
 #include "ss_msa_mfma.h"
+#include "ss_msa_wide.h"
 
 namespace ss {
 
@@ -775,6 +776,25 @@ static int launch_d(const MsaArgs& a, hipStream_t stream) {
 int launch_msa_bf16(const MsaArgs& a, hipStream_t stream) {
   if (a.D == 128) return launch_d<128>(a, stream);
   return launch_d<64>(a, stream);
+}
+
+// ------------------------------------------------------------------ 32 query rows per wave (ss_msa_wide.h)
+// Folded query rows one workgroup takes where a KV head has more than 80: 128 or 96, whichever pads less.
+int msa_bf16_wide_rows(int F) { return ceil_div(F, 96) * 96 < ceil_div(F, 128) * 128 ? 96 : 128; }
+
+// One ring of as many stages as there are waves, whose output tiles take its place at the end.
+MsaLaunch msa_bf16_wide_launch(const MsaArgs& a) {
+  MsaLaunch l;
+  l.wgs = (long)ceil_div(a.B * a.Hkv * a.n_splits, 8) * 8 * a.n_qc;
+  l.groups = 1;
+  l.waves = l.stages = a.chunk_rows / 32;
+  l.extra = 0;
+  l.lds = (size_t)l.stages * 128 * a.D + 8 * sizeof(int);
+  return l;
+}
+
+int launch_msa_bf16_wide(const MsaArgs& a, hipStream_t stream) {
+  return a.chunk_rows == 128 ? launch_wide_dn<128, 4>(a, stream) : launch_wide_dn<128, 3>(a, stream);
 }
 
 }  // namespace ss

@@ -1,5 +1,6 @@
 // a2, bf16 path for large problems with many query rows per KV head (wide_fits in ss_msa.hip): multi-stream attention
-// (Eq. 1 / Eq. 2) with 32 query rows per wave on v_mfma_f32_32x32x16_bf16.
+// (Eq. 1 / Eq. 2) with 32 query rows per wave on v_mfma_f32_32x32x16_bf16: the kernel and its launch, instantiated in
+// ss_msa_bf16.hip.
 //
 // What binds these launches is arithmetic: K and V of a KV head are wanted by several row chunks and come from the L2.  With
 // 16 rows per wave (ss_msa_bf16.hip) sixteen waves read every K and V tile out of LDS for 16 rows each and meet at one
@@ -13,6 +14,7 @@
 //
 // Scores are computed transposed, S^T = K Q^T, so that a lane holds 16 tokens of one query row; which token a row of the
 // score tile holds is chosen so that they are the k-slots the lane must supply to O^T += V^T P^T (wide_key).
+#pragma once
 #include <mutex>
 
 #include "ss_msa_mfma.h"
@@ -444,20 +446,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
   if (f_valid && lh == 0) a.part_lse[part_row_of<CUTS>(a, b, slot0, s, q_h, q_r)] = my_lse;
 }
 
-// Folded query rows one workgroup takes where a KV head has more than 80: 128 or 96, whichever pads less.
-int msa_bf16_wide_rows(int F) { return ceil_div(F, 96) * 96 < ceil_div(F, 128) * 128 ? 96 : 128; }
-
-// One ring of as many stages as there are waves, whose output tiles take its place at the end.
-MsaLaunch msa_bf16_wide_launch(const MsaArgs& a) {
-  MsaLaunch l;
-  l.wgs = (long)ceil_div(a.B * a.Hkv * a.n_splits, 8) * 8 * a.n_qc;
-  l.groups = 1;
-  l.waves = l.stages = a.chunk_rows / 32;
-  l.extra = 0;
-  l.lds = (size_t)l.stages * 128 * a.D + 8 * sizeof(int);
-  return l;
-}
-
 template <int D, int NW, bool STREAM, bool CUTS>
 static int launch_wide_dns(const MsaArgs& a, hipStream_t stream) {
   const MsaLaunch l = msa_bf16_wide_launch(a);
@@ -479,10 +467,6 @@ static int launch_wide_dn(const MsaArgs& a, hipStream_t stream) {
   if constexpr (NW == 3)
     if (a.n_qc == 1) return launch_wide_dns<D, NW, true, false>(a, stream);
   return a.adaptive ? launch_wide_dns<D, NW, false, true>(a, stream) : launch_wide_dns<D, NW, false, false>(a, stream);
-}
-
-int launch_msa_bf16_wide(const MsaArgs& a, hipStream_t stream) {
-  return a.chunk_rows == 128 ? launch_wide_dn<128, 4>(a, stream) : launch_wide_dn<128, 3>(a, stream);
 }
 
 }  // namespace ss
