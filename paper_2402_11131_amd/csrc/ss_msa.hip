@@ -415,14 +415,23 @@ static MsaPlan make_plan(int B, int R, int H, int Hkv, int D, int max_len, int d
     // worth of time.  It gets that much less of the prefix; the others take whole iterations of all wave
     // groups where that leaves split 0 something.  Where it does not they take what they must (one sequence of 2048 tokens
     // with 80 rows in 8 splits: one block and 7 x 9 instead of 8 x 8, 20.5 -> 20.0 us; 16 heads 19.9 -> 18.7, heads of 64
-    // 16.3 -> 15.5), with one block of `extra` less: with as many, 40 rows got splits of 9 blocks too, 18.0 -> 18.6 us.
+    // 16.3 -> 15.5), with one block of `extra` less: with as many, 40 rows got splits of 9 blocks too, 18.0 -> 18.6 us.  This
+    // only if split 0 then has fewer blocks than in equal splits (39 shapes against equal splits, means over tables that are a
+    // quarter to all full: 0.4 to 8 % faster where it has less, 1 to 3 % slower with one block more, 5 to 8 % with two and
+    // more; 16 heads, 8320 tokens, 60 rows 20.8 us with 17 in each, 22.3 with 20 and 15 x 16).
     const int nu = ceil_div(len, 32), n = p.n_splits, extra = ceil_div(R, 32) + split0_extra_blocks();
-    int rest = (nu + extra + n / 2) / n;
+    int rest = (nu + extra + n / 2) / n, most = nu;  // blocks of the others, most of split 0
     const int whole = (rest + p.groups / 2) / p.groups * p.groups;
-    rest = nu - (n - 1) * whole >= 1 ? whole : (nu + extra - 1 + n / 2) / n;
-    if (rest >= 2 && nu - (n - 1) * rest >= 1) {
+    if (nu - (n - 1) * whole >= 1) {
+      rest = whole;
+    } else {
+      rest = (nu + extra - 1 + n / 2) / n;
+      most = split_keys / 32 - 1;
+    }
+    const int rest0 = nu - (n - 1) * rest;
+    if (rest >= 2 && rest0 >= 1 && rest0 <= most) {
       p.split_keys = 32 * rest;
-      p.split0_keys = 32 * (nu - (n - 1) * rest);
+      p.split0_keys = 32 * rest0;
     }
   }
   // Cutting on the device needs slots to deal out and a lane per sequence; a caller's split length stays.  With one

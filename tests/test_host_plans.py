@@ -206,3 +206,17 @@ def test_splits_of_long_trees_by_their_cost():
                   (2, 59, 6, 48, 8, 9600)):
         assert plan(*shape) == (16, 1), shape           # as many rounds of 80 rows as of 96
     assert plan(12, 37, 6, 32, 4, 12288)[0] == 32       # the same rows, longer: that kernel would cut them in eight
+
+
+def test_split_0_takes_no_more_than_an_equal_share():
+    # it scans the step's own rows besides
+    def blocks(shape):   # of split 0, of an equal share
+        one = lambda u: api.ss_msa_plan_splits(*shape, api.SS_BF16, [32 * u] * shape[0])[1][0] == 1
+        n, nu = api.ss_msa_plan(*shape, api.SS_BF16)[0], shape[6] // 32
+        assert n > 1
+        return max(u for u in range(1, nu + 1) if one(u)), -(-nu // n)
+    for shape in ((1, 15, 3, 16, 16, 128, 8320), (2, 1, 5, 40, 8, 64, 9376), (1, 9, 4, 16, 16, 64, 6272), (6, 2, 3, 32, 4, 128, 2368),
+                  (1, 9, 3, 32, 8, 128, 3584), (1, 4, 3, 16, 16, 128, 2912)):
+        own, share = blocks(shape)
+        assert own <= share, (shape, own, share)
+    assert blocks((1, 16, 4, 32, 32, 128, 2048)) == (1, 8) and blocks((2, 6, 4, 32, 8, 128, 3712)) == (8, 9)   # less, where the others can take it
