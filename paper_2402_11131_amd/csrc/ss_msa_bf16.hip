@@ -698,11 +698,14 @@ static int stages_for(int n_groups, int wanted, size_t stage_bytes, int lpb) {
 
 // Stages for the step's own rows beyond one per group (their later blocks need no trip of their own then), where they cost no
 // residency: the launch has a workgroup per compute unit at most, or as many fit one as without them.  What fits is bounded by
-// 160 KB of LDS and, for heads of 64, by six waves per SIMD (73 registers or more; heads of 128 fill the LDS alone).
+// 160 KB of LDS and, for heads of 64, by six waves per SIMD (73 registers or more; heads of 128 fill the LDS alone).  Of 15
+// waves only one workgroup runs at a time, but the next one starts as soon as two of the three groups have left and its ring
+// fits beside the old one.
 // Us per layer with a stage more wherever 144 KB of ring allow it and by this rule, heads of 64: 576 rows in nine chunks of 64
 // (12 waves, 74 KB or 98), 8 x 4096 tokens 185 and 133; 192 rows in three, 16 x 4096 75 and 62, 32 x 512 35 and 27; 525 rows in
-// eleven of 48, 16 x 4096 226 and 218.  Without any: 640 rows in five of 128 (16 waves) 110 and 106, 80 rows (10 waves) of 7 x 32
-// heads x 2048 40 and 37; one sequence of 2048 tokens, heads of 128, 22.7 and 22.1.
+// eleven of 48, 16 x 4096 226 and 218; 915 rows in twelve of 80 (15 waves), 6 x 3200 122.7 and 119.8, 800 rows in ten, 4 x 2048
+// 56.7 and 53.7.  Without any: 640 rows in five of 128 (16 waves) 110 and 106, 384 rows in three, 2 x 2800 of 4096 34.5 and
+// 33.6, 80 rows (10 waves) of 7 x 32 heads x 2048 40 and 37; one sequence of 2048 tokens, heads of 128, 22.7 and 22.1.
 MsaLaunch msa_bf16_launch(const MsaArgs& a) {
   const int nw = a.chunk_rows / 16, lw = nw >= 4 ? 4 : nw >= 2 ? 2 : 1;
   const size_t stage_bytes = 2 * 32 * (size_t)a.D * 2;
@@ -716,7 +719,10 @@ MsaLaunch msa_bf16_launch(const MsaArgs& a) {
     const size_t ring = (size_t)l.groups * (l.stages + extra) * stage_bytes;
     return (ring > merge_bytes ? ring : merge_bytes) + 8 * sizeof(int) + (size_t)l.waves * 32 * 4;
   };
-  auto resident = [&](int extra) { const int by_lds = (int)(160 * 1024 / lds(extra)), by_waves = 24 / l.waves; return by_lds < by_waves ? by_lds : by_waves; };
+  auto resident = [&](int extra) {
+    const int by_lds = (int)(160 * 1024 / lds(extra)), by_waves = l.groups > 2 ? 2 : 24 / l.waves;
+    return by_lds < by_waves ? by_lds : by_waves;
+  };
   l.extra = 0;
   if (l.groups > 1)
     while (l.extra + 1 < ceil_div(ceil_div(a.R, 32), l.groups) && (size_t)l.groups * (l.stages + l.extra + 1) * stage_bytes <= 144 * 1024 &&

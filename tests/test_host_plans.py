@@ -180,7 +180,8 @@ def test_shapes_of_the_uneven_batches_are_of_the_kind_they_stand_for():
 def test_stages_for_the_own_rows_cost_no_resident_workgroup():
     # heads of 64 in several row chunks of nine to twelve waves: two workgroups fit a compute unit's 160 KB, whatever the tree
     # (more of the step's own rows get stages only where no workgroup goes for them)
-    for T, gamma, H, rows, waves in ((21, 4, 40, 48, 9), (64, 2, 8, 64, 12), (64, 8, 8, 64, 12)):
+    # (of fifteen waves the second one's ring, for it to start while the first one's last group is still at work)
+    for T, gamma, H, rows, waves in ((21, 4, 40, 48, 9), (64, 2, 8, 64, 12), (64, 8, 8, 64, 12), (61, 2, 40, 80, 15), (50, 5, 8, 80, 15)):
         p = api.ss_msa_plan_launch(16, T, gamma, H, 8, 64, 4096)
         assert (p["rows_per_wave"], p["rows"], p["waves"]) == (16, rows, waves) and p["workgroups"] > 256
         assert 2 * p["lds"] <= 160 * 1024, p
