@@ -33,6 +33,7 @@ struct MsaArgs {
   uint32_t flags;
   int n_groups, n_stages;  // what the launch has of `groups` and `stages`
   int n_extra;             // stages per wave group for more blocks of the step's own rows (MFMA path)
+  int by_split;            // whether the split is the slowest index of the workgroups (MFMA path)
   // last, so that kernels that do not cut read no more of the arguments than they need
   int2* cut_table;  // [B] adaptive calls: splits and first slot of every sequence, which workgroup 0 of the attention
                     // kernel leaves in the workspace for the merge kernel; else NULL
@@ -200,10 +201,11 @@ int launch_msa_bf16(const MsaArgs& a, hipStream_t stream);
 // Query rows per workgroup chunk the MFMA path uses for F = g*R folded rows.
 int msa_bf16_rows_per_chunk(int F);
 // The launch of that kernel: workgroups, wave groups of each, ring stages per group, stages per group for more of the step's
-// own rows, waves and bytes of LDS per workgroup.
+// own rows, waves and bytes of LDS per workgroup; whether the split is the slowest index of the workgroups.
 struct MsaLaunch {
   long wgs;
   int groups, stages, extra, waves;
+  bool by_split;
   size_t lds;
 };
 MsaLaunch msa_bf16_launch(const MsaArgs& a);
