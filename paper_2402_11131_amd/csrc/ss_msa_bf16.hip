@@ -735,12 +735,13 @@ MsaLaunch msa_bf16_launch(const MsaArgs& a) {
   l.lds = lds(l.extra);
   // Workgroups i and i + 256 share a compute unit, and of sequences shorter than the table the last splits leave at once.  With
   // the split as the fastest index those are among the first 256, and units that are given two have two with work to do.
-  // Twelve waves (heads of 64 in chunks of 64 rows), us per layer with the split fastest and slowest: 2 sequences x 40 heads on 8,
-  // 34 rows, half of 2688 tokens (288 workgroups) 17.1 and 13.6; 40 shapes of 264 to 384 workgroups, a third to all of the table
-  // used, 0.99 to 1.37 times as fast, 1.11 on average.  Others as they are: the split slowest is faster there too where tables
-  // are partly used (up to 1.7 times), but 2 to 7 % slower for full tables of four and more splits, and with up to 256
-  // workgroups, which have a unit each, 0.93 to 1.1 times as fast.
-  l.by_split = a.D == 64 && l.waves == 12 && l.wgs > 256;
+  // Ten and twelve waves (heads of 64, 80 rows in one chunk or chunks of 64), us per layer with the split fastest and slowest: 2
+  // sequences x 40 heads on 8, 34 rows, half of 2688 tokens (288 workgroups) 17.1 and 13.6; 280 shapes of 264 to 500
+  // workgroups, a third to all of the table used, 0.95 (full tables of many splits) to 1.44 times as fast, 1.14 on average.
+  // Others as they are: the split slowest is faster there too where tables are partly used (up to 1.7 times), but 2 to 7 %
+  // slower for full tables of four and more splits, and with up to 256 workgroups, which have a unit each, 0.93 to 1.1 times
+  // as fast.
+  l.by_split = a.D == 64 && (l.waves == 10 || l.waves == 12) && l.wgs > 256;
   return l;
 }
 

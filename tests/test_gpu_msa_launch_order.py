@@ -1,4 +1,4 @@
-"""Launches of twelve waves and more workgroups than compute units, whose workgroups come in order of the splits: batches of
+"""Launches of ten and twelve waves (heads of 64) and more workgroups than compute units, whose workgroups come in order of the splits: batches of
 full, partly filled and empty tables against the oracle, with groups that are no multiple of eight, and bit for bit what the
 attention and the merge kernel give as two calls."""
 import numpy as np
@@ -13,18 +13,19 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 CASES = {
-    # B, H, Hkv, T, gamma, page, tokens of the table, lens -> splits, workgroups
-    "three_chunks": (3, 15, 5, 12, 4, 16, 1536, [1536, 700, 33], 6, 288),
-    "two_splits": (3, 27, 27, 32, 5, 64, 768, [768, 0, 385], 2, 504),
-    "one_split": (10, 18, 9, 16, 5, 32, 480, [480, 479, 1, 0, 31, 32, 33, 300, 64, 17], 1, 288),
+    # B, H, Hkv, T, gamma, page, tokens of the table, lens -> waves, splits, workgroups
+    "three_chunks": (3, 15, 5, 12, 4, 16, 1536, [1536, 700, 33], 12, 6, 288),
+    "two_splits": (3, 27, 27, 32, 5, 64, 768, [768, 0, 385], 12, 2, 504),
+    "one_split": (10, 18, 9, 16, 5, 32, 480, [480, 479, 1, 0, 31, 32, 33, 300, 64, 17], 12, 1, 288),
+    "one_chunk": (3, 30, 30, 12, 5, 16, 1024, [1024, 340, 0], 10, 3, 272),
 }
 
 
 @pytest.mark.parametrize("name", list(CASES))
 def test_order_of_the_splits(name):
-    B, H, Hkv, T, gamma, page, cap, lens, splits, wgs = CASES[name]
+    B, H, Hkv, T, gamma, page, cap, lens, waves, splits, wgs = CASES[name]
     p = api.ss_msa_plan_launch(B, T, gamma, H, Hkv, 64, cap)
-    assert (p["waves"], p["n_splits"], p["workgroups"]) == (12, splits, wgs)
+    assert (p["waves"], p["n_splits"], p["workgroups"]) == (waves, splits, wgs)
     cfg = synth.scaled(synth.CONFIGS["c2"], B=B, H=H, Hkv=Hkv, D=64, page=page, T=T, gamma=gamma, branching=(4, 4, 4), max_depth=3,
                        L_min=cap, L_max=cap)
     inp = synth.make_msa_inputs(cfg, 7)
